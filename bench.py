@@ -161,13 +161,16 @@ def roofline(kernel, stats, kms, kln, bits, q, workload):
             kname, vcfg = "k_verify_bidir", "<%d, %d>" % (last["verify_words"], planes)
         elif last["verify_group"] == -3:  # each pair's window by its band class
             kname, vcfg = "k_verify_classes", "<%d>" % planes
+        elif last["verify_group"] == -4:  # the skewed band
+            kname, vcfg = "k_verify_ring", "<%d>" % planes
         else:
             kname = "k_verify_persist"
             vcfg = "<%d, %d, %d>" % (last["verify_words"], last["verify_group"], planes)
         r.update(kernel=kname + vcfg, bound="alu", unit="Tops/s",
                  achieved=ops / secs / 1e12, peak=INT_PEAK_TOPS,
                  band_cells_per_s=cells / secs)
-        r["traffic"] = measured_traffic(workload, r["kernel"], os.path.join(csrc, "verify_lg.hip"))
+        src = "verify_ring.hip" if last["verify_group"] == -4 else "verify_lg.hip"
+        r["traffic"] = measured_traffic(workload, r["kernel"], os.path.join(csrc, src))
     elif kernel == "anchors":
         per_pos = 10 if q * bits <= 12 else 42
         r.update(kernel="k_anchor_tiles<%s>" % ("uint32_t" if per_pos == 10 else "uint64_t"),

@@ -128,7 +128,8 @@ typedef struct {
     int64_t positions;   /* symbols scanned by the anchor kernel, over all repetitions */
     int32_t verify_group;  /* lanes per pair of the batched verifier (0: plain; -2: two
                               lanes splitting the text columns, forward and reversed; -3:
-                              per-pair band classes) */
+                              per-pair band classes; -4: the skewed band, whose pairs hold
+                              8 to 32 lanes by band class) */
     int32_t verify_words;  /* band words per lane of the batched verifier */
     int32_t verify_blocks; /* most workgroups the batched verifier's persistent launch may
                               have (fewer when the pairs need fewer) */

@@ -114,15 +114,16 @@ extern "C" mj_status mj_ctx_set_streaming(mj_ctx *ctx, int mode) {
 
 // ---------------------------------------------------------------- helpers
 // The verify_lanes / verify_group code of a batched configuration: lanes per pair, -2 for
-// the column split, -3 for the band classes.
+// the column split, -3 for the band classes, -4 for the skewed band.
 static int lanes_code(int g) {
-    return g == VERIFY_BIDIR ? -2 : g == VERIFY_CLASSES ? -3 : g;
+    return g == VERIFY_BIDIR ? -2 : g == VERIFY_CLASSES ? -3 : g == VERIFY_RING ? -4 : g;
 }
 
 // Band words per lane of configuration g for a band of cmax words (the window holds
 // cmax + 1), 0 when it cannot hold it; the band classes give their widest class's 4.
 static int window_words_per_lane(int g, int cmax) {
     if (g == VERIFY_CLASSES) return cmax + 1 <= 32 ? 4 : 0;
+    if (g == VERIFY_RING) return ring_words_per_lane(cmax);
     for (int v : {1, 2, 3, 4, 5, 6, 7, 8, 9, 11})
         if (v * (g == VERIFY_BIDIR ? 1 : g) >= cmax + 1) return v;
     return 0;

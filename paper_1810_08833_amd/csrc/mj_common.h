@@ -374,10 +374,11 @@ int verify_planes(int bits);   // planes the verifier needs for b bits per symbo
 // verify_lg.hip: one persistent launch for all pairs (lane groups, longest first).
 // The lane-group width is timed once per (ceil(Kmax/32), planes) and kept in `tune`.
 // VerifyTuning::last_g value of the kernel that splits each pair's text columns over two
-// lanes (forward and reversed halves), and of the launch that sizes each pair's window by
-// its band class
+// lanes (forward and reversed halves), of the launch that sizes each pair's window by
+// its band class, and of the skewed band (both halves, by band class)
 constexpr int VERIFY_BIDIR = 3;
 constexpr int VERIFY_CLASSES = 5;
+constexpr int VERIFY_RING = 6;
 struct VerifyTuning {
     int best_g[64][4] = {};
     int best_blocks[64][4] = {};
@@ -398,6 +399,7 @@ int64_t verify_pairs_batched(const uint64_t *pairs, int64_t n, const DevStrings 
                              uint64_t *cells_defer = nullptr, int force_lanes = 0);
 int persist_max_c();
 int verify_small_call_lanes(int cmax);
+int ring_words_per_lane(int cmax);  // of the skewed band, for bands of cmax words
 void verify_pairs_batched_streamed(const uint64_t *pairs, int64_t cap, const uint32_t *n_dev,
                                    const DevStrings &A, const DevStrings &B, int kmode, int cmax,
                                    uint8_t *flags, Workspace &ws, hipStream_t s, KTimer *kt,

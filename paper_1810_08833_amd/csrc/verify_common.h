@@ -33,6 +33,40 @@ __device__ __forceinline__ uint32_t and_xnor(uint32_t a, uint32_t b, uint32_t c)
     return __builtin_amdgcn_bitop3_b32(a, b, c, 0x90);
 }
 
+// As load_word, for a string read in either direction.
+template <int NP>
+__device__ __forceinline__ uint32_t load_dir(const uint32_t *plane, int64_t bitpos, bool rev) {
+    // forward: symbols bitpos .. bitpos + 31 at bits 0 .. 31; reversed: bit t holds symbol
+    // bitpos + 31 - t.  Positions before the start of the planes read as 0.
+    uint32_t w;
+    if (bitpos >= 0) w = load_word<NP>(plane, bitpos);
+    else if (bitpos > -32) w = load_word<NP>(plane, 0) << (uint32_t)(-bitpos);
+    else w = 0u;
+    return rev ? __builtin_bitreverse32(w) : w;
+}
+
+// The work queue of a persistent launch: interleaved sub-queues, each counter on lines of
+// its own.
+constexpr int QUEUES = 32;
+constexpr int QSTRIDE = 32;  // uint64 words between two sub-queue counters (256 bytes)
+
+// The launch of the skewed band (verify_ring.hip): pairs in the class order of ring_class,
+// off[] the bin offsets of that order (bins per class: RING_BINS, widest class first).
+using PersistClassKernel = void (*)(const uint64_t *, const int64_t *, const uint32_t *, VSet, VSet,
+                                    int, uint8_t *, unsigned long long *, unsigned long long *);
+PersistClassKernel ring_kernel(int np);
+// Lanes per half (G) and words per lane (W) of each class; a class holds bands of
+// K <= 32 W (G - 2).
+constexpr int RING_CLASSES = 6;
+constexpr int RING_G[RING_CLASSES] = {4, 8, 16, 16, 16, 16};
+constexpr int RING_W[RING_CLASSES] = {1, 1, 1, 2, 3, 5};
+constexpr int RING_BINS = 512;  // length bins per class
+__host__ __device__ __forceinline__ int ring_class(int32_t K) {
+    int c = 0;
+    while (c + 1 < RING_CLASSES && 32 * RING_W[c] * (RING_G[c] - 2) < K) c++;
+    return c;
+}
+
 inline VSet vset(const DevStrings &d) {
     return VSet{d.n, d.offsets, d.len, d.kk, d.planes};
 }

@@ -65,9 +65,6 @@ __device__ __forceinline__ int gshfl_xor(int v, int d) {
     return G > 1 ? __shfl_xor(v, d, G) : v;
 }
 
-constexpr int QUEUES = 32;
-constexpr int QSTRIDE = 64;  // uint64 words between two sub-queue counters (512 bytes)
-
 // The pairs order[0 .. n) with lane groups of G lanes and NWL window words per lane, taken
 // from the sub-queues whose counters `next` holds; returns when every sub-queue is dry.
 template <int NWL, int G, int NP>
@@ -392,17 +389,6 @@ __global__ __launch_bounds__(256) void k_verify_persist(const uint64_t *__restri
 // and an alignment of cost <= K crosses column mid inside the band, where both halves hold
 // exact values whenever they are <= K: the decision ED <= K is that of the one-lane kernel.
 // A pair's latency halves; texts shorter than 64 columns stay with the first lane alone.
-template <int NP>
-__device__ __forceinline__ uint32_t load_dir(const uint32_t *plane, int64_t bitpos, bool rev) {
-    // forward: symbols bitpos .. bitpos + 31 at bits 0 .. 31; reversed: bit t holds symbol
-    // bitpos + 31 - t.  Positions before the start of the planes read as 0.
-    uint32_t w;
-    if (bitpos >= 0) w = load_word<NP>(plane, bitpos);
-    else if (bitpos > -32) w = load_word<NP>(plane, 0) << (uint32_t)(-bitpos);
-    else w = 0u;
-    return rev ? __builtin_bitreverse32(w) : w;
-}
-
 // 32 bits of a padded window (A[0] = 0, A[1 .. NW] = the words, A[NW + 1] = 0) starting
 // at bit e of the unpadded words, -32 < e < 32 NW
 template <int NW>
@@ -742,16 +728,16 @@ __global__ __launch_bounds__(256) void k_verify_bidir(const uint64_t *__restrict
 using PersistKernel = void (*)(const uint64_t *, const int64_t *, int64_t, VSet, VSet, int,
                                uint8_t *, unsigned long long *, unsigned long long *,
                                const uint32_t *);
-using PersistClassKernel = void (*)(const uint64_t *, const int64_t *, const uint32_t *, VSet, VSet,
-                                    int, uint8_t *, unsigned long long *, unsigned long long *);
 constexpr int VCLS_NW_MAX = 32;  // the widest band class's window words
 
 constexpr int NWL_CHOICES[] = {1, 2, 3, 4, 5, 6, 7, 8, 9, 11};
 // g == BIDIR: two lanes per pair, split by columns (each lane holds the whole window);
 // g == CLASSES: lanes per pair and window chosen per pair by its band class
+// g == RING: the skewed band (verify_ring.hip)
 constexpr int BIDIR = VERIFY_BIDIR;
 constexpr int CLASSES = VERIFY_CLASSES;
-constexpr int G_CHOICES[] = {1, 2, BIDIR, 4, 8, CLASSES};
+constexpr int RING = VERIFY_RING;
+constexpr int G_CHOICES[] = {1, 2, BIDIR, 4, 8, CLASSES, RING};
 
 template <int NWL, int G>
 static PersistKernel by_np(int np) {
@@ -816,8 +802,10 @@ static PersistKernel persist_kernel(int nwl, int g, int np) {
 }
 
 // smallest supported NWL with NWL * G >= nw (the whole window per lane for BIDIR), or 0;
-// for CLASSES 4 (the widest class's words per lane) when the widest class holds nw words
+// for CLASSES 4 (the widest class's words per lane) when the widest class holds nw words;
+// for RING the words per lane of the class of the widest band
 static int nwl_for(int nw, int g) {
+    if (g == RING) return RING_W[ring_class(32 * (nw - 1))];
     if (g == CLASSES) return nw <= VCLS_NW_MAX ? 4 : 0;
     const int lanes = g == BIDIR ? 1 : g;
     for (int v : NWL_CHOICES)
@@ -828,16 +816,11 @@ static int nwl_for(int nw, int g) {
 // The window needs ceil(K/32) + 1 words (at most 11 * 8); K <= 2047 keeps c <= 64.
 int persist_max_c() { return 64; }
 
-// The configuration of calls too small to time: the most lanes per pair that still gives
-// each lane more than one word (one lane when the band fits one word).
-int verify_small_call_lanes(int cmax) {
-    const int nw = cmax + 1;
-    int best = 0;
-    for (int g : G_CHOICES)
-        if (g != BIDIR && g != CLASSES && nwl_for(nw, g) != 0 && (g == 1 || nwl_for(nw, g / 2) > 1))
-            best = g;
-    return best;
-}
+// The configuration of calls too small to time, where the longest pair's chain of columns
+// sets the time: the skewed band.  (Lane groups of 8 took 0.37 ms for one pair of 2,100
+// symbols at K = 212 and 2.9 ms for 175 of up to 10,000 at K <= 1,000.)
+int verify_small_call_lanes(int) { return RING; }
+int ring_words_per_lane(int cmax) { return nwl_for(cmax + 1, RING); }
 
 // Calls with fewer pairs use a fixed configuration instead of timing the choices.
 constexpr int64_t TUNE_MIN_PAIRS = 4096;
@@ -881,13 +864,18 @@ __device__ __forceinline__ int pair_class(int32_t K) {
     return c;
 }
 
-// The bin of a pair: longest first, or (classes) widest class first, then longest first.
+// The bin of a pair: longest first, or (classes: LPT_CLASSES or LPT_RING, by the kernel the
+// order is for) widest class first, then longest first.
+constexpr int LPT_PLAIN = 0, LPT_CLASSES = 1, LPT_RING = 2;
+static_assert(RING_CLASSES * RING_BINS <= LPT_BINS, "ring class bins");
 __device__ __forceinline__ int lpt_bin(const uint64_t pr, const VSet &A, const VSet &B, int kmode,
                                        int classes) {
     const uint32_t ia = (uint32_t)(pr >> 32), ib = (uint32_t)pr;
     int32_t nt = min(A.len[ia], B.len[ib]);
     if (!classes) return LPT_BINS - 1 - min(nt >> 4, LPT_BINS - 1);
     const int32_t K = kmode == 0 ? max(A.kk[ia], B.kk[ib]) : A.kk[ia];
+    if (classes == LPT_RING)
+        return (RING_CLASSES - 1 - ring_class(K)) * RING_BINS + RING_BINS - 1 - min(nt >> 4, RING_BINS - 1);
     return (VCLS - 1 - pair_class(K)) * VCLS_BINS + VCLS_BINS - 1 - min(nt >> 4, VCLS_BINS - 1);
 }
 
@@ -972,6 +960,10 @@ __global__ __launch_bounds__(256) void k_verify_classes(const uint64_t *__restri
 }
 
 // ---------------------------------------------------------------- dispatch
+// Sub-queue counters of one launch: a set per class.
+constexpr int QUEUE_SETS = VCLS > RING_CLASSES ? VCLS : RING_CLASSES;
+static int lpt_mode(int g) { return g == CLASSES ? LPT_CLASSES : g == RING ? LPT_RING : LPT_PLAIN; }
+
 // The pairs in bin order (longest first; class-major when classes) and the bins' offsets
 // off[0 .. LPT_BINS]; cnt and fill (LPT_BINS + 4 words each) must be zero.
 static void build_order(const uint64_t *pairs, int64_t n, const VSet &va, const VSet &vb,
@@ -1003,13 +995,13 @@ static void launch_persist(int nwl, int g, int np, int max_blocks, const uint64_
                            int kmode, uint8_t *flags, unsigned long long *cells,
                            unsigned long long *next, hipStream_t s, bool next_zero = false,
                            const uint32_t *ndev = nullptr, const uint32_t *off = nullptr) {
-    if (!next_zero) fill_u64((uint64_t *)next, 0, (int64_t)VCLS * QUEUES * QSTRIDE, s);
+    if (!next_zero) fill_u64((uint64_t *)next, 0, (int64_t)QUEUE_SETS * QUEUES * QSTRIDE, s);
     // at most max_blocks resident workgroups, and no more than the pairs need
-    int64_t groups_per_block = 256 / (g == BIDIR ? 2 : g == CLASSES ? 1 : g);
+    int64_t groups_per_block = 256 / (g == BIDIR ? 2 : g == CLASSES ? 1 : g == RING ? 2 * RING_G[RING_CLASSES - 1] : g);
     int64_t blocks = (n + groups_per_block - 1) / groups_per_block;
     blocks = std::min<int64_t>(blocks, max_blocks);
-    if (g == CLASSES) {
-        hipLaunchKernelGGL(classes_kernel(np), dim3((unsigned)std::max<int64_t>(blocks, 1)),
+    if (g == CLASSES || g == RING) {
+        hipLaunchKernelGGL(g == RING ? ring_kernel(np) : classes_kernel(np), dim3((unsigned)std::max<int64_t>(blocks, 1)),
                            dim3(256), 0, s, pairs, order, off, va, vb, kmode, flags, cells, next);
         MJ_LAUNCH_CHECK();
         return;
@@ -1029,29 +1021,28 @@ int64_t verify_pairs_batched(const uint64_t *pairs, int64_t n, const DevStrings 
     const int np = verify_planes(std::max(A.bits, B.bits));
     VSet va = vset(A), vb = vset(B);
     // one block cleared by one launch: the sub-queue counters (one set per band class), the
-    // band-cell counter, the K pass's two words and two pairs of length-bin counter arrays
-    // (longest-first and class-major orders)
-    constexpr int64_t ZNEXT = 2 * VCLS * QUEUES * QSTRIDE, ZCNT = LPT_BINS + 4;
-    uint32_t *zb = ws.get_n<uint32_t>(ZNEXT + 4 + 4 + 4 * ZCNT);
+    // band-cell counter, the K pass's two words and a pair of length-bin counter arrays per
+    // order (longest first, and the two class-major orders)
+    constexpr int64_t ZNEXT = 2 * QUEUE_SETS * QUEUES * QSTRIDE, ZCNT = LPT_BINS + 4;
+    uint32_t *zb = ws.get_n<uint32_t>(ZNEXT + 4 + 4 + 6 * ZCNT);
     unsigned long long *next = (unsigned long long *)zb;
     unsigned long long *cells = (unsigned long long *)(zb + ZNEXT);
     uint32_t *cm = zb + ZNEXT + 4;
     // longest pairs first
     uint32_t *cnt = zb + ZNEXT + 8;
-    uint32_t *fillc = cnt + ZCNT;
-    fill_u32(zb, 0, ZNEXT + 8 + 4 * ZCNT, s);
+    fill_u32(zb, 0, ZNEXT + 8 + 6 * ZCNT, s);
     bool next_zero = true;
-    uint32_t *off = ws.get_n<uint32_t>(LPT_BINS + 1);
-    int64_t *order = ws.get_n<int64_t>(n);
-    // the class-major order, built when the band classes are timed or chosen
-    uint32_t *off_c = nullptr;
-    int64_t *order_c = nullptr;
-    auto class_order = [&]() {
-        if (order_c) return;
-        off_c = ws.get_n<uint32_t>(LPT_BINS + 1);
-        order_c = ws.get_n<int64_t>(n);
-        build_order(pairs, n, va, vb, kmode, 1, fillc + ZCNT, fillc + 2 * ZCNT, off_c, order_c, ws,
-                    s, nullptr);
+    // one order per mode, built when a configuration that reads it is timed or chosen
+    uint32_t *off_of[3] = {};
+    int64_t *order_of[3] = {};
+    auto order_for = [&](int g) {
+        const int m = lpt_mode(g);
+        if (order_of[m]) return m;
+        off_of[m] = ws.get_n<uint32_t>(LPT_BINS + 1);
+        order_of[m] = ws.get_n<int64_t>(n);
+        build_order(pairs, n, va, vb, kmode, m, cnt + 2 * m * ZCNT, cnt + (2 * m + 1) * ZCNT,
+                    off_of[m], order_of[m], ws, s, nullptr);
+        return m;
     };
     int cmax;
     if (uniform_k >= 0) {
@@ -1083,11 +1074,8 @@ int64_t verify_pairs_batched(const uint64_t *pairs, int64_t n, const DevStrings 
         if (nwl_for(nw, best_g) == 0)
             throw Error(MJ_ECAPACITY, "verify_lanes: the lanes of a pair cannot hold this band");
     }
-    if (best_g == CLASSES) class_order();
-    else build_order(pairs, n, va, vb, kmode, 0, cnt, fillc, off, order, ws, s, nullptr);
     if (best_g == 0 && (n < TUNE_MIN_PAIRS || !tune)) {
-        // a small call leaves most of the chip idle: the most lanes per pair (shortest
-        // path per pair); timing the choices would cost more than the work.  Without a
+        // a small call leaves most of the chip idle: the shortest path per pair; timing the choices would cost more than the work.  Without a
         // tuning table (latency-first callers) the same fixed choice.
         best_g = verify_small_call_lanes(cmax);
         best_blocks = 512;
@@ -1106,16 +1094,15 @@ int64_t verify_pairs_batched(const uint64_t *pairs, int64_t n, const DevStrings 
         for (int g : G_CHOICES) {
             int nwl = nwl_for(nw, g);
             if (nwl == 0 || (g == CLASSES && !classes_ok)) continue;
-            if (g == CLASSES) class_order();
+            const int m = order_for(g);
             int step = 0;
             for (int mb : {256, 512, 768, 1024, 2048}) {
                 const float penalty = 1.0f + 0.03f * (float)step++;
                 float ms = 1e30f;
                 for (int rep = 0; rep < 2; rep++) {  // best of two: timing noise
                     MJ_HIP(hipEventRecord(e0, s));
-                    launch_persist(nwl, g, np, mb, pairs, g == CLASSES ? order_c : order, n, va, vb,
-                                   kmode, flags, cells, next, s, next_zero, nullptr,
-                                   g == CLASSES ? off_c : off);
+                    launch_persist(nwl, g, np, mb, pairs, order_of[m], n, va, vb, kmode, flags,
+                                   cells, next, s, next_zero, nullptr, off_of[m]);
                     next_zero = false;
                     MJ_HIP(hipEventRecord(e1, s));
                     MJ_HIP(hipEventSynchronize(e1));
@@ -1138,11 +1125,10 @@ int64_t verify_pairs_batched(const uint64_t *pairs, int64_t n, const DevStrings 
         }
         fill_u64((uint64_t *)cells, 0, 1, s);
     }
+    const int om = order_for(best_g);
     int th = kt ? kt->begin(KTimer::VERIFY, s) : -1;
-    if (best_g == CLASSES) class_order();
-    launch_persist(nwl_for(nw, best_g), best_g, np, best_blocks, pairs,
-                   best_g == CLASSES ? order_c : order, n, va, vb, kmode, flags, cells, next, s,
-                   next_zero, nullptr, best_g == CLASSES ? off_c : off);
+    launch_persist(nwl_for(nw, best_g), best_g, np, best_blocks, pairs, order_of[om], n, va, vb,
+                   kmode, flags, cells, next, s, next_zero, nullptr, off_of[om]);
     if (kt) kt->end(th, s);
     if (tune) {
         tune->last_g = best_g;
@@ -1176,7 +1162,7 @@ void verify_pairs_batched_streamed(const uint64_t *pairs, int64_t cap, const uin
     const int np = verify_planes(std::max(A.bits, B.bits));
     VSet va = vset(A), vb = vset(B);
     cap = std::max<int64_t>(cap, 1);
-    constexpr int64_t ZNEXT = 2 * VCLS * QUEUES * QSTRIDE, ZCNT = LPT_BINS + 4;
+    constexpr int64_t ZNEXT = 2 * QUEUE_SETS * QUEUES * QSTRIDE, ZCNT = LPT_BINS + 4;
     uint32_t *zb = ws.get_n<uint32_t>(ZNEXT + 4 + 4 + 2 * ZCNT);
     unsigned long long *next = (unsigned long long *)zb;
     unsigned long long *cells = (unsigned long long *)(zb + ZNEXT);
@@ -1199,7 +1185,7 @@ void verify_pairs_batched_streamed(const uint64_t *pairs, int64_t cap, const uin
     }
     if (g == 0 || nwl_for(nw, g) == 0)
         throw Error(MJ_EINVAL, "no verifier configuration for this band size");
-    build_order(pairs, cap, va, vb, kmode, g == CLASSES ? 1 : 0, cnt, fillc, off, order, ws, s, n_dev);
+    build_order(pairs, cap, va, vb, kmode, lpt_mode(g), cnt, fillc, off, order, ws, s, n_dev);
     int th = kt ? kt->begin(KTimer::VERIFY, s) : -1;
     launch_persist(nwl_for(nw, g), g, np, blocks, pairs, order, cap, va, vb, kmode, flags, cells, next,
                    s, true, n_dev, off);
