@@ -526,7 +526,7 @@ static StreamedDev launch_streamed_main(mj_ctx *ctx, DevStrings &d, const Partit
     uint8_t *flags = ws.get_n<uint8_t>(pl.ccap + 4);
     unsigned long long *cells = nullptr;
     verify_pairs_batched_streamed(uniq, pl.ccap, u, d, d, 0, pl.cmax, flags, ws, s, kt, ctx->tune,
-                                  params->verify_lanes, &cells);
+                                  params->verify_lanes, ctx->stream.candidates, &cells);
     if (tm) tm->mark();  // 5 verify
     int64_t *idx = ws.get_n<int64_t>(pl.ccap + 1);
     const uint32_t *on = compact_flags_async(flags, pl.ccap, idx, ws, s);
@@ -583,6 +583,7 @@ static mj_pairs *finish_streamed(mj_ctx *ctx, const StreamedPlan &pl, const Stre
     ctx->stream.cand_per_record = (double)c0h / (double)pl.rcap;
     ctx->stream.rec_per_bound = (double)R / (double)pl.rcap;
     ctx->stream.mem_per_bound = (double)M / (double)pl.rcap;
+    ctx->stream.candidates = C;
     ctx->stream.emit = emit_hints((uint64_t)hv[3], (uint64_t)hv[11], (uint64_t)hv[12], M, d.n,
                                   ctx->tile_min);
     return out;
@@ -754,6 +755,7 @@ extern "C" mj_status mj_join(mj_ctx *ctx, const mj_strings *strings, const mj_pa
                             stats->members, strings->n, ctx->tile_min);
         h.verify_g = ctx->tune.last_g;
         h.verify_blocks = ctx->tune.last_blocks;
+        h.candidates = stats->candidates;
     }
     return MJ_OK;
     MJ_API_END

@@ -20,6 +20,7 @@ struct StreamHints {
     double mem_per_bound = 1;    // records kept by the member filter per record bound
     EmitHints emit;
     int verify_g = 0, verify_blocks = 0;
+    int64_t candidates = 0;      // distinct candidates
 };
 
 // Sizes of a streamed join, fixed by the set-up read-back and the hints of the last join,

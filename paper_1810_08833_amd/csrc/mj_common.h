@@ -403,7 +403,7 @@ int ring_words_per_lane(int cmax);  // of the skewed band, for bands of cmax wor
 void verify_pairs_batched_streamed(const uint64_t *pairs, int64_t cap, const uint32_t *n_dev,
                                    const DevStrings &A, const DevStrings &B, int kmode, int cmax,
                                    uint8_t *flags, Workspace &ws, hipStream_t s, KTimer *kt,
-                                   const VerifyTuning &tune, int force_lanes,
+                                   const VerifyTuning &tune, int force_lanes, int64_t expect,
                                    unsigned long long **cells_out);
 
 }  // namespace mj

@@ -54,7 +54,7 @@ constexpr int QSTRIDE = 32;  // uint64 words between two sub-queue counters (256
 // off[] the bin offsets of that order (bins per class: RING_BINS, widest class first).
 using PersistClassKernel = void (*)(const uint64_t *, const int64_t *, const uint32_t *, VSet, VSet,
                                     int, uint8_t *, unsigned long long *, unsigned long long *);
-PersistClassKernel ring_kernel(int np);
+PersistClassKernel ring_kernel(int np, int cmax);  // bands of up to cmax words
 // Lanes per half (G) and words per lane (W) of each class; a class holds bands of
 // K <= 32 W (G - 2).
 constexpr int RING_CLASSES = 6;
@@ -66,6 +66,14 @@ __host__ __device__ __forceinline__ int ring_class(int32_t K) {
     while (c + 1 < RING_CLASSES && 32 * RING_W[c] * (RING_G[c] - 2) < K) c++;
     return c;
 }
+
+// The block filter (verify_filter.hip): flags[i] = 0 for the pairs it rejects, 1 for those
+// left to verify (n, or *ndev, pairs; ids valid).
+constexpr int BF_K_MIN = 64;
+constexpr int64_t BF_MIN_PAIRS = 4096;
+bool block_filter_applies(int bits, int cmax, int64_t n);
+void block_filter(const uint64_t *pairs, int64_t n, const DevStrings &A, const DevStrings &B,
+                  int kmode, uint8_t *flags, hipStream_t s, const uint32_t *ndev);
 
 inline VSet vset(const DevStrings &d) {
     return VSet{d.n, d.offsets, d.len, d.kk, d.planes};

@@ -879,15 +879,17 @@ __device__ __forceinline__ int lpt_bin(const uint64_t pr, const VSet &A, const V
     return (VCLS - 1 - pair_class(K)) * VCLS_BINS + VCLS_BINS - 1 - min(nt >> 4, VCLS_BINS - 1);
 }
 
+// keep (nullable): only the pairs i with keep[i] != 0 are counted and ordered.
 __global__ void k_lpt_hist(const uint64_t *pairs, int64_t n, VSet A, VSet B, int kmode,
-                           int classes, uint32_t *cnt, const uint32_t *ndev) {
+                           int classes, uint32_t *cnt, const uint32_t *ndev, const uint8_t *keep) {
     if (ndev) n = min(n, (int64_t)*ndev);
     __shared__ uint32_t h[LPT_BINS];
     for (int t = threadIdx.x; t < LPT_BINS; t += blockDim.x) h[t] = 0;
     __syncthreads();
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (; i < n; i += stride) atomicAdd(&h[lpt_bin(pairs[i], A, B, kmode, classes)], 1u);
+    for (; i < n; i += stride)
+        if (!keep || keep[i]) atomicAdd(&h[lpt_bin(pairs[i], A, B, kmode, classes)], 1u);
     __syncthreads();
     for (int t = threadIdx.x; t < LPT_BINS; t += blockDim.x)
         if (h[t]) atomicAdd(&cnt[t], h[t]);
@@ -900,7 +902,8 @@ constexpr int LPT_ITEMS = 16;
 __global__ __launch_bounds__(256) void k_lpt_scatter(const uint64_t *pairs, int64_t n, VSet A,
                                                      VSet B, int kmode, int classes,
                                                      const uint32_t *off, uint32_t *fill,
-                                                     int64_t *order, const uint32_t *ndev) {
+                                                     int64_t *order, const uint32_t *ndev,
+                                                     const uint8_t *keep) {
     if (ndev) n = min(n, (int64_t)*ndev);
     __shared__ uint32_t cnt[LPT_BINS];
     __shared__ uint32_t base[LPT_BINS];
@@ -912,9 +915,9 @@ __global__ __launch_bounds__(256) void k_lpt_scatter(const uint64_t *pairs, int6
 #pragma unroll
     for (int k = 0; k < LPT_ITEMS; k++) {
         const int64_t i = first + (int64_t)k * blockDim.x + threadIdx.x;
-        bin[k] = 0;
+        bin[k] = -1;
         rank[k] = 0;
-        if (i < n) {
+        if (i < n && (!keep || keep[i])) {
             bin[k] = lpt_bin(pairs[i], A, B, kmode, classes);
             rank[k] = atomicAdd(&cnt[bin[k]], 1u);
         }
@@ -926,7 +929,7 @@ __global__ __launch_bounds__(256) void k_lpt_scatter(const uint64_t *pairs, int6
 #pragma unroll
     for (int k = 0; k < LPT_ITEMS; k++) {
         const int64_t i = first + (int64_t)k * blockDim.x + threadIdx.x;
-        if (i < n) order[base[bin[k]] + rank[k]] = i;
+        if (bin[k] >= 0) order[base[bin[k]] + rank[k]] = i;
     }
 }
 
@@ -968,15 +971,16 @@ static int lpt_mode(int g) { return g == CLASSES ? LPT_CLASSES : g == RING ? LPT
 // off[0 .. LPT_BINS]; cnt and fill (LPT_BINS + 4 words each) must be zero.
 static void build_order(const uint64_t *pairs, int64_t n, const VSet &va, const VSet &vb,
                         int kmode, int classes, uint32_t *cnt, uint32_t *fill, uint32_t *off,
-                        int64_t *order, Workspace &ws, hipStream_t s, const uint32_t *ndev) {
+                        int64_t *order, Workspace &ws, hipStream_t s, const uint32_t *ndev,
+                        const uint8_t *keep) {
     hipLaunchKernelGGL(k_lpt_hist, dim3(grid_for(n, 256, 1024)), dim3(256), 0, s, pairs, n, va, vb,
-                       kmode, classes, cnt, ndev);
+                       kmode, classes, cnt, ndev, keep);
     MJ_LAUNCH_CHECK();
     exclusive_scan_u32(cnt, off, LPT_BINS, ws, s);
     const int64_t sblocks = (n + 256 * LPT_ITEMS - 1) / (256 * LPT_ITEMS);
     if (sblocks > 0x7FFFFFFFLL) throw Error(MJ_ECAPACITY, "too many pairs for one verification");
     hipLaunchKernelGGL(k_lpt_scatter, dim3((unsigned)sblocks), dim3(256), 0, s, pairs, n, va, vb,
-                       kmode, classes, off, fill, order, ndev);
+                       kmode, classes, off, fill, order, ndev, keep);
     MJ_LAUNCH_CHECK();
 }
 
@@ -990,18 +994,19 @@ static PersistClassKernel classes_kernel(int np) {
 }
 
 // order / off: the longest-first order and its bin offsets (class-major for CLASSES)
-static void launch_persist(int nwl, int g, int np, int max_blocks, const uint64_t *pairs,
+static void launch_persist(int cmax, int g, int np, int max_blocks, const uint64_t *pairs,
                            const int64_t *order, int64_t n, const VSet &va, const VSet &vb,
                            int kmode, uint8_t *flags, unsigned long long *cells,
                            unsigned long long *next, hipStream_t s, bool next_zero = false,
                            const uint32_t *ndev = nullptr, const uint32_t *off = nullptr) {
     if (!next_zero) fill_u64((uint64_t *)next, 0, (int64_t)QUEUE_SETS * QUEUES * QSTRIDE, s);
+    const int nwl = nwl_for(cmax + 1, g);
     // at most max_blocks resident workgroups, and no more than the pairs need
     int64_t groups_per_block = 256 / (g == BIDIR ? 2 : g == CLASSES ? 1 : g == RING ? 2 * RING_G[RING_CLASSES - 1] : g);
     int64_t blocks = (n + groups_per_block - 1) / groups_per_block;
     blocks = std::min<int64_t>(blocks, max_blocks);
     if (g == CLASSES || g == RING) {
-        hipLaunchKernelGGL(g == RING ? ring_kernel(np) : classes_kernel(np), dim3((unsigned)std::max<int64_t>(blocks, 1)),
+        hipLaunchKernelGGL(g == RING ? ring_kernel(np, cmax) : classes_kernel(np), dim3((unsigned)std::max<int64_t>(blocks, 1)),
                            dim3(256), 0, s, pairs, order, off, va, vb, kmode, flags, cells, next);
         MJ_LAUNCH_CHECK();
         return;
@@ -1032,6 +1037,8 @@ int64_t verify_pairs_batched(const uint64_t *pairs, int64_t n, const DevStrings 
     uint32_t *cnt = zb + ZNEXT + 8;
     fill_u32(zb, 0, ZNEXT + 8 + 6 * ZCNT, s);
     bool next_zero = true;
+    // the pairs the block filter leaves, nullptr: all of them
+    const uint8_t *keep = nullptr;
     // one order per mode, built when a configuration that reads it is timed or chosen
     uint32_t *off_of[3] = {};
     int64_t *order_of[3] = {};
@@ -1041,7 +1048,7 @@ int64_t verify_pairs_batched(const uint64_t *pairs, int64_t n, const DevStrings 
         off_of[m] = ws.get_n<uint32_t>(LPT_BINS + 1);
         order_of[m] = ws.get_n<int64_t>(n);
         build_order(pairs, n, va, vb, kmode, m, cnt + 2 * m * ZCNT, cnt + (2 * m + 1) * ZCNT,
-                    off_of[m], order_of[m], ws, s, nullptr);
+                    off_of[m], order_of[m], ws, s, nullptr, keep);
         return m;
     };
     int cmax;
@@ -1074,7 +1081,16 @@ int64_t verify_pairs_batched(const uint64_t *pairs, int64_t n, const DevStrings 
         if (nwl_for(nw, best_g) == 0)
             throw Error(MJ_ECAPACITY, "verify_lanes: the lanes of a pair cannot hold this band");
     }
-    if (best_g == 0 && (n < TUNE_MIN_PAIRS || !tune)) {
+    int64_t left = n;  // pairs to verify
+    if (tune && force_lanes == 0 && block_filter_applies(std::max(A.bits, B.bits), cmax, n)) {
+        block_filter(pairs, n, A, B, kmode, flags, s, nullptr);
+        keep = flags;
+        if (best_g == 0) {
+            const int m = order_for(RING);
+            left = read_back<uint32_t>(off_of[m] + LPT_BINS, s, host_scratch);
+        }
+    }
+    if (best_g == 0 && (left < TUNE_MIN_PAIRS || !tune)) {
         // a small call leaves most of the chip idle: the shortest path per pair; timing the choices would cost more than the work.  Without a
         // tuning table (latency-first callers) the same fixed choice.
         best_g = verify_small_call_lanes(cmax);
@@ -1091,9 +1107,12 @@ int64_t verify_pairs_batched(const uint64_t *pairs, int64_t n, const DevStrings 
         MJ_HIP(hipEventCreate(&e1));
         float best = 1e30f;
         best_g = 0;
+        // every order before the first launch: the launches write the filter's flags over
+        order_for(1);
+        if (classes_ok) order_for(CLASSES);
+        order_for(RING);
         for (int g : G_CHOICES) {
-            int nwl = nwl_for(nw, g);
-            if (nwl == 0 || (g == CLASSES && !classes_ok)) continue;
+            if (nwl_for(nw, g) == 0 || (g == CLASSES && !classes_ok)) continue;
             const int m = order_for(g);
             int step = 0;
             for (int mb : {256, 512, 768, 1024, 2048}) {
@@ -1101,8 +1120,8 @@ int64_t verify_pairs_batched(const uint64_t *pairs, int64_t n, const DevStrings 
                 float ms = 1e30f;
                 for (int rep = 0; rep < 2; rep++) {  // best of two: timing noise
                     MJ_HIP(hipEventRecord(e0, s));
-                    launch_persist(nwl, g, np, mb, pairs, order_of[m], n, va, vb, kmode, flags,
-                                   cells, next, s, next_zero, nullptr, off_of[m]);
+                    launch_persist(cmax, g, np, mb, pairs, order_of[m], n, va, vb, kmode, flags,
+                                   cells, next, s, next_zero, off_of[m] + LPT_BINS, off_of[m]);
                     next_zero = false;
                     MJ_HIP(hipEventRecord(e1, s));
                     MJ_HIP(hipEventSynchronize(e1));
@@ -1127,8 +1146,8 @@ int64_t verify_pairs_batched(const uint64_t *pairs, int64_t n, const DevStrings 
     }
     const int om = order_for(best_g);
     int th = kt ? kt->begin(KTimer::VERIFY, s) : -1;
-    launch_persist(nwl_for(nw, best_g), best_g, np, best_blocks, pairs, order_of[om], n, va, vb,
-                   kmode, flags, cells, next, s, next_zero, nullptr, off_of[om]);
+    launch_persist(cmax, best_g, np, best_blocks, pairs, order_of[om], n, va, vb,
+                   kmode, flags, cells, next, s, next_zero, off_of[om] + LPT_BINS, off_of[om]);
     if (kt) kt->end(th, s);
     if (tune) {
         tune->last_g = best_g;
@@ -1152,12 +1171,12 @@ int64_t verify_pairs_batched(const uint64_t *pairs, int64_t n, const DevStrings 
 // The batched verification with the pair count on the device (*n_dev <= cap): pairs
 // longest first, then the persistent launch in the configuration the context timed for this
 // band size (the caller makes sure one is known: `cmax` words of band from the largest K),
-// no host read.  flags[n .. cap) are written 0; the band-cell count and the window error
+// no host read.  expect: how many pairs there may be (speed only).  flags[n .. cap) are written 0; the band-cell count and the window error
 // word go to cells_out[0..1] (device).
 void verify_pairs_batched_streamed(const uint64_t *pairs, int64_t cap, const uint32_t *n_dev,
                                    const DevStrings &A, const DevStrings &B, int kmode, int cmax,
                                    uint8_t *flags, Workspace &ws, hipStream_t s, KTimer *kt,
-                                   const VerifyTuning &tune, int force_lanes,
+                                   const VerifyTuning &tune, int force_lanes, int64_t expect,
                                    unsigned long long **cells_out) {
     const int np = verify_planes(std::max(A.bits, B.bits));
     VSet va = vset(A), vb = vset(B);
@@ -1185,10 +1204,15 @@ void verify_pairs_batched_streamed(const uint64_t *pairs, int64_t cap, const uin
     }
     if (g == 0 || nwl_for(nw, g) == 0)
         throw Error(MJ_EINVAL, "no verifier configuration for this band size");
-    build_order(pairs, cap, va, vb, kmode, lpt_mode(g), cnt, fillc, off, order, ws, s, n_dev);
+    const uint8_t *keep = nullptr;
+    if (force_lanes == 0 && block_filter_applies(std::max(A.bits, B.bits), cmax, expect)) {
+        block_filter(pairs, cap, A, B, kmode, flags, s, n_dev);
+        keep = flags;
+    }
+    build_order(pairs, cap, va, vb, kmode, lpt_mode(g), cnt, fillc, off, order, ws, s, n_dev, keep);
     int th = kt ? kt->begin(KTimer::VERIFY, s) : -1;
-    launch_persist(nwl_for(nw, g), g, np, blocks, pairs, order, cap, va, vb, kmode, flags, cells, next,
-                   s, true, n_dev, off);
+    launch_persist(cmax, g, np, blocks, pairs, order, cap, va, vb, kmode, flags, cells, next,
+                   s, true, off + LPT_BINS, off);
     if (kt) kt->end(th, s);
 }
 

@@ -58,22 +58,20 @@ __device__ __forceinline__ uint32_t other_half(uint32_t v) {
 }
 
 // Rows of a wave's halves: 32 / G pairs of G strips, kept as 16-bit values for the meeting.
-constexpr int RING_W_MAX = 5;
-constexpr int RING_VALS = 32 * (32 * RING_W_MAX - 1);
-
+template <int W>
 struct RingShared {
-    uint16_t val[RING_VALS];
+    uint16_t val[32 * (32 * W - 1)];
     int32_t strip[64];  // the strip each lane's values belong to, -1: none
 };
 
 // The pairs order[0 .. n) with G lanes a half and W words a lane, from the sub-queues whose
 // counters `next` holds; returns when every sub-queue is dry.
-template <int G, int W, int NP>
+template <int G, int W, int NP, class Shared>
 __device__ __forceinline__ void ring_body(const uint64_t *__restrict__ pairs,
                                           const int64_t *__restrict__ order, int64_t n, VSet A,
                                           VSet B, int kmode, uint8_t *__restrict__ flags,
                                           unsigned long long *cells, unsigned long long *next,
-                                          RingShared &sh) {
+                                          Shared &sh) {
     constexpr int STR = 16 / G, R = 32 * W - 1, P = 32 * W;
     constexpr int FAR = 0x3FFFFFFF;
     const int lane = threadIdx.x & 63;
@@ -438,8 +436,10 @@ __device__ __forceinline__ void ring_body(const uint64_t *__restrict__ pairs,
     if (lane == 0 && my_cells) atomicAdd(cells, (unsigned long long)my_cells);
 }
 
-// One persistent launch over the classes of ring_class, the widest bands first.
-template <int NP>
+// One persistent launch over the classes 0 .. CMAX of ring_class, the widest bands first.  The
+// wide classes' registers (W words of each of NP planes, twice) leave two waves a SIMD: calls
+// without such bands take a kernel without them.
+template <int NP, int CMAX>
 __global__ __launch_bounds__(256) void k_verify_ring(const uint64_t *__restrict__ pairs,
                                                      const int64_t *__restrict__ order,
                                                      const uint32_t *__restrict__ off, VSet A,
@@ -447,9 +447,9 @@ __global__ __launch_bounds__(256) void k_verify_ring(const uint64_t *__restrict_
                                                      uint8_t *__restrict__ flags,
                                                      unsigned long long *cells,
                                                      unsigned long long *next) {
-    __shared__ RingShared shared[4];
-    RingShared &sh = shared[threadIdx.x >> 6];
-    for (int c = RING_CLASSES - 1; c >= 0; c--) {
+    __shared__ RingShared<RING_W[CMAX]> shared[4];
+    auto &sh = shared[threadIdx.x >> 6];
+    for (int c = CMAX; c >= 0; c--) {
         const int b0 = (RING_CLASSES - 1 - c) * RING_BINS;
         const int64_t base = off[b0], cnt = (int64_t)off[b0 + RING_BINS] - base;
         if (cnt <= 0) continue;
@@ -459,19 +459,35 @@ __global__ __launch_bounds__(256) void k_verify_ring(const uint64_t *__restrict_
             case 0: ring_body<4, 1, NP>(pairs, oc, cnt, A, B, kmode, flags, cells, nx, sh); break;
             case 1: ring_body<8, 1, NP>(pairs, oc, cnt, A, B, kmode, flags, cells, nx, sh); break;
             case 2: ring_body<16, 1, NP>(pairs, oc, cnt, A, B, kmode, flags, cells, nx, sh); break;
-            case 3: ring_body<16, 2, NP>(pairs, oc, cnt, A, B, kmode, flags, cells, nx, sh); break;
-            case 4: ring_body<16, 3, NP>(pairs, oc, cnt, A, B, kmode, flags, cells, nx, sh); break;
-            default: ring_body<16, 5, NP>(pairs, oc, cnt, A, B, kmode, flags, cells, nx, sh); break;
+            case 3:
+                if constexpr (CMAX >= 3)
+                    ring_body<16, 2, NP>(pairs, oc, cnt, A, B, kmode, flags, cells, nx, sh);
+                break;
+            case 4:
+                if constexpr (CMAX >= 4)
+                    ring_body<16, 3, NP>(pairs, oc, cnt, A, B, kmode, flags, cells, nx, sh);
+                break;
+            default:
+                if constexpr (CMAX >= 5)
+                    ring_body<16, 5, NP>(pairs, oc, cnt, A, B, kmode, flags, cells, nx, sh);
+                break;
         }
     }
 }
 
-PersistClassKernel ring_kernel(int np) {
+template <int NP>
+static PersistClassKernel ring_by_class(int c) {
+    return c <= 2 ? k_verify_ring<NP, 2> : c == 3 ? k_verify_ring<NP, 3>
+         : c == 4 ? k_verify_ring<NP, 4> : k_verify_ring<NP, 5>;
+}
+
+PersistClassKernel ring_kernel(int np, int cmax) {
+    const int c = ring_class(32 * cmax);
     switch (np) {
-        case 2: return k_verify_ring<2>;
-        case 4: return k_verify_ring<4>;
-        case 6: return k_verify_ring<6>;
-        default: return k_verify_ring<8>;
+        case 2: return ring_by_class<2>(c);
+        case 4: return ring_by_class<4>(c);
+        case 6: return ring_by_class<6>(c);
+        default: return ring_by_class<8>(c);
     }
 }
 
