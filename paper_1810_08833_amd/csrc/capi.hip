@@ -101,6 +101,12 @@ static bool use_members(const mj_ctx *ctx, int64_t records) {
     return ctx->member_min >= 0 && records >= std::max<int64_t>(ctx->member_min, 2);
 }
 
+// Grouping by LDS buckets.  A context told to test every join's large groups by tile pairs
+// (tile_min 0) takes the path that has them.
+static bool use_buckets(const mj_ctx *ctx, int64_t records, int64_t total) {
+    return ctx->tile_min != 0 && bucket_join_fits(records, total);
+}
+
 extern "C" mj_status mj_ctx_set_streaming(mj_ctx *ctx, int mode) {
     if (!ctx) return fail(MJ_EINVAL, "ctx is NULL");
     if (mode < 0 || mode > 2) return fail(MJ_EINVAL, "streaming mode must be 0, 1 or 2");
@@ -340,15 +346,70 @@ static mj_pairs *run_join(mj_ctx *ctx, const mj_strings *strings, const mj_param
         group_members(rb.key, rb.val, R, nullptr, gkey, gval, R, m_dev, ctx->member_big, ws, s);
         M = read_back<int64_t>(m_dev, s, ctx->pinned);
     }
-    if (M > 1) {
-        sort_records(gkey, gval, M, ws, s, ctx->pinned);
-    }
-    tm.mark();  // 2 sort
-    GroupInfo g = find_groups(gkey, M, ws, s, ctx->pinned);
+    GroupInfo g;
     uint64_t *uniq = nullptr;
     int64_t C = 0;
     const uint64_t pass_tests = (uint64_t)ctx->pair_test_pass;
-    if (g.tests <= pass_tests) {
+    // by LDS buckets where the buckets fit (their records grouped, not sorted further)
+    BucketRecords br;
+    bool bucket = !members && use_buckets(ctx, R, d.total), longs = false;
+    if (bucket) {
+        br = bucket_records(gkey, gval, R, R, nullptr, ws, s);
+        bucket_pairs(br, d, false, nullptr, 0, false, s);
+        std::vector<uint64_t> part(3 * br.blocks + 3);
+        MJ_HIP(hipMemcpyAsync(ctx->pinned, br.part, part.size() * 8, hipMemcpyDeviceToHost, s));
+        MJ_HIP(hipStreamSynchronize(s));
+        memcpy(part.data(), ctx->pinned, part.size() * 8);
+        for (int b = 0; b < br.blocks; b++) {
+            g.tests += part[3 * b];
+            g.groups += (int64_t)part[3 * b + 1];
+        }
+        longs = (part[3 * br.blocks + 2] >> 40) != 0;
+        if ((uint32_t)part[3 * br.blocks + 1] || g.tests > pass_tests) {
+            bucket = false;
+            g = GroupInfo();
+        }
+    }
+    if (!bucket && M > 1) {
+        sort_records(gkey, gval, M, ws, s, ctx->pinned);
+    }
+    tm.mark();  // 2 sort
+    if (!bucket) g = find_groups(gkey, M, ws, s, ctx->pinned);
+    if (bucket) {
+        const int64_t cap = (int64_t)g.tests;
+        uint64_t *cand = ws.get_n<uint64_t>(cap + 1);
+        int64_t c0 = 0;
+        auto emit = [&]() {
+            bucket_reset(br, s);
+            bucket_pairs(br, d, true, cand, cap, longs, s, &ctx->kt);
+            c0 = (int64_t)read_back<uint64_t>((const uint64_t *)br.counter, s, ctx->pinned);
+            if (c0 > cap) throw Error(MJ_ECAPACITY, "candidate buffer overflow");
+        };
+        if (cap > 0) emit();
+        ctx->last_c0 = c0;
+        tm.mark();  // 3 group + filter
+        bool done = false;
+        if (c0 > 0 && dedup_buckets_fit(c0, d.n, d.n)) {
+            uint64_t *res = nullptr;
+            const uint32_t *u = dedup_buckets(cand, c0, c0, br.counter, d.n, d.n, br.over, ws, s, &res);
+            MJ_HIP(hipMemcpyAsync(ctx->pinned, u, 4, hipMemcpyDeviceToHost, s));
+            MJ_HIP(hipMemcpyAsync(ctx->pinned + 1, br.over, 4, hipMemcpyDeviceToHost, s));
+            MJ_HIP(hipStreamSynchronize(s));
+            done = (uint32_t)ctx->pinned[1] == 0;
+            if (done) {
+                C = (int64_t)(uint32_t)ctx->pinned[0];
+                uniq = res;
+                if (upto == 1) {  // the caller's
+                    uniq = (uint64_t *)result_alloc((size_t)(C + 1) * 8, t_dev_alloc, s);
+                    MJ_HIP(hipMemcpyAsync(uniq, res, (size_t)C * 8, hipMemcpyDeviceToDevice, s));
+                }
+            } else {
+                emit();  // the candidates as they were
+            }
+        }
+        if (!done) C = dedup_pairs(cand, c0, d.n, d.n, ws, s, ctx->pinned, &uniq, upto != 1);
+        bucket = done || c0 == 0;
+    } else if (g.tests <= pass_tests) {
         int64_t cap = (int64_t)g.tests;
         uint64_t *cand = ws.get_n<uint64_t>(cap + 1);
         int64_t c0 = emit_candidates(gval, M, g, d, cand, cap, ws, s, ctx->pinned, ctx->tile_min,
@@ -385,6 +446,8 @@ static mj_pairs *run_join(mj_ctx *ctx, const mj_strings *strings, const mj_param
     }
     ctx->last_R = R;
     ctx->last_M = M;
+    ctx->last_bucket = bucket;
+    ctx->last_longs = longs;
     ctx->last_small_tests = g.small_tests;
     ctx->last_units = g.units;
     ctx->last_rcap = std::max<int64_t>(si.rec_bound * pp.reps, 2);
@@ -429,16 +492,31 @@ static mj_pairs *run_join(mj_ctx *ctx, const mj_strings *strings, const mj_param
 // final one, no stage waits for the host.  Returns nullptr when a capacity was exceeded
 // (the caller then runs the join stage by stage, which sizes everything exactly).
 
+// slot: the group counts, or (LDS buckets) part[0 .. 3 blocks + 3): see BucketRecords
 __global__ void k_collect(const int64_t *R, const uint64_t *slot, const unsigned long long *c0,
                           const uint32_t *u, const uint32_t *outn, const unsigned long long *cells,
-                          const uint32_t *symbol_err, const int64_t *M, uint64_t *dst) {
+                          const uint32_t *symbol_err, const int64_t *M, const uint64_t *part,
+                          int blocks, uint64_t *dst) {
+    uint64_t tests = 0, groups = 0;
+    if (part) {
+        for (int b = threadIdx.x; b < blocks; b += 64) {
+            tests += part[3 * b];
+            groups += part[3 * b + 1];
+        }
+        for (int d = 32; d >= 1; d >>= 1) {
+            tests += (uint64_t)__shfl_down((long long)tests, d, 64);
+            groups += (uint64_t)__shfl_down((long long)groups, d, 64);
+        }
+    }
     if (blockIdx.x != 0 || threadIdx.x != 0) return;
+    dst[13] = part ? (uint32_t)part[3 * blocks + 1] : 0;
+    dst[14] = part ? part[3 * blocks + 2] >> 40 : 0;
     dst[10] = (uint64_t)*M;
     dst[9] = symbol_err ? *symbol_err : 0;
     dst[0] = (uint64_t)*R;
     dst[1] = slot ? slot[0] : 0;
-    dst[2] = slot ? slot[1] : 0;
-    dst[3] = slot ? slot[2] : 0;
+    dst[2] = slot ? slot[1] : groups;
+    dst[3] = slot ? slot[2] : tests;
     dst[4] = *c0;
     dst[5] = *u;
     dst[6] = *outn;
@@ -478,7 +556,9 @@ static bool plan_streamed(mj_ctx *ctx, const mj_params *params, const DevStrings
     pl.scap = std::max<int64_t>(
         2, std::min<int64_t>(pl.rcap, (int64_t)(1.02 * h.rec_per_bound * (double)pl.rcap) + 4096));
     // candidates before the dedup: the last join's rate per record bound, with room
-    const double ccap = 1.1 * h.cand_per_record * (double)pl.rcap + 65536.0;
+    pl.cexp = (int64_t)(h.cand_per_record * (double)pl.rcap);
+    const double ccap = 1.15 * (double)pl.cexp +
+                        (double)std::max<int64_t>(4096, std::min<int64_t>(65536, pl.cexp / 2));
     if (ccap > (double)std::min<int64_t>(ctx->pair_test_pass, 0x7FFFFFF0LL))
         return false;  // candidates beyond one emission pass: stage by stage, in passes
     pl.ccap = (int64_t)ccap;
@@ -488,6 +568,10 @@ static bool plan_streamed(mj_ctx *ctx, const mj_params *params, const DevStrings
                                pl.scap, (int64_t)(1.1 * h.mem_per_bound * (double)pl.rcap) + 65536))
                          : pl.scap;
     pl.emit = h.emit;
+    pl.rexp = std::min<int64_t>(pl.scap, (int64_t)(h.rec_per_bound * (double)pl.rcap));
+    pl.bucket = h.bucket && !pl.members && use_buckets(ctx, pl.scap, d.total) &&
+                dedup_buckets_fit(pl.cexp, d.n, d.n);
+    pl.longs = h.longs;
     return true;
 }
 
@@ -513,15 +597,28 @@ static StreamedDev launch_streamed_main(mj_ctx *ctx, DevStrings &d, const Partit
         M_dev = ws.get_n<int64_t>(2);
         group_members(key, val, pl.scap, R_dev, gkey, gval, pl.mcap, M_dev, ctx->member_big, ws, s);
     }
-    sort_records(gkey, gval, pl.mcap, ws, s, ctx->pinned, M_dev);
-    if (tm) tm->mark();  // 2 sort
-    GroupInfo g = find_groups_streamed(gkey, pl.mcap, M_dev, ws, s);
     uint64_t *cand = ws.get_n<uint64_t>(pl.ccap + 1);
-    unsigned long long *c0 = (unsigned long long *)ws.get_n<uint64_t>(2);
-    emit_candidates_streamed(gval, pl.mcap, M_dev, g, d, cand, pl.ccap, c0, pl.emit, ws, s, kt);
-    if (tm) tm->mark();  // 3 group + filter
     uint64_t *uniq = nullptr;
-    const uint32_t *u = dedup_pairs_streamed(cand, pl.ccap, c0, d.n, d.n, ws, s, &uniq);
+    GroupInfo g;
+    BucketRecords br;
+    unsigned long long *c0 = nullptr;
+    const uint32_t *u = nullptr;
+    if (pl.bucket) {
+        br = bucket_records(gkey, gval, pl.mcap, pl.rexp, M_dev, ws, s);
+        if (tm) tm->mark();  // 2 sort
+        c0 = br.counter;
+        bucket_pairs(br, d, true, cand, pl.ccap, pl.longs, s, kt);
+        if (tm) tm->mark();  // 3 group + filter
+        u = dedup_buckets(cand, pl.ccap, pl.cexp, c0, d.n, d.n, br.over, ws, s, &uniq);
+    } else {
+        sort_records(gkey, gval, pl.mcap, ws, s, ctx->pinned, M_dev);
+        if (tm) tm->mark();  // 2 sort
+        g = find_groups_streamed(gkey, pl.mcap, M_dev, ws, s);
+        c0 = (unsigned long long *)ws.get_n<uint64_t>(2);
+        emit_candidates_streamed(gval, pl.mcap, M_dev, g, d, cand, pl.ccap, c0, pl.emit, ws, s, kt);
+        if (tm) tm->mark();  // 3 group + filter
+        u = dedup_pairs_streamed(cand, pl.ccap, c0, d.n, d.n, ws, s, &uniq);
+    }
     if (tm) tm->mark();  // 4 dedup
     uint8_t *flags = ws.get_n<uint8_t>(pl.ccap + 4);
     unsigned long long *cells = nullptr;
@@ -534,9 +631,9 @@ static StreamedDev launch_streamed_main(mj_ctx *ctx, DevStrings &d, const Partit
     gather_u64(uniq, idx, dv.outbuf, pl.ccap, s, on);
     uint64_t *res = ws.get_n<uint64_t>(16);
     hipLaunchKernelGGL(k_collect, dim3(1), dim3(64), 0, s, R_dev, g.slot, c0, u, on, cells,
-                       (const uint32_t *)d.symbol_err, M_dev, res);
+                       (const uint32_t *)d.symbol_err, M_dev, (const uint64_t *)br.part, br.blocks, res);
     MJ_LAUNCH_CHECK();
-    MJ_HIP(hipMemcpyAsync(ctx->pinned, res, 13 * 8, hipMemcpyDeviceToHost, s));
+    MJ_HIP(hipMemcpyAsync(ctx->pinned, res, 15 * 8, hipMemcpyDeviceToHost, s));
     return dv;
 }
 
@@ -545,13 +642,17 @@ static StreamedDev launch_streamed_main(mj_ctx *ctx, DevStrings &d, const Partit
 static mj_pairs *finish_streamed(mj_ctx *ctx, const StreamedPlan &pl, const StreamedDev &dv,
                                  const DevStrings &d, const PartitionParams &pp, hipStream_t s,
                                  mj_stats *stats) {
-    uint64_t hv[13];
+    uint64_t hv[15];
     memcpy(hv, ctx->pinned, sizeof(hv));
     const int64_t R = (int64_t)hv[0], c0h = (int64_t)hv[4], C = (int64_t)hv[5], nout = (int64_t)hv[6];
     const int64_t M = (int64_t)hv[10];
     if (hv[9]) throw Error(MJ_EINVAL, "a symbol code is not below sigma");
+    if (hv[13]) ctx->stream.bucket = false;  // a bucket that does not fit: the general path
+    // long slots not looked for are pairs not tested
+    const bool missed = pl.bucket && hv[14] && !pl.longs;
+    if (pl.bucket && hv[14]) ctx->stream.longs = true;
     // more than the room left: stage by stage
-    if (c0h > pl.ccap || R > pl.scap || M > pl.mcap) return nullptr;
+    if (hv[13] || missed || c0h > pl.ccap || R > pl.scap || M > pl.mcap) return nullptr;
     if (M > 1 && (hv[1] & 0xFFFFFFFFu) != (hv[1] >> 32)) throw Error(MJ_EDEVICE, "group boundary mismatch");
     if (hv[8]) throw Error(MJ_ECAPACITY, "a pair's band exceeds the verifier window");
     mj_pairs *out = new mj_pairs();
@@ -580,7 +681,9 @@ static mj_pairs *finish_streamed(mj_ctx *ctx, const StreamedPlan &pl, const Stre
         stats->members = M;
     }
     // keep the rates current (capacities of the next join)
-    ctx->stream.cand_per_record = (double)c0h / (double)pl.rcap;
+    // (the candidates' rate falls slowly: collections of one kind differ by more than the room)
+    ctx->stream.cand_per_record = std::max((double)c0h / (double)pl.rcap,
+                                           0.99 * ctx->stream.cand_per_record);
     ctx->stream.rec_per_bound = (double)R / (double)pl.rcap;
     ctx->stream.mem_per_bound = (double)M / (double)pl.rcap;
     ctx->stream.candidates = C;
@@ -744,11 +847,14 @@ extern "C" mj_status mj_join(mj_ctx *ctx, const mj_strings *strings, const mj_pa
     if (batched && !ctx->no_tuning && stats) {
         // what the streamed join of the next call with these parameters needs
         StreamHints &h = ctx->stream;
+        const double had = hints_match(h, strings, params) ? 0.99 * h.cand_per_record : 0.0;
         h.valid = true;
         h.q = params->q; h.t_div = params->t_div; h.t_fixed = params->t_fixed; h.reps = params->reps;
         h.seed = params->seed; h.k = params->k; h.sigma = strings->sigma; h.packing = strings->packing;
         h.verify_lanes = params->verify_lanes;
-        h.cand_per_record = (double)ctx->last_c0 / (double)std::max<int64_t>(ctx->last_rcap, 1);
+        h.cand_per_record = std::max(had, (double)ctx->last_c0 / (double)std::max<int64_t>(ctx->last_rcap, 1));
+        h.longs = (had > 0.0 && h.longs) || ctx->last_longs;
+        h.bucket = ctx->last_bucket;
         h.rec_per_bound = (double)ctx->last_R / (double)std::max<int64_t>(ctx->last_rcap, 1);
         h.mem_per_bound = (double)ctx->last_M / (double)std::max<int64_t>(ctx->last_rcap, 1);
         h.emit = emit_hints((uint64_t)stats->pair_tests, ctx->last_small_tests, ctx->last_units,

@@ -21,6 +21,8 @@ struct StreamHints {
     EmitHints emit;
     int verify_g = 0, verify_blocks = 0;
     int64_t candidates = 0;      // distinct candidates
+    bool bucket = false;         // grouped by LDS buckets, which all fitted
+    bool longs = false;          // some of whose slots were long
 };
 
 // Sizes of a streamed join, fixed by the set-up read-back and the hints of the last join,
@@ -32,6 +34,9 @@ struct StreamedPlan {
     bool members = false;  // the member filter runs; mcap: room for its records
     int64_t mcap = 0;
     EmitHints emit;
+    // grouping, pair tests and dedup by LDS buckets; about how many records and candidates
+    bool bucket = false, longs = false;
+    int64_t rexp = 0, cexp = 0;
 };
 struct StreamedDev {
     uint64_t *outbuf = nullptr;
@@ -76,6 +81,7 @@ struct mj_ctx {
     // pair tests of the small groups and tile pairs of the large ones
     int64_t last_c0 = 0, last_R = 0, last_rcap = 0, last_M = 0;
     uint64_t last_small_tests = 0, last_units = 0;
+    bool last_bucket = false, last_longs = false;
 };
 
 struct mj_pairs {

@@ -163,7 +163,7 @@ int64_t compact_flags(const uint8_t *flags, int64_t n, int64_t *idx_out, Workspa
 const uint32_t *compact_flags_async(const uint8_t *flags, int64_t n, int64_t *idx_out,
                                     Workspace &ws, hipStream_t s);
 // Size of the pinned host buffer each context keeps for small device-to-host reads.
-constexpr size_t HOST_SCRATCH_BYTES = 16384;
+constexpr size_t HOST_SCRATCH_BYTES = 32768;
 
 // Stable sort of keys (and an optional payload) ascending, in place.  key_mask has a 1
 // at every bit that may be set in some key (the others must be zero in all keys).
@@ -174,6 +174,10 @@ constexpr size_t HOST_SCRATCH_BYTES = 16384;
 void radix_sort(uint64_t *key, uint64_t *val, int64_t n, uint64_t key_mask, Workspace &ws,
                 hipStream_t s, const int64_t *n_dev = nullptr, uint64_t *k2 = nullptr,
                 uint64_t *v2 = nullptr, uint64_t **sorted_keys = nullptr);
+// One stable pass by the 8 key bits from `shift` up, from kin (and vin, nullable) to kout
+// (and vout); n_dev as for radix_sort.
+void radix_pass(const uint64_t *kin, const uint64_t *vin, uint64_t *kout, uint64_t *vout, int64_t n,
+                int shift, Workspace &ws, hipStream_t s, const int64_t *n_dev);
 // Records (key, payload) sorted by the full 64-bit key, in place; equal keys keep their
 // order only up to the runs that the repair step reorders.
 void sort_records(uint64_t *key, uint64_t *val, int64_t n, Workspace &ws, hipStream_t s,
@@ -360,6 +364,48 @@ int64_t probe_candidates(const uint64_t *qkey, const uint64_t *qval, int64_t RQ,
                          const DevStrings &qd, const DevStrings &id, uint64_t *out,
                          int64_t cap, uint64_t *tests_out, Workspace &ws, hipStream_t s,
                          uint64_t *host_scratch);
+
+// bucket.hip
+// Joins of up to BK_RECORDS_MAX records over fewer than 2^29 symbols: grouping, pair tests
+// and dedup by buckets in LDS, a general path's results without its sorts.
+constexpr int64_t BK_RECORDS_MAX = (int64_t)1 << 23;
+struct BucketRecords {
+    uint64_t *key = nullptr, *val = nullptr;  // grouped by their top `bits` key bits
+    int64_t n = 0;                            // records, or their capacity (n_dev)
+    const int64_t *n_dev = nullptr;
+    int bits = 0;
+    int blocks = 0;
+    // one block of 3 * blocks + 3 words: pair tests, groups and members by workgroup; then the
+    // candidates' number, over (set when a bucket does not fit: nothing else is then worth
+    // reading) and the long slots' state (slots << 40 | records)
+    uint64_t *part = nullptr;
+    unsigned long long *counter = nullptr;
+    uint32_t *over = nullptr;
+    // records of the long slots, the slots, and their tile pairs' prefix
+    uint64_t *xkey = nullptr;
+    int4 *xrec = nullptr;
+    int64_t xcap = 0, xslots = 0;
+    ulonglong2 *xslot = nullptr;
+    uint64_t *ustart = nullptr;
+};
+bool bucket_join_fits(int64_t records, int64_t total);
+// expect: how many records there may be (speed, and whether the buckets fit)
+BucketRecords bucket_records(uint64_t *key, uint64_t *val, int64_t cap, int64_t expect,
+                             const int64_t *n_dev, Workspace &ws, hipStream_t s);
+void bucket_reset(const BucketRecords &r, hipStream_t s);  // before a second bucket_pairs
+// emit: the candidates to out[0 .. cap), their number (which may exceed cap) added to
+// *r.counter; else the counts alone.  longs: there may be long slots (slots << 40 is not 0
+// after a count).
+void bucket_pairs(const BucketRecords &r, const DevStrings &d, bool emit, uint64_t *out, int64_t cap,
+                  bool longs, hipStream_t s, KTimer *kt = nullptr);
+// Whether about `expect` pairs can be deduplicated by buckets.
+bool dedup_buckets_fit(int64_t expect, int32_t n_first, int32_t n_second);
+// The distinct pairs of pairs[0 .. min(cap, *count)), sorted, in *result (workspace, room for
+// cap); returns the device address of their number.  *over is set (never cleared) when a bucket
+// does not fit.  The input is overwritten.
+const uint32_t *dedup_buckets(uint64_t *pairs, int64_t cap, int64_t expect,
+                              const unsigned long long *count, int32_t n_first, int32_t n_second,
+                              uint32_t *over, Workspace &ws, hipStream_t s, uint64_t **result);
 
 // verify.hip
 // flags[i] = ED(A[a], B[b]) <= K for pairs[i] = a << 32 | b; K = max(K_a, K_b) when

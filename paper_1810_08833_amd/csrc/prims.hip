@@ -749,6 +749,35 @@ __global__ __launch_bounds__(RS_THREADS) __attribute__((amdgpu_waves_per_eu(4, 4
     }
 }
 
+static void radix_pass_impl(const uint64_t *kin, const uint64_t *vin, uint64_t *kout, uint64_t *vout,
+                            int64_t n, int shift, bool build, Workspace &ws, hipStream_t s,
+                            const int64_t *n_dev) {
+    const int64_t ntiles = (n + RS_TILE - 1) / RS_TILE;
+    if (ntiles > 0x7FFFFFFFLL || 256 * ntiles > 0xFFFFFFF0LL)
+        throw Error(MJ_ECAPACITY, "radix pass: too many tiles");
+    uint32_t *cnt = ws.get_n<uint32_t>(256 * ntiles + 1);
+    uint32_t *off = ws.get_n<uint32_t>(256 * ntiles + 1);
+    hipLaunchKernelGGL(k_rs_tile_counts, dim3((unsigned)ntiles), dim3(RS_THREADS), 0, s, kin, n,
+                       shift, ntiles, cnt, n_dev);
+    MJ_LAUNCH_CHECK();
+    exclusive_scan_u32(cnt, off, 256 * ntiles, ws, s);
+    if (build)
+        hipLaunchKernelGGL((k_rs_scatter<false, true>), dim3((unsigned)ntiles), dim3(RS_THREADS), 0,
+                           s, kin, nullptr, kout, nullptr, n, shift, ntiles, off, n_dev);
+    else if (vin)
+        hipLaunchKernelGGL((k_rs_scatter<true, false>), dim3((unsigned)ntiles), dim3(RS_THREADS), 0,
+                           s, kin, vin, kout, vout, n, shift, ntiles, off, n_dev);
+    else
+        hipLaunchKernelGGL((k_rs_scatter<false, false>), dim3((unsigned)ntiles), dim3(RS_THREADS), 0,
+                           s, kin, nullptr, kout, nullptr, n, shift, ntiles, off, n_dev);
+    MJ_LAUNCH_CHECK();
+}
+
+void radix_pass(const uint64_t *kin, const uint64_t *vin, uint64_t *kout, uint64_t *vout, int64_t n,
+                int shift, Workspace &ws, hipStream_t s, const int64_t *n_dev) {
+    if (n > 0) radix_pass_impl(kin, vin, kout, vout, n, shift, false, ws, s, n_dev);
+}
+
 void radix_sort(uint64_t *key, uint64_t *val, int64_t n, uint64_t key_mask, Workspace &ws,
                 hipStream_t s, const int64_t *n_dev, uint64_t *k2, uint64_t *v2,
                 uint64_t **sorted_keys) {
@@ -1255,20 +1284,7 @@ __global__ void k_mb_gather(const int64_t *__restrict__ idx, const uint32_t *__r
 
 static void mb_radix_pass(const uint64_t *kin, uint64_t *kout, int64_t n, int shift, bool build,
                           Workspace &ws, hipStream_t s, const int64_t *n_dev) {
-    const int64_t ntiles = (n + RS_TILE - 1) / RS_TILE;
-    uint32_t *cnt = ws.get_n<uint32_t>(256 * ntiles + 1);
-    uint32_t *off = ws.get_n<uint32_t>(256 * ntiles + 1);
-    hipLaunchKernelGGL(k_rs_tile_counts, dim3((unsigned)ntiles), dim3(RS_THREADS), 0, s, kin, n,
-                       shift, ntiles, cnt, n_dev);
-    MJ_LAUNCH_CHECK();
-    exclusive_scan_u32(cnt, off, 256 * ntiles, ws, s);
-    if (build)
-        hipLaunchKernelGGL((k_rs_scatter<false, true>), dim3((unsigned)ntiles), dim3(RS_THREADS), 0,
-                           s, kin, nullptr, kout, nullptr, n, shift, ntiles, off, n_dev);
-    else
-        hipLaunchKernelGGL((k_rs_scatter<false, false>), dim3((unsigned)ntiles), dim3(RS_THREADS), 0,
-                           s, kin, nullptr, kout, nullptr, n, shift, ntiles, off, n_dev);
-    MJ_LAUNCH_CHECK();
+    radix_pass_impl(kin, nullptr, kout, nullptr, n, shift, build, ws, s, n_dev);
 }
 
 void group_members(const uint64_t *key, const uint64_t *val, int64_t n, const int64_t *n_dev,
