@@ -526,6 +526,22 @@ __global__ void k_collect(const int64_t *R, const uint64_t *slot, const unsigned
     dst[12] = slot ? slot[4] : 0;
 }
 
+__global__ void k_collect_search(const int64_t *R, const uint64_t *tests, const unsigned long long *c0,
+                                 const uint32_t *u, const uint32_t *outn,
+                                 const unsigned long long *cells, const uint32_t *symbol_err,
+                                 const uint32_t *over, uint64_t *dst) {
+    if (blockIdx.x != 0 || threadIdx.x != 0) return;
+    dst[0] = (uint64_t)*R;
+    dst[1] = *tests;
+    dst[2] = *c0;
+    dst[3] = *u;
+    dst[4] = *outn;
+    dst[5] = cells[0];
+    dst[6] = cells[1];
+    dst[7] = symbol_err ? *symbol_err : 0;
+    dst[8] = *over;
+}
+
 static bool hints_match(const StreamHints &h, const mj_strings *st, const mj_params *p) {
     return h.valid && h.q == p->q && h.t_div == p->t_div && h.t_fixed == p->t_fixed &&
            h.reps == p->reps && h.seed == p->seed && h.k == p->k && h.sigma == st->sigma &&
@@ -983,6 +999,9 @@ extern "C" mj_status mj_index_build(mj_ctx *ctx, const mj_strings *strings, cons
         ix->planes = (uint32_t *)dev_alloc((size_t)ix->np * ix->plane_words * 4);
         pack_planes(di, ix->np, ws, s, ix->planes);
         sorted_records(di, pk, halo, ix->rec, ws, s, ctx->pinned);
+        ix->dir_bits = key_directory_bits(ix->rec.count);
+        ix->dir = (uint32_t *)dev_alloc((((size_t)1 << ix->dir_bits) + 1) * 4);
+        key_directory(ix->rec.key, ix->rec.count, ix->dir, s);
         if (pp.pi_table) {
             // searches partition their queries with this table long after the caller's
             // copy may be gone: the index keeps its own
@@ -1010,6 +1029,7 @@ extern "C" void mj_index_free(mj_index *ix) {
     dev_free(ix->kk, ix->alloc);
     dev_free(ix->planes, ix->alloc);
     dev_free(ix->pi_table, ix->alloc);
+    dev_free(ix->dir, ix->alloc);
     ix->rec.release();
     delete ix;
 }
@@ -1021,8 +1041,121 @@ extern "C" int64_t mj_index_bytes(const mj_index *ix) {
     int64_t b = ((int64_t)ix->n + 1) * (8 + 4 + 4);  // offsets, lengths, thresholds
     b += (int64_t)ix->np * ix->plane_words * 4;
     b += ix->rec.cap * (8 + 8 + (ix->rec.with_len ? 4 : 0));
+    if (ix->dir) b += (((int64_t)1 << ix->dir_bits) + 1) * 4;
     if (ix->pi_table) b += (int64_t)8 << (ix->pp.q * ix->bits);
     return b;
+}
+
+// The index as the verifier and the probe read it: it keeps no symbols.
+static DevStrings index_strings(const mj_index *ix) {
+    DevStrings id;
+    id.chars = nullptr;
+    id.offsets = ix->offsets;
+    id.n = ix->n;
+    id.sigma = ix->sigma;
+    id.bits = ix->bits;
+    id.total = ix->total;
+    id.len = ix->len;
+    id.kk = ix->kk;
+    id.planes = ix->planes;
+    id.plane_words = ix->plane_words;
+    return id;
+}
+
+// A search whose stages after the per-string set-up are sized by the rates of the context's
+// last search (as the streamed join is): two host reads.  nullptr: more than the room, or no
+// verifier configuration known; the search then runs stage by stage.
+static mj_pairs *run_search_streamed(mj_ctx *ctx, const mj_index *ix, DevStrings &qd,
+                                     const PartitionParams &qp, const SetupInfo &si,
+                                     const mj_params *qparams, StageTimer &tm, hipStream_t s,
+                                     mj_stats *stats) {
+    Workspace &ws = ctx->ws;
+    SearchHints &h = ctx->search;
+    const int cmax = (int)((std::min<int64_t>(qparams->k >= 0 ? qparams->k : si.kmax, 0x3FFFFFFF) + 31) >> 5);
+    if (cmax > persist_max_c()) return nullptr;
+    const int64_t rcap = std::max<int64_t>(si.rec_bound * qp.reps, 2);
+    const double cexp = h.cand_per_record * (double)rcap, vexp = h.verified_per_record * (double)rcap;
+    const double room = 1.25 * cexp + (double)std::max<int64_t>(4096, std::min<int64_t>(65536, rcap));
+    if (room > 2e9 || !dedup_buckets_fit((int64_t)cexp, qd.n, ix->n)) return nullptr;
+    const int64_t ccap = (int64_t)room;
+    VerifyTuning tune;  // (the context's own table is for calls that time their choices)
+    const int ci = std::min(cmax, 63), npi = ix->np / 2 - 1;
+    const int g = qparams->verify_lanes == -2 ? VERIFY_BIDIR
+                : qparams->verify_lanes == -3 ? VERIFY_CLASSES
+                : qparams->verify_lanes ? qparams->verify_lanes
+                : ctx->tune.best_g[ci][npi] ? ctx->tune.best_g[ci][npi] : verify_small_call_lanes(cmax);
+    if (window_words_per_lane(g, cmax) == 0) return nullptr;
+    tune.best_g[ci][npi] = g;
+    tune.best_blocks[ci][npi] = ctx->tune.best_g[ci][npi] && !qparams->verify_lanes
+                                    ? ctx->tune.best_blocks[ci][npi] : 512;
+
+    uint64_t *key = ws.get_n<uint64_t>(rcap + 1), *val = ws.get_n<uint64_t>(rcap + 1);
+    int64_t *R_dev = ws.get_n<int64_t>(2);
+    partition_records_streamed(qd, qp, si, key, val, R_dev, ws, s, &ctx->kt);
+    tm.mark();  // 1 partition
+    tm.mark();  // 2 sort: none
+    const DevStrings id = index_strings(ix);
+    const Probe pr = probe_ranges(key, rcap, R_dev, ix->rec.key, ix->dir, ix->dir_bits, ws, s);
+    uint64_t *cand = ws.get_n<uint64_t>(ccap + 1);
+    probe_emit(pr, val, ix->rec.val, qd, id, (uint64_t)(1.25 * h.tests_per_record * (double)rcap) + 4096,
+               cand, ccap, s);
+    tm.mark();  // 3 probe + filter
+    uint64_t *uniq = nullptr;
+    uint32_t *over = ws.get_n<uint32_t>(2);
+    fill_u32(over, 0, 1, s);
+    const uint32_t *u = dedup_buckets(cand, ccap, (int64_t)cexp, pr.counter, qd.n, ix->n, over, ws, s, &uniq);
+    tm.mark();  // 4 dedup
+    uint8_t *flags = ws.get_n<uint8_t>(ccap + 4);
+    unsigned long long *cells = nullptr;
+    verify_pairs_batched_streamed(uniq, ccap, u, qd, id, 1, cmax, flags, ws, s, &ctx->kt, tune,
+                                  qparams->verify_lanes, (int64_t)vexp, &cells);
+    tm.mark();  // 5 verify
+    int64_t *idx = ws.get_n<int64_t>(ccap + 1);
+    const uint32_t *on = compact_flags_async(flags, ccap, idx, ws, s);
+    uint64_t *outbuf = ws.get_n<uint64_t>(ccap + 1);
+    gather_u64(uniq, idx, outbuf, ccap, s, on);
+    uint64_t *res = ws.get_n<uint64_t>(16);
+    hipLaunchKernelGGL(k_collect_search, dim3(1), dim3(64), 0, s, (const int64_t *)R_dev, pr.tests,
+                       (const unsigned long long *)pr.counter, u, on, (const unsigned long long *)cells,
+                       (const uint32_t *)qd.symbol_err, (const uint32_t *)over, res);
+    MJ_LAUNCH_CHECK();
+    MJ_HIP(hipMemcpyAsync(ctx->pinned, res, 9 * 8, hipMemcpyDeviceToHost, s));
+    MJ_HIP(hipStreamSynchronize(s));
+    uint64_t hv[9];
+    memcpy(hv, ctx->pinned, sizeof(hv));
+    const int64_t R = (int64_t)hv[0], c0 = (int64_t)hv[2], C = (int64_t)hv[3], nout = (int64_t)hv[4];
+    if (hv[7]) throw Error(MJ_EINVAL, "a symbol code is not below sigma");
+    if (hv[8] || c0 > ccap) return nullptr;
+    if (hv[6]) throw Error(MJ_ECAPACITY, "a pair's band exceeds the verifier window");
+    mj_pairs *out = new mj_pairs();
+    out->alloc = t_dev_alloc;
+    out->stream = s;
+    out->n = nout;
+    try {
+        out->d = (uint64_t *)result_alloc((size_t)(nout + 1) * 8, out->alloc, s);
+        if (nout) MJ_HIP(hipMemcpyAsync(out->d, outbuf, (size_t)nout * 8, hipMemcpyDeviceToDevice, s));
+    } catch (...) {
+        mj_pairs_free(out);
+        throw;
+    }
+    tm.mark();  // 6 output
+    if (stats) {
+        stats->records = R;
+        stats->pair_tests = (int64_t)hv[1];
+        stats->candidates = C;
+        stats->output = nout;
+        stats->band_cells = (int64_t)hv[5];
+        stats->positions = qd.total * qp.reps;
+        stats->verify_group = lanes_code(g);
+        stats->verify_words = window_words_per_lane(g, cmax);
+        stats->verify_blocks = tune.best_blocks[ci][npi];
+        stats->streamed = 1;
+        stats->host_reads = 2;
+    }
+    h.cand_per_record = std::max((double)c0 / (double)rcap, 0.99 * h.cand_per_record);
+    h.tests_per_record = (double)hv[1] / (double)rcap;
+    h.verified_per_record = (double)C / (double)rcap;
+    return out;
 }
 
 extern "C" mj_status mj_search(mj_ctx *ctx, const mj_index *ix, const mj_strings *queries,
@@ -1053,39 +1186,45 @@ extern "C" mj_status mj_search(mj_ctx *ctx, const mj_index *ix, const mj_strings
     PartitionParams qp = ix->pp;  // q, seed, T rule, reps of the index
     qp.k = qparams->k;
     qp.k_per_string = qparams->k_per_string;
-    int32_t halo = prepare_strings(qd, qp, ws, s, ctx->pinned);
+    SetupInfo si;
+    int32_t halo = prepare_strings(qd, qp, ws, s, ctx->pinned, &si);
     pack_planes(qd, ix->np, ws, s);
     tm.mark();  // 0 setup
+    const bool batched = qparams->verifier == MJ_VERIFY_BATCHED;
+    SearchHints &h = ctx->search;
+    if (batched && ctx->streaming && h.valid && h.n == ix->n && h.records == ix->rec.count &&
+        h.verify_lanes == qparams->verify_lanes && ix->rec.count > 0 && qd.n > 0) {
+        mj_pairs *r = run_search_streamed(ctx, ix, qd, qp, si, qparams, tm, s, stats);
+        if (r) {
+            tm.fill(stats);
+            *out = r;
+            return MJ_OK;
+        }
+        tm = StageTimer(ctx, s);  // stage by stage: its times from here on
+        tm.mark();
+        if (stats) memset(stats, 0, sizeof(*stats));
+    }
     RecBuf rb;
     rb.ws = &ws;
     partition_records(qd, qp, halo, rb, ws, s, ctx->pinned, &ctx->kt);
     tm.mark();  // 1 partition
-    if (rb.count > 1) {
-        sort_records(rb.key, rb.val, rb.count, ws, s, ctx->pinned);
-    }
-    tm.mark();  // 2 sort
-    DevStrings id;  // the index keeps no symbols: planes, lengths and thresholds only
-    id.chars = nullptr;
-    id.offsets = ix->offsets;
-    id.n = ix->n;
-    id.sigma = ix->sigma;
-    id.bits = ix->bits;
-    id.total = ix->total;
-    id.len = ix->len;
-    id.kk = ix->kk;
-    id.planes = ix->planes;
-    id.plane_words = ix->plane_words;
+    tm.mark();  // 2 sort: none (the directory takes the query records in any order)
+    const DevStrings id = index_strings(ix);
     uint64_t tests = 0;
-    int64_t need = probe_candidates(rb.key, rb.val, rb.count, ix->rec.key, ix->rec.val, ix->rec.count,
-                                    qd, id, nullptr, -1, &tests, ws, s, ctx->pinned);
-    (void)need;
-    if (tests > (uint64_t)0x7FFFFFFF)
-        throw Error(MJ_ECAPACITY, "record-pair tests exceed 2^31");
-    uint64_t *cand = ws.get_n<uint64_t>(tests + 1);
-    int64_t c0 = tests ? probe_candidates(rb.key, rb.val, rb.count, ix->rec.key, ix->rec.val,
-                                          ix->rec.count, qd, id, cand, (int64_t)tests, &tests, ws, s,
-                                          ctx->pinned)
-                       : 0;
+    uint64_t *cand = nullptr;
+    int64_t c0 = 0;
+    if (rb.count > 0 && ix->rec.count > 0) {
+        const Probe pr = probe_ranges(rb.key, rb.count, nullptr, ix->rec.key, ix->dir, ix->dir_bits, ws, s);
+        tests = read_back<uint64_t>(pr.tests, s, ctx->pinned);
+        if (tests > (uint64_t)0x7FFFFFFF)
+            throw Error(MJ_ECAPACITY, "record-pair tests exceed 2^31");
+        if (tests) {
+            cand = ws.get_n<uint64_t>(tests + 1);
+            probe_emit(pr, rb.val, ix->rec.val, qd, id, tests, cand, (int64_t)tests, s);
+            c0 = (int64_t)read_back<uint64_t>((const uint64_t *)pr.counter, s, ctx->pinned);
+            if (c0 > (int64_t)tests) throw Error(MJ_ECAPACITY, "candidate buffer overflow");
+        }
+    }
     tm.mark();  // 3 probe + filter
     uint64_t *uniq = nullptr;
     int64_t C = dedup_pairs(cand, c0, qd.n, ix->n, ws, s, ctx->pinned, &uniq, true);
@@ -1103,6 +1242,18 @@ extern "C" mj_status mj_search(mj_ctx *ctx, const mj_index *ix, const mj_strings
         stats->output = res->n;
         stats->band_cells = cells;
         stats->positions = qd.total * qp.reps;
+    }
+    if (batched) {
+        // what the next search's stages are sized by
+        const double bound = (double)std::max<int64_t>(si.rec_bound * qp.reps, 2);
+        const bool same = h.valid && h.n == ix->n && h.records == ix->rec.count;
+        h.cand_per_record = std::max((double)c0 / bound, same ? 0.99 * h.cand_per_record : 0.0);
+        h.tests_per_record = (double)tests / bound;
+        h.verified_per_record = (double)C / bound;
+        h.valid = true;
+        h.n = ix->n;
+        h.records = ix->rec.count;
+        h.verify_lanes = qparams->verify_lanes;
     }
     tm.fill(stats);
     *out = res;

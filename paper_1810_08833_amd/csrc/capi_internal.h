@@ -25,6 +25,16 @@ struct StreamHints {
     bool longs = false;          // some of whose slots were long
 };
 
+// The same for searches: rates per record bound of the last search of the context, for an
+// index of as many strings and records.
+struct SearchHints {
+    bool valid = false;
+    int32_t n = 0;
+    int64_t records = 0;
+    int32_t verify_lanes = 0;
+    double cand_per_record = 0, tests_per_record = 0, verified_per_record = 0;
+};
+
 // Sizes of a streamed join, fixed by the set-up read-back and the hints of the last join,
 // and the device buffer the host copies the result from after the final read.
 struct StreamedPlan {
@@ -74,6 +84,7 @@ struct mj_ctx {
     uint32_t member_big = 1u << 16;             // its buckets above this are kept whole
     int streaming = 1;  // 0 stage by stage, 1 streamed, 2 streamed and captured (mj_ctx_set_streaming)
     StreamHints stream;
+    SearchHints search;
     JoinGraph graph;
     hipStream_t cap_stream = nullptr;  // the stream graphs are captured on
     int streamed_joins = 0, stream_fallbacks = 0;
@@ -107,6 +118,8 @@ struct mj_index {
     int np = 0;
     uint64_t *pi_table = nullptr;  // the index's own copy of an injected Pi table
     RecBuf rec;  // sorted by key
+    uint32_t *dir = nullptr;  // first record by top key bits (2^dir_bits + 1 entries)
+    int dir_bits = 0;
     mj_allocator alloc{};  // the allocator that made the index's arrays
 };
 

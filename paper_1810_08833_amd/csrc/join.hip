@@ -1071,21 +1071,52 @@ const uint32_t *dedup_pairs_streamed(uint64_t *pairs, int64_t cap, const unsigne
 }
 
 // ---------------------------------------------------------------- search probe
-// For each query record, the equal-key range of the sorted index records.
-__global__ void k_probe_ranges(const uint64_t *qkey, int64_t RQ, const uint64_t *ikey, int64_t RI,
-                               int64_t *lo_out, uint64_t *cnt) {
+// dir[t] = the first of the sorted keys whose top `bits` bits are >= t, t = 0 .. 2^bits: one
+// pass over the keys, each writing the entries between its predecessor's bits and its own.
+__global__ void k_key_directory(const uint64_t *__restrict__ key, int64_t n, int bits,
+                                uint32_t *__restrict__ dir) {
+    auto top = [&](int64_t i) -> int64_t {
+        return i < 0 ? -1 : i >= n ? (1ll << bits) : bits ? (int64_t)(key[i] >> (64 - bits)) : 0;
+    };
+    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    for (; i <= n; i += stride) {
+        const int64_t hi = top(i);
+        for (int64_t t = top(i - 1) + 1; t <= hi; t++) dir[t] = (uint32_t)i;
+    }
+}
+
+int key_directory_bits(int64_t n) { return std::max(0, std::min(26, ceil_log2((uint64_t)std::max<int64_t>(n, 1)) - 5)); }
+
+void key_directory(const uint64_t *key, int64_t n, uint32_t *dir, hipStream_t s) {
+    hipLaunchKernelGGL(k_key_directory, dim3(grid_for(n + 1, 256, 16384)), dim3(256), 0, s, key, n,
+                       key_directory_bits(n), dir);
+    MJ_LAUNCH_CHECK();
+}
+
+// For each query record, the equal-key range of the sorted index records: two binary searches
+// of the whole array are about 56 dependent reads for 287 M records, the 16 to 32 records of a
+// directory entry lie in a few cache lines.
+__global__ void k_probe_ranges(const uint64_t *__restrict__ qkey, int64_t RQ,
+                               const int64_t *__restrict__ RQ_dev,
+                               const uint64_t *__restrict__ ikey,
+                               const uint32_t *__restrict__ dir, int bits,
+                               uint32_t *__restrict__ lo_out, uint64_t *__restrict__ cnt) {
+    if (RQ_dev) RQ = min(RQ, *RQ_dev);
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     int64_t stride = (int64_t)gridDim.x * blockDim.x;
     for (; i < RQ; i += stride) {
-        uint64_t k = qkey[i];
-        int64_t lo = 0, hi = RI;  // first index with ikey >= k
+        const uint64_t k = qkey[i];
+        const int64_t t = bits ? (int64_t)(k >> (64 - bits)) : 0;
+        const uint32_t d1 = dir[t + 1];
+        uint32_t lo = dir[t], hi = d1;  // first index with ikey >= k
         while (lo < hi) {
-            int64_t mid = (lo + hi) >> 1;
+            const uint32_t mid = lo + (hi - lo) / 2;
             if (ikey[mid] < k) lo = mid + 1; else hi = mid;
         }
-        int64_t e = lo, hi2 = RI;  // first index with ikey > k
+        uint32_t e = lo, hi2 = d1;  // first index with ikey > k
         while (e < hi2) {
-            int64_t mid = (e + hi2) >> 1;
+            const uint32_t mid = e + (hi2 - e) / 2;
             if (ikey[mid] <= k) e = mid + 1; else hi2 = mid;
         }
         lo_out[i] = lo;
@@ -1094,9 +1125,10 @@ __global__ void k_probe_ranges(const uint64_t *qkey, int64_t RQ, const uint64_t 
 }
 
 __global__ __launch_bounds__(EMIT_BLOCK) void k_probe_emit(const uint64_t *__restrict__ qval,
-                                                    const int64_t *__restrict__ lo_arr,
+                                                    const uint32_t *__restrict__ lo_arr,
                                                     const uint64_t *__restrict__ ts, int64_t RQ,
-                                                    uint64_t P, const uint64_t *__restrict__ ival,
+                                                    const int64_t *__restrict__ RQ_dev,
+                                                    const uint64_t *__restrict__ ival,
                                                     const int32_t *__restrict__ qlen,
                                                     const int32_t *__restrict__ qk,
                                                     const int32_t *__restrict__ ilen,
@@ -1105,6 +1137,8 @@ __global__ __launch_bounds__(EMIT_BLOCK) void k_probe_emit(const uint64_t *__res
     __shared__ EmitStage st;
     if (threadIdx.x == 0) st.n = 0;
     __syncthreads();
+    if (RQ_dev) RQ = min(RQ, *RQ_dev);
+    const uint64_t P = RQ > 0 ? ts[RQ] : 0;
     const uint64_t nthreads = (uint64_t)gridDim.x * EMIT_BLOCK;
     for (uint64_t t0 = ((uint64_t)blockIdx.x * EMIT_BLOCK + threadIdx.x) * EMIT_CHUNK; ;
          t0 += nthreads * EMIT_CHUNK) {
@@ -1132,11 +1166,13 @@ __global__ __launch_bounds__(EMIT_BLOCK) void k_probe_emit(const uint64_t *__res
                     j = 0;
                     r++;
                 }
-                uint64_t qv = qval[r];
-                uint64_t iv = ival[lo_arr[r] + (int64_t)j];
-                int32_t qi = (int32_t)(qv >> 32), si = (int32_t)(iv >> 32);
-                pass = pass_filter(qlen[qi], (int64_t)(uint32_t)qv, ilen[si], (int64_t)(uint32_t)iv,
-                                   qk[qi]);
+                const uint64_t qv = qval[r];
+                const uint64_t iv = ival[lo_arr[r] + (int64_t)j];
+                const int32_t qi = (int32_t)(qv >> 32), si = (int32_t)(iv >> 32);
+                const int64_t pq = (int64_t)(uint32_t)qv, ps = (int64_t)(uint32_t)iv, K = qk[qi];
+                // the positions alone decide most: |pos_i - pos_j| <= K whenever the filter
+                // passes, and the index string's length is a gather of its own
+                if (iabs64(pq - ps) <= K) pass = pass_filter(qlen[qi], pq, ilen[si], ps, K);
                 pairkey = ((uint64_t)(uint32_t)qi << 32) | (uint64_t)(uint32_t)si;
                 j++;
             }
@@ -1146,33 +1182,33 @@ __global__ __launch_bounds__(EMIT_BLOCK) void k_probe_emit(const uint64_t *__res
     }
 }
 
-int64_t probe_candidates(const uint64_t *qkey, const uint64_t *qval, int64_t RQ,
-                         const uint64_t *ikey, const uint64_t *ival, int64_t RI,
-                         const DevStrings &qd, const DevStrings &id, uint64_t *out, int64_t cap,
-                         uint64_t *tests_out, Workspace &ws, hipStream_t s, uint64_t *host_scratch) {
-    *tests_out = 0;
-    if (RQ == 0 || RI == 0) return 0;
-    int64_t *lo = ws.get_n<int64_t>(RQ + 1);
+Probe probe_ranges(const uint64_t *qkey, int64_t RQ, const int64_t *RQ_dev, const uint64_t *ikey,
+                   const uint32_t *dir, int bits, Workspace &ws, hipStream_t s) {
+    Probe p;
+    p.RQ = RQ;
+    p.RQ_dev = RQ_dev;
+    p.lo = ws.get_n<uint32_t>(RQ + 1);
     uint64_t *cnt = ws.get_n<uint64_t>(RQ + 1);
-    uint64_t *ts = ws.get_n<uint64_t>(RQ + 1);
+    p.ts = ws.get_n<uint64_t>(RQ + 1);
+    p.tests = ws.get_n<uint64_t>(2);
+    p.counter = (unsigned long long *)(p.tests + 1);
+    fill_u64(p.tests, 0, 2, s);
     hipLaunchKernelGGL(k_probe_ranges, dim3(grid_for(RQ, 256, 16384)), dim3(256), 0, s, qkey, RQ,
-                       ikey, RI, lo, cnt);
+                       RQ_dev, ikey, dir, bits, p.lo, cnt);
     MJ_LAUNCH_CHECK();
-    exclusive_scan_u64(cnt, ts, RQ, ws, s);
-    uint64_t P = read_back<uint64_t>(ts + RQ, s, host_scratch);
-    *tests_out = P;
-    if (P == 0) return 0;
-    if (cap < 0) return -(int64_t)P;
-    unsigned long long *counter = (unsigned long long *)ws.get_n<uint64_t>(2);
-    fill_u64((uint64_t *)counter, 0, 1, s);
-    uint64_t threads = (P + EMIT_CHUNK - 1) / EMIT_CHUNK;
-    unsigned grid = (unsigned)std::min<uint64_t>((threads + EMIT_BLOCK - 1) / EMIT_BLOCK, 1u << 16);
-    hipLaunchKernelGGL(k_probe_emit, dim3(grid), dim3(EMIT_BLOCK), 0, s, qval, lo, ts, RQ, P, ival,
-                       qd.len, qd.kk, id.len, out, cap, counter);
+    // (a count below 2^32: its low word)
+    exclusive_scan_u64_dev(cnt, p.ts, RQ, reinterpret_cast<const uint32_t *>(RQ_dev), p.tests, ws, s);
+    return p;
+}
+
+void probe_emit(const Probe &p, const uint64_t *qval, const uint64_t *ival, const DevStrings &qd,
+                const DevStrings &id, uint64_t expect, uint64_t *out, int64_t cap, hipStream_t s) {
+    const uint64_t threads = (expect + EMIT_CHUNK - 1) / EMIT_CHUNK;
+    const unsigned grid = (unsigned)std::max<uint64_t>(
+        1, std::min<uint64_t>((threads + EMIT_BLOCK - 1) / EMIT_BLOCK, 1u << 16));
+    hipLaunchKernelGGL(k_probe_emit, dim3(grid), dim3(EMIT_BLOCK), 0, s, qval, p.lo, p.ts, p.RQ,
+                       p.RQ_dev, ival, qd.len, qd.kk, id.len, out, cap, p.counter);
     MJ_LAUNCH_CHECK();
-    uint64_t c = read_back<uint64_t>((const uint64_t *)counter, s, host_scratch);
-    if ((int64_t)c > cap) throw Error(MJ_ECAPACITY, "candidate buffer overflow");
-    return (int64_t)c;
 }
 
 }  // namespace mj

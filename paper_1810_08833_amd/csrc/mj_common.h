@@ -358,12 +358,24 @@ int64_t emit_candidates(const uint64_t *val, int64_t R, const GroupInfo &g, cons
 // (result_alloc with the thread's allocator on s) that the caller owns.
 int64_t dedup_pairs(uint64_t *pairs, int64_t n, int32_t n_first, int32_t n_second, Workspace &ws,
                     hipStream_t s, uint64_t *host_scratch, uint64_t **result, bool to_ws);
-// Search: probe sorted index keys with sorted query records.
-int64_t probe_candidates(const uint64_t *qkey, const uint64_t *qval, int64_t RQ,
-                         const uint64_t *ikey, const uint64_t *ival, int64_t RI,
-                         const DevStrings &qd, const DevStrings &id, uint64_t *out,
-                         int64_t cap, uint64_t *tests_out, Workspace &ws, hipStream_t s,
-                         uint64_t *host_scratch);
+// Search: a directory of the sorted index keys by their top bits (about 16 to 32 keys an entry;
+// 2^bits + 1 entries), and the probe of the index with query records (in any order).
+int key_directory_bits(int64_t n);
+void key_directory(const uint64_t *key, int64_t n, uint32_t *dir, hipStream_t s);
+struct Probe {
+    int64_t RQ = 0;                  // query records, or their capacity (RQ_dev)
+    const int64_t *RQ_dev = nullptr;
+    uint32_t *lo = nullptr;          // first equal-key index record of each
+    uint64_t *ts = nullptr;          // exclusive prefix of the ranges' sizes
+    uint64_t *tests = nullptr;       // their sum (device)
+    unsigned long long *counter = nullptr;  // candidates emitted (device)
+};
+Probe probe_ranges(const uint64_t *qkey, int64_t RQ, const int64_t *RQ_dev, const uint64_t *ikey,
+                   const uint32_t *dir, int bits, Workspace &ws, hipStream_t s);
+// The pairs through the filter to out[0 .. cap), their number (which may exceed cap) to
+// *p.counter; expect: how many tests there may be (speed only).
+void probe_emit(const Probe &p, const uint64_t *qval, const uint64_t *ival, const DevStrings &qd,
+                const DevStrings &id, uint64_t expect, uint64_t *out, int64_t cap, hipStream_t s);
 
 // bucket.hip
 // Joins of up to BK_RECORDS_MAX records over fewer than 2^29 symbols: grouping, pair tests

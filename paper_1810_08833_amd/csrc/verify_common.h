@@ -50,6 +50,42 @@ __device__ __forceinline__ uint32_t load_dir(const uint32_t *plane, int64_t bitp
 constexpr int QUEUES = 32;
 constexpr int QSTRIDE = 32;  // uint64 words between two sub-queue counters (256 bytes)
 
+// The next pairs (their ranks in the order) for the lanes that ask, -1 where there is none
+// left; whole wave.  qj: the wave's current sub-queue; done is set once every sub-queue is dry.
+// A wave that finds its sub-queue dry reads all counters and goes on where there are pairs.
+// (Trying the sub-queues one by one, one a block of columns, every wave ended with up to 32
+// blocks of idle columns and an atomic each: 75 us of a launch, whatever its pairs.)
+__device__ __forceinline__ long long take_pairs(unsigned long long *next, int64_t n, bool ask,
+                                                int &qj, bool &done) {
+    const int lane = threadIdx.x & 63;
+    long long got = -1;
+    for (uint64_t req = __ballot(ask); req && !done; req = __ballot(ask && got < 0)) {
+        const int first = __ffsll((unsigned long long)req) - 1;
+        const long long size = n > qj ? (n - qj + QUEUES - 1) / QUEUES : 0;
+        const long long want = __popcll(req);
+        unsigned long long base = 0;
+        if (lane == first) base = atomicAdd(next + qj * QSTRIDE, (unsigned long long)want);
+        // (wave-uniform, in scalar registers: a few vector registers more and the kernels' 4
+        // waves a SIMD become 3)
+        const uint32_t blo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)base, first);
+        const uint32_t bhi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(base >> 32), first);
+        const long long b0 = (long long)(((uint64_t)bhi << 32) | blo);
+        const long long room = size - b0;  // pairs left here, for the first askers
+        const int rank = __popcll(req & ((1ull << lane) - 1));
+        if (ask && got < 0 && rank < room) got = (b0 + rank) * QUEUES + qj;
+        if (want <= room) break;
+        long long left = 0;
+        if (lane < QUEUES && n > lane)
+            left = (n - lane + QUEUES - 1) / QUEUES -
+                   (long long)__hip_atomic_load(next + lane * QSTRIDE, __ATOMIC_RELAXED,
+                                                __HIP_MEMORY_SCOPE_AGENT);
+        const uint64_t some = __ballot(left > 0), after = some & (~0ull << (qj + 1));
+        if (!some) done = true;
+        else qj = __ffsll((unsigned long long)(after ? after : some)) - 1;
+    }
+    return got;
+}
+
 // The launch of the skewed band (verify_ring.hip): pairs in the class order of ring_class,
 // off[] the bin offsets of that order (bins per class: RING_BINS, widest class first).
 using PersistClassKernel = void (*)(const uint64_t *, const int64_t *, const uint32_t *, VSet, VSet,

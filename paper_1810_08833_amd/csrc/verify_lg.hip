@@ -77,9 +77,8 @@ __device__ __forceinline__ void persist_body(const uint64_t *__restrict__ pairs,
     const int g = lane & (G - 1);
     const int leader_lane = lane - g;
     bool active = false, exhausted = false;
-    // wave-uniform: current sub-queue and how many sub-queues were found dry
+    // wave-uniform: the current sub-queue
     int qj = (int)((blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)) % QUEUES);
-    int qdry = 0;
     int64_t pi = 0;
     int32_t K = 0, mp = 0, nt = 0, wlo = 0, jb = 0, S = 0, band = 0, phi = 32;
     int64_t offx = 0, offy = 0;
@@ -98,23 +97,7 @@ __device__ __forceinline__ void persist_body(const uint64_t *__restrict__ pairs,
     for (;;) {
         // ---- refill: each group without a pair takes the next one
         const bool need = !active && !exhausted;
-        const uint64_t req = __ballot(need && g == 0);
-        long long got = -1;
-        if (req) {
-            const int first = __ffsll((unsigned long long)req) - 1;
-            const long long qn = n > qj ? (n - qj + QUEUES - 1) / QUEUES : 0;  // sub-queue size
-            const long long want = __popcll(req);
-            unsigned long long base = 0;
-            if (lane == first) base = atomicAdd(next + qj * QSTRIDE, (unsigned long long)want);
-            const long long b0 = (long long)__shfl(base, first, 64);
-            const long long k = b0 + __popcll(req & ((1ull << lane) - 1));
-            if (need && g == 0 && k < qn) got = k * QUEUES + qj;
-            if (b0 + want > qn) {  // this sub-queue is dry from now on
-                qj = qj + 1 == QUEUES ? 0 : qj + 1;
-                if (++qdry == QUEUES) exhausted = true;  // every sub-queue is dry
-            }
-        }
-        got = __shfl(got, leader_lane, 64);
+        const long long got = __shfl(take_pairs(next, n, need && g == 0, qj, exhausted), leader_lane, 64);
         if (need) {
             if (got < 0 || got >= n) {
                 // no pair this time: retried on the next sub-queue unless all are dry
@@ -416,7 +399,6 @@ __global__ __launch_bounds__(256) void k_verify_bidir(const uint64_t *__restrict
     int lbv = 0;  // lower bound of this half's window values at its current column
     uint8_t solo_res = 0;
     int qj = (int)((blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)) % QUEUES);
-    int qdry = 0;
     int64_t pi = 0;
     int32_t K = 0, mp = 0, nt = 0, ncols = 0, mid = 0, wlo = 0, jb = 0, S = 0, band = 0;
     int32_t phi = 32, blo = 0, bhi = 0;
@@ -526,23 +508,7 @@ __global__ __launch_bounds__(256) void k_verify_bidir(const uint64_t *__restrict
 
         // ---- refill: each lane pair without a pair takes the next one
         const bool need = !active && !exhausted;
-        const uint64_t req = __ballot(need && !bwd);
-        long long got = -1;
-        if (req) {
-            const int first = __ffsll((unsigned long long)req) - 1;
-            const long long qn = n > qj ? (n - qj + QUEUES - 1) / QUEUES : 0;
-            const long long want = __popcll(req);
-            unsigned long long base = 0;
-            if (lane == first) base = atomicAdd(next + qj * QSTRIDE, (unsigned long long)want);
-            const long long b0 = (long long)__shfl(base, first, 64);
-            const long long k = b0 + __popcll(req & ((1ull << lane) - 1));
-            if (need && !bwd && k < qn) got = k * QUEUES + qj;
-            if (b0 + want > qn) {
-                qj = qj + 1 == QUEUES ? 0 : qj + 1;
-                if (++qdry == QUEUES) exhausted = true;
-            }
-        }
-        got = __shfl(got, leader_lane, 64);
+        const long long got = __shfl(take_pairs(next, n, need && !bwd, qj, exhausted), leader_lane, 64);
         if (need && got >= 0 && got < n) {
             pi = order ? order[got] : got;
             const uint64_t pr = pairs[pi];

@@ -83,7 +83,6 @@ __device__ __forceinline__ void ring_body(const uint64_t *__restrict__ pairs,
     const int bwd0 = G == 16 ? leader_lane + 16 : leader_lane + 1;
     bool active = false, exhausted = false;
     int qj = (int)((blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)) % QUEUES);
-    int qdry = 0;
     int64_t pi = 0, offx = 0, offy = 0;
     const uint32_t *PX = nullptr, *PY = nullptr;
     int32_t K = 0, mp = 0, nt = 0, ncols = 0, bhi = 0, life = 0, band = 0;
@@ -196,23 +195,7 @@ __device__ __forceinline__ void ring_body(const uint64_t *__restrict__ pairs,
 
         // ---- refill: each pair slot without a pair takes the next one
         const bool need = !active && !exhausted;
-        const uint64_t req = __ballot(need && lane == leader_lane);
-        long long got = -1;
-        if (req) {
-            const int first = __ffsll((unsigned long long)req) - 1;
-            const long long qn = n > qj ? (n - qj + QUEUES - 1) / QUEUES : 0;
-            const long long want = __popcll(req);
-            unsigned long long base = 0;
-            if (lane == first) base = atomicAdd(next + qj * QSTRIDE, (unsigned long long)want);
-            const long long b0 = (long long)__shfl(base, first, 64);
-            const long long k = b0 + __popcll(req & ((1ull << lane) - 1));
-            if (need && lane == leader_lane && k < qn) got = k * QUEUES + qj;
-            if (b0 + want > qn) {
-                qj = qj + 1 == QUEUES ? 0 : qj + 1;
-                if (++qdry == QUEUES) exhausted = true;
-            }
-            got = __shfl(got, leader_lane, 64);
-        }
+        const long long got = __shfl(take_pairs(next, n, need && lane == leader_lane, qj, exhausted), leader_lane, 64);
         if (need && got >= 0 && got < n) {
             pi = order[got];
             const uint64_t pr = pairs[pi];
