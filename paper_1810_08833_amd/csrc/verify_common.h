@@ -45,6 +45,24 @@ __device__ __forceinline__ uint32_t load_dir(const uint32_t *plane, int64_t bitp
     return rev ? __builtin_bitreverse32(w) : w;
 }
 
+// The same for all planes at once, without branches: the 2 NP words are adjacent.  (bitpos may
+// lie before the planes; what a string's own symbols do not fill is then made up.)
+template <int NP>
+__device__ __forceinline__ void load_planes(const uint32_t *planes, int64_t bitpos, bool rev,
+                                            uint32_t (&out)[NP]) {
+    const int64_t at = bitpos < 0 ? 0 : bitpos;
+    const uint32_t gap = (uint32_t)min<int64_t>(at - bitpos, 31), sh = (uint32_t)at & 31u;
+    const uint32_t *w = planes + (at >> 5) * NP;
+    uint32_t v[2 * NP];
+#pragma unroll
+    for (int p = 0; p < 2 * NP; p++) v[p] = w[p];
+#pragma unroll
+    for (int p = 0; p < NP; p++) {
+        const uint32_t x = __builtin_amdgcn_alignbit(v[NP + p], v[p], sh) << gap;
+        out[p] = rev ? __builtin_bitreverse32(x) : x;
+    }
+}
+
 // The work queue of a persistent launch: interleaved sub-queues, each counter on lines of
 // its own.
 constexpr int QUEUES = 32;

@@ -91,29 +91,28 @@ __device__ __forceinline__ void ring_body(const uint64_t *__restrict__ pairs,
     bool live = false;          // the strip has begun
     int32_t S = 0;              // value at the strip's last row, current column
     int32_t lbsum = 0;          // lower bound of both halves together
-    uint32_t Pv[W], Mv[W], PL[NP][W], PLn[NP][W], TY[NP], TYn[NP];
+    uint32_t Pv[W], Mv[W], PL[W][NP], PLn[W][NP], TY[NP], TYn[NP];
     uint32_t phs = 0, mhb = 0;  // deltas leaving the strip: +1 in bit 31, -1 in bit 0
     uint64_t my_cells = 0;
 #pragma unroll
     for (int s = 0; s < W; s++) {
         Pv[s] = Mv[s] = 0;
 #pragma unroll
-        for (int p = 0; p < NP; p++) PL[p][s] = PLn[p][s] = 0;
+        for (int p = 0; p < NP; p++) PL[s][p] = PLn[s][p] = 0;
     }
 #pragma unroll
     for (int p = 0; p < NP; p++) TY[p] = TYn[p] = 0;
-    // pattern word s of strip v (rows R v + 32 s + 1 ..), text word from column j on; both
-    // reversed in the second half.  Strips past the pattern and columns past the half read
-    // as 0, so a read ends at most one strip past a string (within the planes' padding).
-    auto xword = [&](int p, int v, int s) -> uint32_t {
-        if (R * v >= mp) return 0u;
+    // pattern words s of strip v (rows R v + 32 s + 1 ..), text words from column j on; both
+    // reversed in the second half.  A strip that begins meets the band, so it ends at most K +
+    // R + 32 symbols past the pattern, and a half's columns end a few strips' steps past its
+    // own: within the planes' padding (3,072 symbols), or before their start.
+    auto xwords = [&](int v, int s, uint32_t (&o)[NP]) {
         const int64_t at = (int64_t)R * v + 32 * s;
-        return load_dir<NP>(PX + p, bwd ? offx + mp - 32 - at : offx + at, bwd);
+        load_planes<NP>(PX, bwd ? offx + mp - 32 - at : offx + at, bwd, o);
     };
-    auto yword = [&](int p, int j) -> uint32_t {
-        if (j > ncols) return 0u;
+    auto ywords = [&](int j, uint32_t (&o)[NP]) {
         const int64_t at = j - 1;
-        return load_dir<NP>(PY + p, bwd ? offy + nt - 32 - at : offy + at, bwd);
+        load_planes<NP>(PY, bwd ? offy + nt - 32 - at : offy + at, bwd, o);
     };
     for (;;) {
         // ---- pairs whose two halves are done, or rejected: an alignment pays at least the
@@ -244,15 +243,13 @@ __device__ __forceinline__ void ring_body(const uint64_t *__restrict__ pairs,
                 S = R * w + R;  // column 0: row i holds i
                 lbsum = 0;
                 phs = mhb = 0;
+                ywords(t0 - w, TY);
 #pragma unroll
                 for (int s = 0; s < W; s++) {
                     Pv[s] = ~0u;
                     Mv[s] = 0u;
-#pragma unroll
-                    for (int p = 0; p < NP; p++) PL[p][s] = live ? xword(p, w, s) : 0u;
+                    if (live) xwords(w, s, PL[s]);
                 }
-#pragma unroll
-                for (int p = 0; p < NP; p++) TY[p] = yword(p, t0 - w);
             }
         }
         if (__all(!active && exhausted)) break;
@@ -265,15 +262,10 @@ __device__ __forceinline__ void ring_body(const uint64_t *__restrict__ pairs,
         const int wn = adv ? w + G : w;
         const int tEn = adv ? tE + P * G : tE;
         const bool begin = active && (adv || !live) && tn == tEn - life && tn - wn <= ncols;
-        if (active) {
-#pragma unroll
-            for (int p = 0; p < NP; p++) TYn[p] = yword(p, tn - wn);
-        }
+        if (active) ywords(tn - wn, TYn);
         if (begin) {
 #pragma unroll
-            for (int s = 0; s < W; s++)
-#pragma unroll
-                for (int p = 0; p < NP; p++) PLn[p][s] = xword(p, wn, s);
+            for (int s = 0; s < W; s++) xwords(wn, s, PLn[s]);
         }
 
         // ---- 32 steps
@@ -290,9 +282,9 @@ __device__ __forceinline__ void ring_body(const uint64_t *__restrict__ pairs,
             uint32_t eq[W], xh[W];
 #pragma unroll
             for (int s = 0; s < W; s++) {
-                uint32_t e = ~(PL[0][s] ^ tb[0]);
+                uint32_t e = ~(PL[s][0] ^ tb[0]);
 #pragma unroll
-                for (int p = 1; p < NP; p++) e = and_xnor(e, PL[p][s], tb[p]);
+                for (int p = 1; p < NP; p++) e = and_xnor(e, PL[s][p], tb[p]);
                 eq[s] = e;
             }
             if constexpr (W == 1) {
@@ -404,7 +396,7 @@ __device__ __forceinline__ void ring_body(const uint64_t *__restrict__ pairs,
                 Pv[s] = ~0u;
                 Mv[s] = 0u;
 #pragma unroll
-                for (int p = 0; p < NP; p++) PL[p][s] = PLn[p][s];
+                for (int p = 0; p < NP; p++) PL[s][p] = PLn[s][p];
             }
         }
 #pragma unroll
