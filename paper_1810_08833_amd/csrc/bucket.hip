@@ -569,21 +569,21 @@ BucketRecords bucket_records(uint64_t *key, uint64_t *val, int64_t cap, int64_t 
     }
     const int64_t nb = 1ll << r.bits;
     r.blocks = (int)std::min<int64_t>(nb, BK_BLOCKS);
-    // the workgroups' sums, then: candidates, over, the long slots' state
-    r.part = ws.get_n<uint64_t>(3 * r.blocks + 3);
-    r.counter = reinterpret_cast<unsigned long long *>(r.part + 3 * r.blocks);
-    r.over = reinterpret_cast<uint32_t *>(r.part + 3 * r.blocks + 1);
+    // the workgroups' sums; candidates, over, the long slots' state
+    r.state = reinterpret_cast<uint64_t *>(ws.zeroed(6, s));
+    r.part = ws.get_n<uint64_t>(3 * r.blocks);
+    r.counter = reinterpret_cast<unsigned long long *>(r.state);
+    r.over = reinterpret_cast<uint32_t *>(r.state + 1);
     r.xcap = cap;
     r.xkey = ws.get_n<uint64_t>(r.xcap + 1);
     r.xrec = reinterpret_cast<int4 *>(ws.get((size_t)(r.xcap + 1) * 16));
     r.xslots = r.xcap / (BK_LONG + 1) + 1;
     r.xslot = reinterpret_cast<ulonglong2 *>(ws.get((size_t)r.xslots * 16));
     r.ustart = ws.get_n<uint64_t>(r.xslots + 1);
-    bucket_reset(r, s);
     return r;
 }
 
-void bucket_reset(const BucketRecords &r, hipStream_t s) { fill_u64(r.part + 3 * r.blocks, 0, 3, s); }
+void bucket_reset(const BucketRecords &r, hipStream_t s) { fill_u64(r.state, 0, 3, s); }
 
 void bucket_pairs(const BucketRecords &r, const DevStrings &d, bool emit, uint64_t *out, int64_t cap,
                   bool longs, hipStream_t s, KTimer *kt) {

@@ -357,7 +357,8 @@ static mj_pairs *run_join(mj_ctx *ctx, const mj_strings *strings, const mj_param
         br = bucket_records(gkey, gval, R, R, nullptr, ws, s);
         bucket_pairs(br, d, false, nullptr, 0, false, s);
         std::vector<uint64_t> part(3 * br.blocks + 3);
-        MJ_HIP(hipMemcpyAsync(ctx->pinned, br.part, part.size() * 8, hipMemcpyDeviceToHost, s));
+        MJ_HIP(hipMemcpyAsync(ctx->pinned, br.part, (size_t)3 * br.blocks * 8, hipMemcpyDeviceToHost, s));
+        MJ_HIP(hipMemcpyAsync(ctx->pinned + 3 * br.blocks, br.state, 24, hipMemcpyDeviceToHost, s));
         MJ_HIP(hipStreamSynchronize(s));
         memcpy(part.data(), ctx->pinned, part.size() * 8);
         for (int b = 0; b < br.blocks; b++) {
@@ -492,54 +493,112 @@ static mj_pairs *run_join(mj_ctx *ctx, const mj_strings *strings, const mj_param
 // final one, no stage waits for the host.  Returns nullptr when a capacity was exceeded
 // (the caller then runs the join stage by stage, which sizes everything exactly).
 
-// slot: the group counts, or (LDS buckets) part[0 .. 3 blocks + 3): see BucketRecords
-__global__ void k_collect(const int64_t *R, const uint64_t *slot, const unsigned long long *c0,
-                          const uint32_t *u, const uint32_t *outn, const unsigned long long *cells,
-                          const uint32_t *symbol_err, const int64_t *M, const uint64_t *part,
-                          int blocks, uint64_t *dst) {
+// What the host reads at the end of a streamed join or search: the counts, in dst[0 .. 14].
+// slot: the group counts of a join by the general path; part, state: of one by LDS buckets
+// (see BucketRecords); tests, over: of a search.
+struct Collect {
+    const int64_t *R;
+    const uint64_t *slot;
+    const unsigned long long *c0;
+    const uint32_t *u;
+    const unsigned long long *cells;
+    const uint32_t *symbol_err;
+    const int64_t *M;
+    const uint64_t *part, *state;
+    int blocks;
+    const uint64_t *tests;
+    const uint32_t *over;
+};
+
+// by one wave
+__device__ void collect(const Collect &c, uint32_t outn, uint64_t *dst) {
+    const int lane = threadIdx.x & 63;
     uint64_t tests = 0, groups = 0;
-    if (part) {
-        for (int b = threadIdx.x; b < blocks; b += 64) {
-            tests += part[3 * b];
-            groups += part[3 * b + 1];
+    if (c.part) {
+        for (int b = lane; b < c.blocks; b += 64) {
+            tests += c.part[3 * b];
+            groups += c.part[3 * b + 1];
         }
         for (int d = 32; d >= 1; d >>= 1) {
             tests += (uint64_t)__shfl_down((long long)tests, d, 64);
             groups += (uint64_t)__shfl_down((long long)groups, d, 64);
         }
     }
-    if (blockIdx.x != 0 || threadIdx.x != 0) return;
-    dst[13] = part ? (uint32_t)part[3 * blocks + 1] : 0;
-    dst[14] = part ? part[3 * blocks + 2] >> 40 : 0;
-    dst[10] = (uint64_t)*M;
-    dst[9] = symbol_err ? *symbol_err : 0;
-    dst[0] = (uint64_t)*R;
-    dst[1] = slot ? slot[0] : 0;
-    dst[2] = slot ? slot[1] : groups;
-    dst[3] = slot ? slot[2] : tests;
-    dst[4] = *c0;
-    dst[5] = *u;
-    dst[6] = *outn;
-    dst[7] = cells[0];
-    dst[8] = cells[1];
-    dst[11] = slot ? slot[3] : 0;
-    dst[12] = slot ? slot[4] : 0;
+    if (lane != 0) return;
+    dst[0] = (uint64_t)*c.R;
+    dst[1] = c.slot ? c.slot[0] : 0;
+    dst[2] = c.slot ? c.slot[1] : groups;
+    dst[3] = c.slot ? c.slot[2] : c.tests ? *c.tests : tests;
+    dst[4] = *c.c0;
+    dst[5] = *c.u;
+    dst[6] = outn;
+    dst[7] = c.cells[0];
+    dst[8] = c.cells[1];
+    dst[9] = c.symbol_err ? *c.symbol_err : 0;
+    dst[10] = (uint64_t)*c.M;
+    dst[11] = c.slot ? c.slot[3] : 0;
+    dst[12] = c.slot ? c.slot[4] : 0;
+    dst[13] = c.state ? (uint32_t)c.state[1] : c.over ? *c.over : 0;
+    dst[14] = c.state ? c.state[2] >> 40 : 0;
 }
 
-__global__ void k_collect_search(const int64_t *R, const uint64_t *tests, const unsigned long long *c0,
-                                 const uint32_t *u, const uint32_t *outn,
-                                 const unsigned long long *cells, const uint32_t *symbol_err,
-                                 const uint32_t *over, uint64_t *dst) {
-    if (blockIdx.x != 0 || threadIdx.x != 0) return;
-    dst[0] = (uint64_t)*R;
-    dst[1] = *tests;
-    dst[2] = *c0;
-    dst[3] = *u;
-    dst[4] = *outn;
-    dst[5] = cells[0];
-    dst[6] = cells[1];
-    dst[7] = symbol_err ? *symbol_err : 0;
-    dst[8] = *over;
+__global__ void k_collect(Collect c, const uint32_t *outn, uint64_t *dst) { collect(c, *outn, dst); }
+
+// The accepted pairs and the counts by one workgroup.
+constexpr int CO_THREADS = 1024, CO_ITEMS = 8;
+constexpr int64_t CO_SMALL = 32768;
+__global__ __launch_bounds__(CO_THREADS) void k_collect_small(Collect c,
+                                                              const uint64_t *__restrict__ pairs,
+                                                              const uint8_t *__restrict__ flags,
+                                                              int64_t cap, uint64_t *__restrict__ out,
+                                                              uint64_t *dst) {
+    __shared__ uint32_t tmp[CO_THREADS / 64];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int64_t n = min(cap, (int64_t)*c.u);
+    uint32_t run = 0;
+    for (int64_t t0 = 0; t0 < n; t0 += CO_THREADS * CO_ITEMS) {
+        const int64_t i0 = t0 + (int64_t)threadIdx.x * CO_ITEMS;
+        uint32_t m = 0;
+        if (i0 + CO_ITEMS <= n && ((uintptr_t)(flags + i0) & 7) == 0) {
+            const uint64_t w = *reinterpret_cast<const uint64_t *>(flags + i0);
+#pragma unroll
+            for (int k = 0; k < CO_ITEMS; k++) m |= ((w >> (8 * k)) & 0xFF) ? 1u << k : 0u;
+        } else {
+            for (int k = 0; k < CO_ITEMS; k++)
+                if (i0 + k < n && flags[i0 + k]) m |= 1u << k;
+        }
+        uint32_t inc = (uint32_t)__popc(m);
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const uint32_t y = (uint32_t)__shfl_up((int)inc, d, 64);
+            if (lane >= d) inc += y;
+        }
+        if (lane == 63) tmp[wv] = inc;
+        __syncthreads();
+        uint32_t at = run + inc - (uint32_t)__popc(m);
+        for (int w = 0; w < CO_THREADS / 64; w++) {
+            if (w < wv) at += tmp[w];
+            run += tmp[w];
+        }
+        for (; m; m &= m - 1) out[at++] = pairs[i0 + __ffs(m) - 1];
+        __syncthreads();
+    }
+    if (wv == 0) collect(c, run, dst);
+}
+
+// expect: how many candidates there may be (speed only; about 12 us for CO_SMALL of them in
+// one launch, as long as the four of the general compaction)
+static void collect_output(const Collect &c, const uint64_t *pairs, const uint8_t *flags, int64_t cap,
+                           int64_t expect, uint64_t *out, uint64_t *dst, Workspace &ws, hipStream_t s) {
+    if (expect <= CO_SMALL) {
+        hipLaunchKernelGGL(k_collect_small, dim3(1), dim3(CO_THREADS), 0, s, c, pairs, flags, cap, out,
+                           dst);
+        MJ_LAUNCH_CHECK();
+        return;
+    }
+    const uint32_t *on = compact_values_async(pairs, flags, cap, c.u, out, ws, s);
+    hipLaunchKernelGGL(k_collect, dim3(1), dim3(64), 0, s, c, on, dst);
+    MJ_LAUNCH_CHECK();
 }
 
 static bool hints_match(const StreamHints &h, const mj_strings *st, const mj_params *p) {
@@ -552,6 +611,7 @@ static bool plan_streamed(mj_ctx *ctx, const mj_params *params, const DevStrings
                           const PartitionParams &pp, const SetupInfo &si, StreamedPlan &pl) {
     const StreamHints &h = ctx->stream;
     pl.si = si;
+    pl.vexp = h.candidates;
     pl.cmax = (int)((std::min<int64_t>(params->k >= 0 ? params->k : si.kmax, 0x3FFFFFFF) + 31) >> 5);
     if (pl.cmax > persist_max_c()) return false;
     const int np = verify_planes(d.bits);
@@ -641,14 +701,11 @@ static StreamedDev launch_streamed_main(mj_ctx *ctx, DevStrings &d, const Partit
     verify_pairs_batched_streamed(uniq, pl.ccap, u, d, d, 0, pl.cmax, flags, ws, s, kt, ctx->tune,
                                   params->verify_lanes, ctx->stream.candidates, &cells);
     if (tm) tm->mark();  // 5 verify
-    int64_t *idx = ws.get_n<int64_t>(pl.ccap + 1);
-    const uint32_t *on = compact_flags_async(flags, pl.ccap, idx, ws, s);
     dv.outbuf = ws.get_n<uint64_t>(pl.ccap + 1);
-    gather_u64(uniq, idx, dv.outbuf, pl.ccap, s, on);
     uint64_t *res = ws.get_n<uint64_t>(16);
-    hipLaunchKernelGGL(k_collect, dim3(1), dim3(64), 0, s, R_dev, g.slot, c0, u, on, cells,
-                       (const uint32_t *)d.symbol_err, M_dev, (const uint64_t *)br.part, br.blocks, res);
-    MJ_LAUNCH_CHECK();
+    const Collect cl{R_dev, g.slot, c0, u, cells, d.symbol_err, M_dev, br.part, br.state, br.blocks,
+                     nullptr, nullptr};
+    collect_output(cl, uniq, flags, pl.ccap, pl.vexp, dv.outbuf, res, ws, s);
     MJ_HIP(hipMemcpyAsync(ctx->pinned, res, 15 * 8, hipMemcpyDeviceToHost, s));
     return dv;
 }
@@ -1101,8 +1158,7 @@ static mj_pairs *run_search_streamed(mj_ctx *ctx, const mj_index *ix, DevStrings
                cand, ccap, s);
     tm.mark();  // 3 probe + filter
     uint64_t *uniq = nullptr;
-    uint32_t *over = ws.get_n<uint32_t>(2);
-    fill_u32(over, 0, 1, s);
+    uint32_t *over = ws.zeroed(2, s);
     const uint32_t *u = dedup_buckets(cand, ccap, (int64_t)cexp, pr.counter, qd.n, ix->n, over, ws, s, &uniq);
     tm.mark();  // 4 dedup
     uint8_t *flags = ws.get_n<uint8_t>(ccap + 4);
@@ -1110,23 +1166,19 @@ static mj_pairs *run_search_streamed(mj_ctx *ctx, const mj_index *ix, DevStrings
     verify_pairs_batched_streamed(uniq, ccap, u, qd, id, 1, cmax, flags, ws, s, &ctx->kt, tune,
                                   qparams->verify_lanes, (int64_t)vexp, &cells);
     tm.mark();  // 5 verify
-    int64_t *idx = ws.get_n<int64_t>(ccap + 1);
-    const uint32_t *on = compact_flags_async(flags, ccap, idx, ws, s);
     uint64_t *outbuf = ws.get_n<uint64_t>(ccap + 1);
-    gather_u64(uniq, idx, outbuf, ccap, s, on);
     uint64_t *res = ws.get_n<uint64_t>(16);
-    hipLaunchKernelGGL(k_collect_search, dim3(1), dim3(64), 0, s, (const int64_t *)R_dev, pr.tests,
-                       (const unsigned long long *)pr.counter, u, on, (const unsigned long long *)cells,
-                       (const uint32_t *)qd.symbol_err, (const uint32_t *)over, res);
-    MJ_LAUNCH_CHECK();
-    MJ_HIP(hipMemcpyAsync(ctx->pinned, res, 9 * 8, hipMemcpyDeviceToHost, s));
+    const Collect cl{R_dev, nullptr, pr.counter, u, cells, qd.symbol_err, R_dev, nullptr, nullptr, 0,
+                     pr.tests, over};
+    collect_output(cl, uniq, flags, ccap, (int64_t)vexp, outbuf, res, ws, s);
+    MJ_HIP(hipMemcpyAsync(ctx->pinned, res, 15 * 8, hipMemcpyDeviceToHost, s));
     MJ_HIP(hipStreamSynchronize(s));
-    uint64_t hv[9];
+    uint64_t hv[15];
     memcpy(hv, ctx->pinned, sizeof(hv));
-    const int64_t R = (int64_t)hv[0], c0 = (int64_t)hv[2], C = (int64_t)hv[3], nout = (int64_t)hv[4];
-    if (hv[7]) throw Error(MJ_EINVAL, "a symbol code is not below sigma");
-    if (hv[8] || c0 > ccap) return nullptr;
-    if (hv[6]) throw Error(MJ_ECAPACITY, "a pair's band exceeds the verifier window");
+    const int64_t R = (int64_t)hv[0], c0 = (int64_t)hv[4], C = (int64_t)hv[5], nout = (int64_t)hv[6];
+    if (hv[9]) throw Error(MJ_EINVAL, "a symbol code is not below sigma");
+    if (hv[13] || c0 > ccap) return nullptr;
+    if (hv[8]) throw Error(MJ_ECAPACITY, "a pair's band exceeds the verifier window");
     mj_pairs *out = new mj_pairs();
     out->alloc = t_dev_alloc;
     out->stream = s;
@@ -1141,10 +1193,10 @@ static mj_pairs *run_search_streamed(mj_ctx *ctx, const mj_index *ix, DevStrings
     tm.mark();  // 6 output
     if (stats) {
         stats->records = R;
-        stats->pair_tests = (int64_t)hv[1];
+        stats->pair_tests = (int64_t)hv[3];
         stats->candidates = C;
         stats->output = nout;
-        stats->band_cells = (int64_t)hv[5];
+        stats->band_cells = (int64_t)hv[7];
         stats->positions = qd.total * qp.reps;
         stats->verify_group = lanes_code(g);
         stats->verify_words = window_words_per_lane(g, cmax);
@@ -1153,7 +1205,7 @@ static mj_pairs *run_search_streamed(mj_ctx *ctx, const mj_index *ix, DevStrings
         stats->host_reads = 2;
     }
     h.cand_per_record = std::max((double)c0 / (double)rcap, 0.99 * h.cand_per_record);
-    h.tests_per_record = (double)hv[1] / (double)rcap;
+    h.tests_per_record = (double)hv[3] / (double)rcap;
     h.verified_per_record = (double)C / (double)rcap;
     return out;
 }

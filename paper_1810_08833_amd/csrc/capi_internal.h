@@ -47,6 +47,7 @@ struct StreamedPlan {
     // grouping, pair tests and dedup by LDS buckets; about how many records and candidates
     bool bucket = false, longs = false;
     int64_t rexp = 0, cexp = 0;
+    int64_t vexp = 0;  // about how many distinct candidates
 };
 struct StreamedDev {
     uint64_t *outbuf = nullptr;

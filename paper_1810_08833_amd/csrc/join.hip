@@ -1190,9 +1190,8 @@ Probe probe_ranges(const uint64_t *qkey, int64_t RQ, const int64_t *RQ_dev, cons
     p.lo = ws.get_n<uint32_t>(RQ + 1);
     uint64_t *cnt = ws.get_n<uint64_t>(RQ + 1);
     p.ts = ws.get_n<uint64_t>(RQ + 1);
-    p.tests = ws.get_n<uint64_t>(2);
+    p.tests = reinterpret_cast<uint64_t *>(ws.zeroed(4, s));
     p.counter = (unsigned long long *)(p.tests + 1);
-    fill_u64(p.tests, 0, 2, s);
     hipLaunchKernelGGL(k_probe_ranges, dim3(grid_for(RQ, 256, 16384)), dim3(256), 0, s, qkey, RQ,
                        RQ_dev, ikey, dir, bits, p.lo, cnt);
     MJ_LAUNCH_CHECK();

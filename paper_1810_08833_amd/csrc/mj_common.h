@@ -87,6 +87,10 @@ class Workspace {
     ~Workspace();
     void *get(size_t bytes);
     template <class T> T *get_n(size_t n) { return static_cast<T *>(get(n * sizeof(T) + 16)); }
+    // Zeroed words for counters: slices of one block that begin_zeroed clears with a single
+    // launch at the start of a call (a block and a fill of their own beyond it).
+    void begin_zeroed(size_t words, hipStream_t s);
+    uint32_t *zeroed(size_t words, hipStream_t s);
     void release_all();
     size_t bytes_held() const { return held_; }
     // bytes of the blocks the last call used (measured by release_all)
@@ -121,6 +125,8 @@ class Workspace {
     bool holding_ = false;
     std::vector<Block> blocks_;
     size_t held_ = 0, last_used_ = 0;
+    uint32_t *zero_base_ = nullptr;
+    size_t zero_words_ = 0, zero_used_ = 0;
     uint8_t *arena_base_ = nullptr;
     size_t arena_bytes_ = 0, arena_used_ = 0;
 };
@@ -162,6 +168,11 @@ int64_t compact_flags(const uint8_t *flags, int64_t n, int64_t *idx_out, Workspa
 // The same without the read-back: returns the device address of the count (n >= 1).
 const uint32_t *compact_flags_async(const uint8_t *flags, int64_t n, int64_t *idx_out,
                                     Workspace &ws, hipStream_t s);
+// The values whose flags are not 0, in order, to out, of the first min(n, *n_dev) (flags past
+// them are not read); returns the device address of their number.
+const uint32_t *compact_values_async(const uint64_t *values, const uint8_t *flags, int64_t n,
+                                     const uint32_t *n_dev, uint64_t *out, Workspace &ws,
+                                     hipStream_t s);
 // Size of the pinned host buffer each context keeps for small device-to-host reads.
 constexpr size_t HOST_SCRATCH_BYTES = 32768;
 
@@ -387,10 +398,10 @@ struct BucketRecords {
     const int64_t *n_dev = nullptr;
     int bits = 0;
     int blocks = 0;
-    // one block of 3 * blocks + 3 words: pair tests, groups and members by workgroup; then the
-    // candidates' number, over (set when a bucket does not fit: nothing else is then worth
-    // reading) and the long slots' state (slots << 40 | records)
-    uint64_t *part = nullptr;
+    uint64_t *part = nullptr;  // pair tests, groups and members by workgroup (3 * blocks words)
+    // 3 words, zero at first: the candidates' number, over (set when a bucket does not fit:
+    // nothing else is then worth reading) and the long slots' state (slots << 40 | records)
+    uint64_t *state = nullptr;
     unsigned long long *counter = nullptr;
     uint32_t *over = nullptr;
     // records of the long slots, the slots, and their tile pairs' prefix

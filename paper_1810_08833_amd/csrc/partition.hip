@@ -40,7 +40,8 @@ __global__ void k_prepare(const int64_t *off, int32_t n, int q, int64_t kuni, co
                           int t_div, int t_fixed, int32_t *len, int32_t *kk, int32_t *rr,
                           uint32_t *halo, uint32_t *err, unsigned long long *rec_bound,
                           uint32_t *kmax, int32_t *wide_ids, int32_t *wide_r, uint32_t *wide_count,
-                          unsigned long long *wide_pos) {
+                          unsigned long long *wide_pos, int64_t *total) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) *total = off[n];
     uint32_t hr = 0;  // the strings' contribution to the halo
     // and to the bound on the partitions of one repetition: interior anchors are strict
     // minima of radius r, so two of them are more than r apart, and a string of npos q-gram
@@ -108,6 +109,9 @@ __global__ void k_prepare(const int64_t *off, int32_t n, int q, int64_t kuni, co
     }
 }
 
+// Counters of one call: the set-up's, the symbol check's, the LDS buckets' and the verifier's.
+constexpr size_t ZEROED_WORDS = 24 << 10;
+
 void prepare_launch(DevStrings &d, const PartitionParams &p, Workspace &ws, hipStream_t s,
                     uint64_t *host_dst) {
     int32_t n = d.n;
@@ -117,21 +121,20 @@ void prepare_launch(DevStrings &d, const PartitionParams &p, Workspace &ws, hipS
     d.wide_ids = ws.get_n<int32_t>(n + 1);
     d.wide_r = ws.get_n<int32_t>(n + 1);
     // [0] halo, [1] error bits, [2..3] partition bound (u64), [4] largest K, [5] wide
-    // strings, [6..7] their q-gram starts (u64)
-    uint32_t *flags = ws.get_n<uint32_t>(8);
-    fill_u32(flags, 0, 8, s);
+    // strings, [6..7] their q-gram starts (u64), [8..9] offsets[n]
+    ws.begin_zeroed(ZEROED_WORDS, s);
+    uint32_t *flags = ws.zeroed(10, s);
     if (n > 0) {
         const unsigned grid = (unsigned)std::min<int64_t>(((int64_t)n + 255) / 256, 128);
         hipLaunchKernelGGL(k_prepare, dim3(grid), dim3(256), 0, s, d.offsets, n, p.q, p.k,
                            p.k_per_string, p.t_div, p.t_fixed, d.len, d.kk, d.rr, flags,
                            flags + 1, reinterpret_cast<unsigned long long *>(flags + 2), flags + 4,
                            d.wide_ids, d.wide_r, flags + 5,
-                           reinterpret_cast<unsigned long long *>(flags + 6));
+                           reinterpret_cast<unsigned long long *>(flags + 6),
+                           reinterpret_cast<int64_t *>(flags + 8));
         MJ_LAUNCH_CHECK();
     }
-    MJ_HIP(hipMemcpyAsync(host_dst, flags, 32, hipMemcpyDeviceToHost, s));
-    if (d.total < 0)  // offsets[n] read back with the flags
-        MJ_HIP(hipMemcpyAsync(host_dst + 4, d.offsets + n, 8, hipMemcpyDeviceToHost, s));
+    MJ_HIP(hipMemcpyAsync(host_dst, flags, 40, hipMemcpyDeviceToHost, s));
 }
 
 int32_t prepare_finish(DevStrings &d, const uint64_t *host_src, SetupInfo *info) {
@@ -290,8 +293,7 @@ __global__ void k_pack_planes_2bit(const uint32_t *packed, int64_t total, uint32
 void pack_planes(DevStrings &d, int np, Workspace &ws, hipStream_t s, uint32_t *dest) {
     d.plane_words = plane_words_for(d.total);
     d.planes = dest ? dest : ws.get_n<uint32_t>((size_t)np * d.plane_words);
-    uint32_t *err = ws.get_n<uint32_t>(2);
-    fill_u32(err, 0, 1, s);
+    uint32_t *err = ws.zeroed(2, s);
     d.symbol_err = err;
     int aligned = ((uintptr_t)d.chars & 15) == 0 ? 1 : 0;
     const uint32_t sg = (uint32_t)d.sigma;
@@ -337,14 +339,13 @@ constexpr int AT_THREADS = 256;
 constexpr int RANK_MAX_BITS = 12;
 // One wave per code (four per block): the block hashes every code into LDS, each lane
 // counts the smaller hashes among every 64th code, and the wave adds the counts.
-__global__ __launch_bounds__(256) void k_rank_table(int ncodes, uint64_t salt,
-                                                    const uint64_t *__restrict__ table,
-                                                    uint16_t *__restrict__ rank) {
-    __shared__ uint64_t v[1 << RANK_MAX_BITS];
+__device__ __forceinline__ void rank_codes(int block, uint64_t *v, int ncodes, uint64_t salt,
+                                           const uint64_t *__restrict__ table,
+                                           uint16_t *__restrict__ rank) {
     for (int c = threadIdx.x; c < ncodes; c += blockDim.x)
         v[c] = table ? table[c] : mix64((uint64_t)c ^ salt);
     __syncthreads();
-    const int c = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int c = block * (blockDim.x >> 6) + (threadIdx.x >> 6), lane = threadIdx.x & 63;
     if (c >= ncodes) return;  // wave-uniform
     const uint64_t x = v[c];
     int below = 0;
@@ -368,10 +369,10 @@ struct TileDesc {
 };
 static_assert(sizeof(TileDesc) == 128, "tile descriptor size");
 
-__global__ void k_tile_desc(const int64_t *__restrict__ off, const int32_t *__restrict__ rr,
-                            int32_t n, int64_t total, int64_t ntiles, int TP, int H, int NR,
-                            int q, TileDesc *__restrict__ td) {
-    int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+__device__ __forceinline__ void tile_desc(int64_t t, const int64_t *__restrict__ off,
+                                          const int32_t *__restrict__ rr, int32_t n, int64_t total,
+                                          int64_t ntiles, int TP, int H, int NR, int q,
+                                          TileDesc *__restrict__ td) {
     if (t >= ntiles) return;
     int64_t base = t * TP - H;
     int64_t g0 = base < 0 ? 0 : base;
@@ -1096,8 +1097,8 @@ __device__ __forceinline__ uint64_t fold61(uint64_t s) { return (s & P61) + (s >
 // and the same values times B^4 (2 * 2^(4b) entries).
 // lsb != 0 (2-bit packed input): a chunk x holds its first symbol in the low bits, so a
 // packed byte is its own table index.
-__global__ void k_phi_table(int nc, int bits, uint64_t B, int pt, int lsb, uint64_t *__restrict__ T) {
-    const int idx = blockIdx.x * blockDim.x + threadIdx.x;
+__device__ __forceinline__ void phi_entry(int idx, int nc, int bits, uint64_t B, int pt, int lsb,
+                                          uint64_t *__restrict__ T) {
     if (idx >= nc) return;
     uint64_t h = 0;
     const int pbase = pt ? 0 : 2 << (4 * bits);  // first power-table entry
@@ -1113,6 +1114,43 @@ __global__ void k_phi_table(int nc, int bits, uint64_t B, int pt, int lsb, uint6
             for (int k = 0; k < 4; k++) h = mulmod61(h, B);
     }
     T[idx] = h;
+}
+
+// The tables of a partition in one launch, a share of the workgroups each: the tile descriptors,
+// the rank tables of every repetition, the chunk and power tables of the bucket function.
+struct TableArgs {
+    const int64_t *off;
+    const int32_t *rr;
+    int32_t n;
+    int64_t total, ntiles;
+    int TP, H, region, q;
+    TileDesc *td;
+    int ncodes, rstride, reps;  // ncodes 0: no ranks
+    uint64_t seed;
+    const uint64_t *pi;
+    uint16_t *rank;
+    int nc, bits, pt, lsb;
+    uint64_t B;
+    uint64_t *phi;
+};
+__global__ __launch_bounds__(256) void k_tables(TableArgs a, unsigned desc_blocks,
+                                                unsigned rank_blocks) {
+    __shared__ uint64_t v[1 << RANK_MAX_BITS];
+    unsigned b = blockIdx.x;
+    if (b < desc_blocks) {
+        tile_desc((int64_t)b * 256 + threadIdx.x, a.off, a.rr, a.n, a.total, a.ntiles, a.TP, a.H,
+                  a.region, a.q, a.td);
+        return;
+    }
+    b -= desc_blocks;
+    if (b < rank_blocks * (unsigned)a.reps) {
+        const int rho = (int)(b / rank_blocks);
+        rank_codes((int)(b % rank_blocks), v, a.ncodes, mix64(a.seed + (uint64_t)rho + GAMMA), a.pi,
+                   a.rank + (int64_t)rho * a.rstride);
+        return;
+    }
+    b -= rank_blocks * (unsigned)a.reps;
+    phi_entry((int)(b * 256 + threadIdx.x), a.nc, a.bits, a.B, a.pt, a.lsb, a.phi);
 }
 
 constexpr int REC_THREADS = 256;
@@ -1621,13 +1659,54 @@ void RecBuf::release() {
     key = val = nullptr; len = nullptr; cap = count = 0;
 }
 
+// The tables k_tables makes, and what the bucket function's Horner steps are made of.
+struct Tables {
+    TileDesc *ts = nullptr;
+    uint16_t *rank = nullptr;  // rank tables one after another (rstride entries each), or null
+    int rstride = 0;
+    uint64_t *phi = nullptr;
+    int nc = 0, pt = 0;
+    uint64_t B = 0;
+};
+
+static Tables tables_launch(const DevStrings &d, const PartitionParams &p, int reps, int TP, int H,
+                            int region, int64_t ntiles, Workspace &ws, hipStream_t s) {
+    Tables t;
+    const int code_bits = p.q * d.bits;
+    const int packed = d.packing == MJ_PACK_2BIT ? 1 : 0;
+    t.ts = ws.get_n<TileDesc>(ntiles + 1);
+    // rank tables one after another, each on a 16-byte boundary (with 16 bytes of slack)
+    t.rstride = code_bits <= RANK_MAX_BITS ? ((1 << code_bits) + 7) & ~7 : 0;
+    t.rank = t.rstride ? ws.get_n<uint16_t>((size_t)reps * t.rstride + 8) : nullptr;
+    t.B = 2 + mix64(p.seed ^ GAMMA_B) % (P61 - 3);
+    // Horner steps of 8 symbols (see phi_entry): power tables, and for b <= 2 tables of
+    // all 4-symbol chunks before them (at most 2,048 entries)
+    // (2-bit packed input with b = 1 has chunks of 2-bit fields, not 4-bit codes: the
+    // power tables serve it)
+    t.pt = (d.bits > 2 || (packed && d.bits != 2)) ? 1 : 0;
+    t.nc = (t.pt ? 0 : 2 << (4 * d.bits)) + (8 << d.bits);
+    t.phi = ws.get_n<uint64_t>(t.nc);
+    const int ncodes = t.rank ? 1 << code_bits : 0;
+    const TableArgs a{d.offsets, d.rr, d.n, d.total, ntiles, TP, H, region, p.q, t.ts, ncodes,
+                      t.rstride, reps, p.seed, p.pi_table, t.rank, t.nc, d.bits, t.pt, packed, t.B,
+                      t.phi};
+    const int64_t desc = (ntiles + 255) / 256, ranks = (ncodes + 3) / 4, phi = (t.nc + 255) / 256;
+    hipLaunchKernelGGL(k_tables, dim3((unsigned)(desc + ranks * reps + phi)), dim3(256), 0, s, a,
+                       (unsigned)desc, (unsigned)ranks);
+    MJ_LAUNCH_CHECK();
+    return t;
+}
+
 // Anchors and string starts of every repetition: their bitmaps (nw + 1 words each) and
 // per-tile counts (ntiles + 1 each) in one workspace block apiece, filled by one launch of
 // the tile kernel over all repetitions, then by the wide-radius kernels per repetition.
 static void anchor_launch(const DevStrings &d, const PartitionParams &p, int reps, int TP, int H,
-                          int region, int64_t ntiles, const TileDesc *ts, Workspace &ws,
+                          int region, int64_t ntiles, const Tables &tb, Workspace &ws,
                           hipStream_t s, std::vector<uint64_t *> &bitmap,
                           std::vector<uint32_t *> &tcount) {
+    const TileDesc *ts = tb.ts;
+    const uint16_t *rank = tb.rank;
+    const int rstride = tb.rstride;
     const int64_t nw = (d.total + 63) / 64;
     const int code_bits = p.q * d.bits;
     const int aligned4 = ((uintptr_t)d.chars & 3) == 0 ? 1 : 0;
@@ -1637,18 +1716,6 @@ static void anchor_launch(const DevStrings &d, const PartitionParams &p, int rep
     for (int rho = 0; rho < reps; rho++) {
         bitmap[rho] = bm_all + (int64_t)rho * (nw + 1);
         tcount[rho] = tc_all + (int64_t)rho * (ntiles + 1);
-    }
-    // rank tables one after another, each on a 16-byte boundary (with 16 bytes of slack)
-    const int rstride = code_bits <= RANK_MAX_BITS ? ((1 << code_bits) + 7) & ~7 : 0;
-    uint16_t *rank = rstride ? ws.get_n<uint16_t>((size_t)reps * rstride + 8) : nullptr;
-    if (rank) {
-        const int nc = 1 << code_bits;
-        for (int rho = 0; rho < reps; rho++) {
-            const uint64_t salt = mix64(p.seed + (uint64_t)rho + GAMMA);
-            hipLaunchKernelGGL(k_rank_table, dim3((nc + 3) / 4), dim3(256), 0, s, nc, salt,
-                               p.pi_table, rank + (int64_t)rho * rstride);
-            MJ_LAUNCH_CHECK();
-        }
     }
     const size_t rank_lds = rank ? ((size_t)2 << code_bits) + 16 : 0;
 #define MJ_ANCHORS(R, V, T)                                                                     \
@@ -1670,18 +1737,97 @@ static void anchor_launch(const DevStrings &d, const PartitionParams &p, int rep
         wide_anchors(d, wb, p, mix64(p.seed + (uint64_t)rho + GAMMA), TP, bitmap[rho], tcount[rho], s);
 }
 
-// Record bases of the repetitions and the record total, from the repetitions' scanned
-// anchor-tile counts (pre_all holds reps arrays of ntiles + 1 words, the last one each
-// repetition's count).
+// Record bases of the repetitions, the record total (base[reps], and *total when given) and the
+// symbol check (base[reps + 1]), from the repetitions' scanned anchor-tile counts (pre_all
+// holds reps arrays of ntiles + 1 words, the last one each repetition's count).
 __global__ void k_rep_bases(const uint32_t *pre_all, int reps, int64_t ntiles, int64_t *base,
-                            int64_t *total) {
+                            const uint32_t *symbol_err, int64_t *total) {
     if (blockIdx.x != 0 || threadIdx.x != 0) return;
     int64_t acc = 0;
     for (int r = 0; r < reps; r++) {
         base[r] = acc;
         acc += pre_all[(int64_t)r * (ntiles + 1) + ntiles];
     }
-    *total = acc;
+    base[reps] = acc;
+    base[reps + 1] = symbol_err ? *symbol_err : 0;
+    if (total) *total = acc;
+}
+
+// The repetitions' scans and the bases by one workgroup, a launch in place of reps + 1.
+constexpr int TS_THREADS = 1024, TS_ITEMS = 8, TS_CHUNK = TS_THREADS * TS_ITEMS;
+constexpr int TS_CHUNKS_MAX = 8;  // chunks of all repetitions it takes on (about 2.5 us each)
+__global__ __launch_bounds__(TS_THREADS) void k_tile_scan(const uint32_t *__restrict__ cnt, int reps,
+                                                          int64_t ntiles, uint32_t *__restrict__ pre,
+                                                          int64_t *base, const uint32_t *symbol_err,
+                                                          int64_t *total) {
+    __shared__ uint32_t tmp[TS_THREADS / 64];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    int64_t acc = 0;
+    for (int r = 0; r < reps; r++) {
+        const uint32_t *c = cnt + (int64_t)r * (ntiles + 1);
+        uint32_t *o = pre + (int64_t)r * (ntiles + 1);
+        uint32_t run = 0;
+        for (int64_t t0 = 0; t0 < ntiles; t0 += TS_CHUNK) {
+            const int64_t i0 = t0 + (int64_t)threadIdx.x * TS_ITEMS;
+            uint32_t v[TS_ITEMS], sum = 0;
+#pragma unroll
+            for (int k = 0; k < TS_ITEMS; k++) {
+                v[k] = i0 + k < ntiles ? c[i0 + k] : 0u;
+                sum += v[k];
+            }
+            uint32_t inc = sum;
+#pragma unroll
+            for (int d = 1; d < 64; d <<= 1) {
+                const uint32_t y = (uint32_t)__shfl_up((int)inc, d, 64);
+                if (lane >= d) inc += y;
+            }
+            if (lane == 63) tmp[wv] = inc;
+            __syncthreads();
+            uint32_t at = run + inc - sum;
+            for (int w = 0; w < TS_THREADS / 64; w++) {
+                if (w < wv) at += tmp[w];
+                run += tmp[w];
+            }
+#pragma unroll
+            for (int k = 0; k < TS_ITEMS; k++) {
+                if (i0 + k < ntiles) o[i0 + k] = at;
+                at += v[k];
+            }
+            __syncthreads();
+        }
+        if (threadIdx.x == 0) {
+            o[ntiles] = run;
+            base[r] = acc;
+        }
+        acc += run;
+    }
+    if (threadIdx.x == 0) {
+        base[reps] = acc;
+        base[reps + 1] = symbol_err ? *symbol_err : 0;
+        if (total) *total = acc;
+    }
+}
+
+// Scans of the repetitions' tile counts (tcount: reps arrays of ntiles + 1 words one after
+// another) into *pre_all, and the bases (see k_rep_bases).
+static int64_t *scan_tiles(const std::vector<uint32_t *> &tcount, int reps, int64_t ntiles,
+                           const uint32_t *symbol_err, uint32_t **pre_all, Workspace &ws,
+                           hipStream_t s, int64_t *total = nullptr) {
+    uint32_t *pre = ws.get_n<uint32_t>((size_t)reps * (ntiles + 1));
+    int64_t *base = ws.get_n<int64_t>(reps + 2);
+    *pre_all = pre;
+    if (reps * ((ntiles + TS_CHUNK - 1) / TS_CHUNK) <= TS_CHUNKS_MAX) {
+        hipLaunchKernelGGL(k_tile_scan, dim3(1), dim3(TS_THREADS), 0, s, tcount[0], reps, ntiles, pre,
+                           base, symbol_err, total);
+        MJ_LAUNCH_CHECK();
+        return base;
+    }
+    for (int rho = 0; rho < reps; rho++)
+        exclusive_scan_u32(tcount[rho], pre + (int64_t)rho * (ntiles + 1), ntiles, ws, s);
+    hipLaunchKernelGGL(k_rep_bases, dim3(1), dim3(64), 0, s, pre, reps, ntiles, base, symbol_err,
+                       total);
+    MJ_LAUNCH_CHECK();
+    return base;
 }
 
 // Persistent grid of a kernel: the workgroups that fit the device at once.
@@ -1702,29 +1848,22 @@ static unsigned resident_grid(K kern, int threads) {
 // chunk tables: cheaper per symbol than the tile kernel's prefix sums when nothing is
 // shared); rcap bounds its partitions and stage says whether to stage their symbols.
 static void records_launch(const DevStrings &d, const PartitionParams &p, int reps, int TP,
-                           int region, int64_t ntiles, const TileDesc *ts, const uint64_t *bm_all,
+                           int region, int64_t ntiles, const Tables &tb, const uint64_t *bm_all,
                            const uint32_t *pre_all, const int64_t *rbase, int64_t rcap, bool stage,
                            uint64_t *key, uint64_t *val, uint32_t *len, Workspace &ws,
                            hipStream_t s) {
     const int64_t nw = (d.total + 63) / 64;
     const int aligned4 = ((uintptr_t)d.chars & 3) == 0 ? 1 : 0;
     const int packed = d.packing == MJ_PACK_2BIT ? 1 : 0;
-    const uint64_t B = 2 + mix64(p.seed ^ GAMMA_B) % (P61 - 3);
+    const TileDesc *ts = tb.ts;
+    const uint64_t B = tb.B;
     const uint64_t salt_f = mix64(p.seed + GAMMA);
     auto mulp = [](uint64_t a, uint64_t b) { return (uint64_t)(((unsigned __int128)a * b) % P61); };
-    // Horner steps of 8 symbols (see k_phi_table): power tables, and for b <= 2 tables of
-    // all 4-symbol chunks before them (at most 2,048 entries)
-    // (2-bit packed input with b = 1 has chunks of 2-bit fields, not 4-bit codes: the
-    // power tables serve it)
-    const int pt = (d.bits > 2 || (packed && d.bits != 2)) ? 1 : 0;
+    const int pt = tb.pt, nc = tb.nc;
+    const uint64_t *phi_table = tb.phi;
     uint64_t B4 = 1;
     for (int i = 0; i < 4; i++) B4 = mulp(B4, B);
     const uint64_t B8 = mulp(B4, B4);
-    const int nc = (pt ? 0 : 2 << (4 * d.bits)) + (8 << d.bits);
-    uint64_t *phi_table = ws.get_n<uint64_t>(nc);
-    hipLaunchKernelGGL(k_phi_table, dim3((nc + 255) / 256), dim3(256), 0, s, nc, d.bits, B, pt,
-                       packed, phi_table);
-    MJ_LAUNCH_CHECK();
     if (reps == 1) {
         int64_t *apos = ws.get_n<int64_t>(rcap + 1);
         hipLaunchKernelGGL(k_anchor_scatter, dim3((unsigned)ntiles), dim3(64), 0, s, bm_all, nw,
@@ -1788,45 +1927,22 @@ int64_t partition_records(const DevStrings &d, const PartitionParams &p, int32_t
 
     // phase 1: anchors of every repetition (Pi seeded with seed + rho), their counts
     int th = kt ? kt->begin(KTimer::ANCHORS, s) : -1;
-    TileDesc *ts = ws.get_n<TileDesc>(ntiles + 1);
-    hipLaunchKernelGGL(k_tile_desc, dim3((unsigned)((ntiles + 255) / 256)), dim3(256), 0, s,
-                       d.offsets, d.rr, d.n, d.total, ntiles, TP, H, region, p.q, ts);
-    MJ_LAUNCH_CHECK();
+    const Tables ts = tables_launch(d, p, reps, TP, H, region, ntiles, ws, s);
     std::vector<uint64_t *> bitmap(reps);
     std::vector<uint32_t *> tcount(reps);  // per tile: flagged positions
     anchor_launch(d, p, reps, TP, H, region, ntiles, ts, ws, s, bitmap, tcount);
     if (kt) kt->end(th, s, 1);
-    // their scans, one after another (ntiles + 1 words each, the last the repetition's count)
-    uint32_t *pre_all = ws.get_n<uint32_t>((size_t)reps * (ntiles + 1));
-    for (int rho = 0; rho < reps; rho++) {
-        uint32_t *pre = pre_all + (int64_t)rho * (ntiles + 1);
-        exclusive_scan_u32(tcount[rho], pre, ntiles, ws, s);
-        MJ_HIP(hipMemcpyAsync((uint8_t *)host_scratch + 4 * rho, pre + ntiles, 4,
-                              hipMemcpyDeviceToHost, s));
-    }
-    // the symbol check of the plane packing comes back with the counts
-    uint32_t *sym_err_h = (uint32_t *)host_scratch + reps;
-    *sym_err_h = 0;
-    if (d.symbol_err)
-        MJ_HIP(hipMemcpyAsync(sym_err_h, d.symbol_err, 4, hipMemcpyDeviceToHost, s));
+    // their scans, the record total and the symbol check of the plane packing in one read
+    uint32_t *pre_all = nullptr;
+    int64_t *base_dev = scan_tiles(tcount, reps, ntiles, d.symbol_err, &pre_all, ws, s);
+    MJ_HIP(hipMemcpyAsync(host_scratch, base_dev + reps, 16, hipMemcpyDeviceToHost, s));
     MJ_HIP(hipStreamSynchronize(s));
-    if (*sym_err_h) throw Error(MJ_EINVAL, "a symbol code is not below sigma");
-    std::vector<int64_t> R(reps);
-    int64_t total = 0;
-    for (int rho = 0; rho < reps; rho++) {
-        uint32_t v;
-        memcpy(&v, (const uint8_t *)host_scratch + 4 * rho, 4);
-        R[rho] = v;
-        total += v;
-    }
+    if (host_scratch[1]) throw Error(MJ_EINVAL, "a symbol code is not below sigma");
+    const int64_t total = (int64_t)host_scratch[0];
 
     // phase 2: one reservation, then the records of every repetition
     const int64_t base0 = out.count;
     out.reserve(base0 + total + 1, s);
-    int64_t *base_dev = ws.get_n<int64_t>(reps + 2);
-    hipLaunchKernelGGL(k_rep_bases, dim3(1), dim3(64), 0, s, pre_all, reps, ntiles, base_dev,
-                       base_dev + reps + 1);
-    MJ_LAUNCH_CHECK();
     if (total > 0) {
         int tr = kt ? kt->begin(KTimer::RECORDS, s) : -1;
         // stage the symbols when partitions average 24 symbols or more
@@ -1857,21 +1973,13 @@ int64_t partition_records_streamed(const DevStrings &d, const PartitionParams &p
         throw Error(MJ_ECAPACITY, "more than 2^32 partitions per repetition");
 
     int th = kt ? kt->begin(KTimer::ANCHORS, s) : -1;
-    TileDesc *ts = ws.get_n<TileDesc>(ntiles + 1);
-    hipLaunchKernelGGL(k_tile_desc, dim3((unsigned)((ntiles + 255) / 256)), dim3(256), 0, s,
-                       d.offsets, d.rr, d.n, d.total, ntiles, TP, H, region, p.q, ts);
-    MJ_LAUNCH_CHECK();
+    const Tables ts = tables_launch(d, p, reps, TP, H, region, ntiles, ws, s);
     std::vector<uint64_t *> bitmap(reps);
     std::vector<uint32_t *> tcount(reps);
-    uint32_t *pre_all = ws.get_n<uint32_t>((size_t)reps * (ntiles + 1));
     anchor_launch(d, p, reps, TP, H, region, ntiles, ts, ws, s, bitmap, tcount);
     if (kt) kt->end(th, s, 1);
-    for (int rho = 0; rho < reps; rho++)
-        exclusive_scan_u32(tcount[rho], pre_all + (int64_t)rho * (ntiles + 1), ntiles, ws, s);
-    int64_t *base_dev = ws.get_n<int64_t>(reps + 1);
-    hipLaunchKernelGGL(k_rep_bases, dim3(1), dim3(64), 0, s, pre_all, reps, ntiles, base_dev, R_dev);
-    MJ_LAUNCH_CHECK();
-
+    uint32_t *pre_all = nullptr;
+    const int64_t *base_dev = scan_tiles(tcount, reps, ntiles, nullptr, &pre_all, ws, s, R_dev);
     int tr = kt ? kt->begin(KTimer::RECORDS, s) : -1;
     // partitions average about half the bound's length (the bound counts anchors r + 1
     // apart, Lemma 1 expects them 2r + 1 apart): stage the symbols when that is 24 or more

@@ -132,7 +132,28 @@ void *Workspace::get(size_t bytes) {
     return p;
 }
 
+void Workspace::begin_zeroed(size_t words, hipStream_t s) {
+    if (arena()) return;  // (its size is a documented limit)
+    zero_base_ = get_n<uint32_t>(words);
+    zero_words_ = words;
+    zero_used_ = 0;
+    fill_u32(zero_base_, 0, (int64_t)words, s);
+}
+
+uint32_t *Workspace::zeroed(size_t words, hipStream_t s) {
+    const size_t take = (words + 31) & ~size_t(31);
+    if (zero_base_ && zero_used_ + take <= zero_words_) {
+        uint32_t *p = zero_base_ + zero_used_;
+        zero_used_ += take;
+        return p;
+    }
+    uint32_t *p = get_n<uint32_t>(words);
+    fill_u32(p, 0, (int64_t)words, s);
+    return p;
+}
+
 void Workspace::release_all() {
+    zero_base_ = nullptr;
     size_t used = 0;
     for (auto &b : blocks_) {
         if (b.used) used += b.n;
@@ -480,6 +501,7 @@ constexpr int CT_TILE = SCAN_BLOCK * CT_ITEMS;    // 4,096 flags per tile
 // the CT_ITEMS flags of this thread as bits (bit k: element base + k is flagged)
 __device__ __forceinline__ uint32_t flag_bits(const uint8_t *flags, int64_t n, int64_t base) {
     uint32_t m = 0;
+    if (base >= n) return m;
     if (base + CT_ITEMS <= n && ((uintptr_t)(flags + base) & 15) == 0) {
         const uint4 v = *reinterpret_cast<const uint4 *>(flags + base);
         const uint32_t w[4] = {v.x, v.y, v.z, v.w};
@@ -493,42 +515,67 @@ __device__ __forceinline__ uint32_t flag_bits(const uint8_t *flags, int64_t n, i
 }
 
 __global__ __launch_bounds__(SCAN_BLOCK) void k_flag_counts(const uint8_t *flags, int64_t n,
-                                                            uint32_t *tile_count) {
+                                                            uint32_t *tile_count,
+                                                            const uint32_t *n_dev) {
     __shared__ uint32_t smem[8];
+    if (n_dev) n = min(n, (int64_t)*n_dev);
+    if ((int64_t)blockIdx.x * CT_TILE >= n) {  // (block-uniform)
+        if (threadIdx.x == 0) tile_count[blockIdx.x] = 0;
+        return;
+    }
     const int64_t base = (int64_t)blockIdx.x * CT_TILE + (int64_t)threadIdx.x * CT_ITEMS;
     uint32_t tot;
     (void)block_exclusive_scan<uint32_t>((uint32_t)__popc(flag_bits(flags, n, base)), smem, &tot);
     if (threadIdx.x == 0) tile_count[blockIdx.x] = tot;
 }
 
+// VALUES: the flagged elements' values to out, else their indices to idx.
+template <bool VALUES>
 __global__ __launch_bounds__(SCAN_BLOCK) void k_compact_tiles(const uint8_t *flags, int64_t n,
                                                               const uint32_t *tile_pre,
-                                                              int64_t *idx) {
+                                                              int64_t *idx, const uint64_t *values,
+                                                              uint64_t *out, const uint32_t *n_dev) {
     __shared__ uint32_t smem[8];
+    if (n_dev) n = min(n, (int64_t)*n_dev);
+    if ((int64_t)blockIdx.x * CT_TILE >= n) return;  // (block-uniform)
     const int64_t base = (int64_t)blockIdx.x * CT_TILE + (int64_t)threadIdx.x * CT_ITEMS;
     uint32_t m = flag_bits(flags, n, base);
     uint32_t tot;
     uint32_t r = tile_pre[blockIdx.x] + block_exclusive_scan<uint32_t>((uint32_t)__popc(m), smem, &tot);
     while (m) {
-        idx[r++] = base + __ffs(m) - 1;
+        const int64_t i = base + __ffs(m) - 1;
+        if (VALUES) out[r++] = values[i];
+        else idx[r++] = i;
         m &= m - 1;
     }
 }
 
-const uint32_t *compact_flags_async(const uint8_t *flags, int64_t n, int64_t *idx_out,
-                                    Workspace &ws, hipStream_t s) {
+static const uint32_t *compact(const uint8_t *flags, int64_t n, int64_t *idx_out,
+                               const uint64_t *values, uint64_t *out, const uint32_t *n_dev,
+                               Workspace &ws, hipStream_t s) {
     // 32-bit ranks: the count of kept elements must stay below 2^32
     if (n > 0xFFFFFFF0LL) throw Error(MJ_ECAPACITY, "compaction of more than 2^32 elements");
     const int64_t nb = std::max<int64_t>((n + CT_TILE - 1) / CT_TILE, 1);
     uint32_t *cnt = ws.get_n<uint32_t>(nb + 1);
     uint32_t *pre = ws.get_n<uint32_t>(nb + 1);
-    hipLaunchKernelGGL(k_flag_counts, dim3((unsigned)nb), dim3(SCAN_BLOCK), 0, s, flags, n, cnt);
+    hipLaunchKernelGGL(k_flag_counts, dim3((unsigned)nb), dim3(SCAN_BLOCK), 0, s, flags, n, cnt, n_dev);
     MJ_LAUNCH_CHECK();
     scan_impl<uint32_t, uint32_t>(cnt, pre, nb, ws, s);
-    hipLaunchKernelGGL(k_compact_tiles, dim3((unsigned)nb), dim3(SCAN_BLOCK), 0, s, flags, n, pre,
-                       idx_out);
+    hipLaunchKernelGGL(out ? k_compact_tiles<true> : k_compact_tiles<false>, dim3((unsigned)nb),
+                       dim3(SCAN_BLOCK), 0, s, flags, n, pre, idx_out, values, out, n_dev);
     MJ_LAUNCH_CHECK();
     return pre + nb;
+}
+
+const uint32_t *compact_flags_async(const uint8_t *flags, int64_t n, int64_t *idx_out,
+                                    Workspace &ws, hipStream_t s) {
+    return compact(flags, n, idx_out, nullptr, nullptr, nullptr, ws, s);
+}
+
+const uint32_t *compact_values_async(const uint64_t *values, const uint8_t *flags, int64_t n,
+                                     const uint32_t *n_dev, uint64_t *out, Workspace &ws,
+                                     hipStream_t s) {
+    return compact(flags, std::max<int64_t>(n, 1), nullptr, values, out, n_dev, ws, s);
 }
 
 int64_t compact_flags(const uint8_t *flags, int64_t n, int64_t *idx_out, Workspace &ws,

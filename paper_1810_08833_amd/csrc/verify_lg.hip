@@ -899,6 +899,53 @@ __global__ __launch_bounds__(256) void k_lpt_scatter(const uint64_t *pairs, int6
     }
 }
 
+// The order and the bins' offsets by one workgroup, for few pairs (the three launches of
+// build_order cost 15 us, this about 5 for up to LPT_SMALL pairs; more are taken, slower).
+constexpr int LPT_SMALL_THREADS = 1024;
+constexpr int64_t LPT_SMALL = 8192;
+__global__ __launch_bounds__(LPT_SMALL_THREADS) void k_lpt_small(const uint64_t *pairs, int64_t n,
+                                                                 VSet A, VSet B, int kmode,
+                                                                 int classes, uint32_t *off,
+                                                                 int64_t *order,
+                                                                 const uint32_t *ndev,
+                                                                 const uint8_t *keep) {
+    if (ndev) n = min(n, (int64_t)*ndev);
+    __shared__ __attribute__((aligned(16))) uint32_t cnt[LPT_BINS];
+    __shared__ uint32_t tmp[LPT_SMALL_THREADS / 64];
+    static_assert(LPT_BINS == 4 * LPT_SMALL_THREADS, "bins per thread");
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    reinterpret_cast<uint4 *>(cnt)[threadIdx.x] = make_uint4(0u, 0u, 0u, 0u);
+    __syncthreads();
+    for (int64_t i = threadIdx.x; i < n; i += LPT_SMALL_THREADS)
+        if (!keep || keep[i]) atomicAdd(&cnt[lpt_bin(pairs[i], A, B, kmode, classes)], 1u);
+    __syncthreads();
+    const uint4 c = reinterpret_cast<uint4 *>(cnt)[threadIdx.x];
+    const uint32_t sum = c.x + c.y + c.z + c.w;
+    uint32_t inc = sum;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const uint32_t y = (uint32_t)__shfl_up((int)inc, d, 64);
+        if (lane >= d) inc += y;
+    }
+    if (lane == 63) tmp[wv] = inc;
+    __syncthreads();
+    uint32_t base = inc - sum, total = 0;
+    for (int w = 0; w < LPT_SMALL_THREADS / 64; w++) {
+        if (w < wv) base += tmp[w];
+        total += tmp[w];
+    }
+    const uint4 o = make_uint4(base, base + c.x, base + c.x + c.y, base + c.x + c.y + c.z);
+    reinterpret_cast<uint4 *>(cnt)[threadIdx.x] = o;
+    off[4 * threadIdx.x] = o.x;
+    off[4 * threadIdx.x + 1] = o.y;
+    off[4 * threadIdx.x + 2] = o.z;
+    off[4 * threadIdx.x + 3] = o.w;
+    if (threadIdx.x == 0) off[LPT_BINS] = total;
+    __syncthreads();
+    for (int64_t i = threadIdx.x; i < n; i += LPT_SMALL_THREADS)
+        if (!keep || keep[i]) order[atomicAdd(&cnt[lpt_bin(pairs[i], A, B, kmode, classes)], 1u)] = i;
+}
+
 // One persistent launch over band classes: a wave takes the pairs of the widest class
 // first (with that class's lanes per pair and window) and moves to the next narrower class
 // when the current one is dry, so each pair's window fits its own band instead of the
@@ -1137,7 +1184,7 @@ int64_t verify_pairs_batched(const uint64_t *pairs, int64_t n, const DevStrings 
 // The batched verification with the pair count on the device (*n_dev <= cap): pairs
 // longest first, then the persistent launch in the configuration the context timed for this
 // band size (the caller makes sure one is known: `cmax` words of band from the largest K),
-// no host read.  expect: how many pairs there may be (speed only).  flags[n .. cap) are written 0; the band-cell count and the window error
+// no host read.  expect: how many pairs there may be (speed only).  flags[n .. cap) are not written; the band-cell count and the window error
 // word go to cells_out[0..1] (device).
 void verify_pairs_batched_streamed(const uint64_t *pairs, int64_t cap, const uint32_t *n_dev,
                                    const DevStrings &A, const DevStrings &B, int kmode, int cmax,
@@ -1148,14 +1195,12 @@ void verify_pairs_batched_streamed(const uint64_t *pairs, int64_t cap, const uin
     VSet va = vset(A), vb = vset(B);
     cap = std::max<int64_t>(cap, 1);
     constexpr int64_t ZNEXT = 2 * QUEUE_SETS * QUEUES * QSTRIDE, ZCNT = LPT_BINS + 4;
-    uint32_t *zb = ws.get_n<uint32_t>(ZNEXT + 4 + 4 + 2 * ZCNT);
+    uint32_t *zb = ws.zeroed(ZNEXT + 4 + 4 + 2 * ZCNT, s);
     unsigned long long *next = (unsigned long long *)zb;
     unsigned long long *cells = (unsigned long long *)(zb + ZNEXT);
     uint32_t *cnt = zb + ZNEXT + 8;
     uint32_t *fillc = cnt + ZCNT;
-    fill_u32(zb, 0, ZNEXT + 8 + 2 * ZCNT, s);
     *cells_out = cells;
-    fill_u32(reinterpret_cast<uint32_t *>(flags), 0, (cap + 3) / 4, s);
     uint32_t *off = ws.get_n<uint32_t>(LPT_BINS + 1);
     int64_t *order = ws.get_n<int64_t>(cap);
     if (cmax > persist_max_c())
@@ -1175,7 +1220,13 @@ void verify_pairs_batched_streamed(const uint64_t *pairs, int64_t cap, const uin
         block_filter(pairs, cap, A, B, kmode, flags, s, n_dev);
         keep = flags;
     }
-    build_order(pairs, cap, va, vb, kmode, lpt_mode(g), cnt, fillc, off, order, ws, s, n_dev, keep);
+    if (expect <= LPT_SMALL) {
+        hipLaunchKernelGGL(k_lpt_small, dim3(1), dim3(LPT_SMALL_THREADS), 0, s, pairs, cap, va, vb,
+                           kmode, lpt_mode(g), off, order, n_dev, keep);
+        MJ_LAUNCH_CHECK();
+    } else {
+        build_order(pairs, cap, va, vb, kmode, lpt_mode(g), cnt, fillc, off, order, ws, s, n_dev, keep);
+    }
     int th = kt ? kt->begin(KTimer::VERIFY, s) : -1;
     launch_persist(cmax, g, np, blocks, pairs, order, cap, va, vb, kmode, flags, cells, next,
                    s, true, off + LPT_BINS, off);
