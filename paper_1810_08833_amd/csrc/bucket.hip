@@ -5,8 +5,9 @@
 //   k_bucket_pairs  finds a bucket's members (records whose key may occur twice) with two LDS
 //                   bitmaps over 15 more key bits and brings those alone together by slots of
 //                   11 of them, so that the records of a group (equal keys, Alg. 3's hash table
-//                   D) share a slot; every member tests those after it in its slot.  No record is
-//                   sorted by its full key, no group bounded, no pair test numbered.
+//                   D) share a slot; every member is tested against half of its slot, cyclically.
+//                   No record is sorted by its full key, no group bounded, no pair test numbered.
+//                   Beyond 2^23 records the same goes over the member filter's records.
 //   k_long_pairs    slots of more than BK_LONG records (frequent keys), set aside by the first
 //                   kernel: a wave per 64 x 64 tile of their pairs.
 //   k_dedup_buckets the candidates after one or two radix passes by their top bits, each
@@ -23,16 +24,20 @@
 namespace mj {
 
 constexpr int BK_THREADS = 512, BK_WAVES = BK_THREADS / 64;
+constexpr int BK_MTHREADS = 256;  // of a workgroup where all records are members
 constexpr int BK_AVG = 1024;    // records of a bucket aimed at (keys are hashes)
-constexpr int BK_KEEP = 4;      // of a bucket's records each thread keeps in registers
+constexpr int BK_AVG_MEMBERS = 384;  // where (nearly) all of them are members: half of BK_CAP
+constexpr int BK_KEEP = 4, BK_MKEEP = 2;  // of a bucket's records each thread keeps in registers
 constexpr int BK_CAP = 768;     // members of a bucket in short slots
 constexpr int BK_SUB = 15;      // key bits of a bucket's bitmaps; log2 BK_SLOTS of them number the slot
-constexpr int BK_SLOTS = 2048;
-constexpr int BK_STAGE = 512;   // candidates staged before they take room in the output
-constexpr int BK_LONG = 32;     // slots of more records are set aside
+constexpr int BK_SLOTS = 2048, BK_MSLOTS = 1024;
+constexpr int BK_STAGE = 512;  // candidates staged before they take room in the output
+constexpr int BK_LONG = 63;     // slots of more records are set aside
+constexpr int BK_CHUNK = 64;    // buckets whose bounds are found together
 constexpr int BK_LONGS = 64;    // such slots of a bucket
 constexpr int BK_DISTINCT = 32; // distinct keys of such a slot
 constexpr int BK_BLOCKS = 1024; // four workgroups of 39 KB a CU
+constexpr int BK_MBLOCKS = 1536; // six of 28 KB
 constexpr int DD_CAP = 4096, DD_LOG = 13, DD_AVG = 3072, DD_PARTS = 12;
 static_assert(2 * DD_CAP == 1 << DD_LOG, "dedup table");
 
@@ -53,34 +58,36 @@ __device__ __forceinline__ int64_t bucket_start(const uint64_t *__restrict__ key
     return lo;
 }
 
-// A slot's word: its place among the members (bits 0 .. 15), its number among the long slots
-// (16 .. 29), and whether it has no member or is a long one.
-constexpr uint32_t SLOT_LONG = 1u << 31;
+// A slot's word: the place of its next member (bits 0 .. 15), its size or, of a long slot, its
+// number among them (16 .. 29), and whether it is a long one or has fewer than two members.
+constexpr uint32_t SLOT_LONG = 1u << 31, SLOT_LONE = 1u << 30;
 // Why a bucket does not fit (*over): its short slots' members, its long slots, the room for
 // their records, a long slot's distinct keys; the dedup's part of equal leading bits.
 enum : uint32_t { OVER_MEMBERS = 1, OVER_SLOTS, OVER_ROOM, OVER_DISTINCT, OVER_DEDUP };
 
+template <bool MEMBERS>
 struct BucketShared {
+    static constexpr int THREADS = MEMBERS ? BK_MTHREADS : BK_THREADS, WAVES = THREADS / 64;
+    static constexpr int SLOTS = MEMBERS ? BK_MSLOTS : BK_SLOTS;
     uint64_t key[BK_CAP];    // members by slot
     int4 rec[BK_CAP];        // their string id, m, 2 pos - m, K
     uint64_t stage[BK_STAGE];
-    uint32_t seen[1 << (BK_SUB - 5)], again[1 << (BK_SUB - 5)];
-    uint32_t slot[BK_SLOTS];
-    uint32_t tmp[BK_WAVES];
+    uint32_t seen[MEMBERS ? 4 : 1 << (BK_SUB - 5)], again[MEMBERS ? 4 : 1 << (BK_SUB - 5)];
+    uint32_t slot[SLOTS];
+    uint32_t bin[64];        // short slots' members by the size of their slots, then their places
     uint32_t lcount[BK_LONGS], lfill[BK_LONGS];  // long slots: records, those placed
     int64_t lbase[BK_LONGS];
     uint32_t nlong, nstage, members;
     unsigned long long sbase;
     uint64_t found[BK_DISTINCT];
     uint32_t least, same;
-    int64_t bound[BK_WAVES + 1];
+    int64_t bound[BK_CHUNK + 2];
 };
 
-// What the kernels read and write.  Elements are grouped by their top `bits` bits; NARROW: an
-// element is the top half of a record's key << 32 | the record's number (key and val by that
-// number), else the key itself (val beside it).  n from *n_dev when given.
+// What the kernels read and write.  Records are grouped by their keys' top `bits` bits; n from
+// *n_dev when given.
 struct BucketIn {
-    const uint64_t *elem, *key, *val;
+    const uint64_t *key, *val;
     int64_t n;
     const int64_t *n_dev;
     int bits;
@@ -102,37 +109,52 @@ struct BucketOut {
 };
 
 // For inputs of fewer than 2^29 symbols (32-bit filter).  EMIT false: everything but the short
-// slots' candidates (the counts that size the output).
-template <bool EMIT, bool NARROW>
-__global__ __launch_bounds__(BK_THREADS) void k_bucket_pairs(BucketIn in, BucketOut o) {
-    __shared__ __attribute__((aligned(16))) BucketShared sh;
+// slots' candidates (the counts that size the output).  MEMBERS: the records are those the
+// member filter kept, so no bitmaps are needed.
+//
+// A bucket is a chain of short steps between barriers, so what bounds the kernel is how many
+// workgroups a CU holds and what each step waits for: the next bucket's records and this one's
+// lengths are loaded ahead (MEMBERS: 256 threads, six workgroups of 28 KB a CU), the bounds of
+// 64 buckets found at once, and short slots laid out by size, so that a wave's lanes have about
+// as many tests each.  Room in the output is taken in pieces of 256 candidates or more, since
+// one address takes 80 M atomics a second; a bucket of more than the stage holds is tested twice.
+// 17.3 M members, 256 M tests, 10.1 M candidates: 0.70 ms and 0.27 ms for the long slots, where
+// the two more sort passes, the repair, the groups and the emission took 1.9 ms; with a wave's
+// candidates straight to the output and slots in key order 1.47 ms.  7.0 M unfiltered records
+// (0.41 M groups): 142 us, in key order 170.
+template <bool EMIT, bool MEMBERS>
+__global__ __launch_bounds__(MEMBERS ? BK_MTHREADS : BK_THREADS) void k_bucket_pairs(BucketIn in, BucketOut o) {
+    using Shared = BucketShared<MEMBERS>;
+    constexpr int BK_THREADS = Shared::THREADS, BK_WAVES = Shared::WAVES, BK_SLOTS = Shared::SLOTS;
+    constexpr int BK_KEEP = MEMBERS ? BK_MKEEP : mj::BK_KEEP;
+    __shared__ __attribute__((aligned(16))) Shared sh;
     const int64_t n = in.n_dev ? min(in.n, *in.n_dev) : in.n;
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, bits = in.bits;
     const int64_t nb = 1ll << bits;
     const int64_t b0 = nb * blockIdx.x / gridDim.x, b1 = nb * (blockIdx.x + 1) / gridDim.x;
     uint64_t tests = 0, groups = 0, members = 0;  // this thread's
     if (threadIdx.x == 0) sh.nstage = 0;
-    // a passing pair into the stage, or straight out where that is full (whole wave)
-    auto emit = [&](bool pass, int a, int b) {
-        const uint64_t m = __ballot(pass);
-        if (!m) return;
-        const int leader = __ffsll((unsigned long long)m) - 1, cnt = __popcll(m);
+    // passing pairs (whole wave; up to two a lane, of string a) into the stage, counted beyond
+    // its room; `out` >= 0: to there
+    auto emit = [&](bool p0, bool p1, int a, int c0, int c1, int64_t out) {
+        const uint64_t m0 = __ballot(p0), m1 = __ballot(p1), low = (1ull << lane) - 1;
+        if (!(m0 | m1)) return;
         uint32_t at = 0;
-        if (lane == leader) at = atomicAdd(&sh.nstage, (uint32_t)cnt);
-        at = (uint32_t)__shfl((int)at, leader, 64);
-        const uint32_t mine = at + (uint32_t)__popcll(m & ((1ull << lane) - 1));
-        const uint64_t pr = ((uint64_t)(uint32_t)min(a, b) << 32) | (uint32_t)max(a, b);
-        if (pass && mine < BK_STAGE) sh.stage[mine] = pr;
-        const uint32_t fits = at < BK_STAGE ? min((uint32_t)cnt, BK_STAGE - at) : 0u;
-        if (fits < (uint32_t)cnt) {
-            unsigned long long g = 0;
-            if (lane == leader) g = atomicAdd(o.counter, (unsigned long long)(cnt - fits));
-            g = (unsigned long long)__shfl((long long)g, leader, 64) + (mine - at - fits);
-            if (pass && mine >= BK_STAGE && (int64_t)g < o.cap) o.out[g] = pr;
-        }
+        if (lane == 0) at = atomicAdd(&sh.nstage, (uint32_t)(__popcll(m0) + __popcll(m1)));
+        at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
+        auto put = [&](uint32_t i, int c) {
+            const uint64_t pr = ((uint64_t)(uint32_t)min(a, c) << 32) | (uint32_t)max(a, c);
+            if (out >= 0) {
+                if (out + i < o.cap) o.out[out + i] = pr;
+            } else if (i < BK_STAGE) {
+                sh.stage[i] = pr;
+            }
+        };
+        if (p0) put(at + (uint32_t)__popcll(m0 & low), c0);
+        if (p1) put(at + (uint32_t)(__popcll(m0) + __popcll(m1 & low)), c1);
     };
     auto flush = [&](bool all) {  // whole workgroup, after a barrier
-        const uint32_t staged = min(sh.nstage, (uint32_t)BK_STAGE);
+        const uint32_t staged = sh.nstage;
         if (staged == 0 || (!all && staged < BK_STAGE / 2)) return;
         if (threadIdx.x == 0) sh.sbase = atomicAdd(o.counter, (unsigned long long)staged);
         __syncthreads();
@@ -144,94 +166,141 @@ __global__ __launch_bounds__(BK_THREADS) void k_bucket_pairs(BucketIn in, Bucket
         __syncthreads();
     };
     // BK_SUB key bits besides the bucket's (records of equal key agree on them)
-    auto sub = [](uint64_t e) -> uint32_t { return (uint32_t)(NARROW ? e >> 32 : e) & ((1u << BK_SUB) - 1); };
-    for (int64_t c0 = b0; c0 < b1; c0 += BK_WAVES) {
-        // the bounds of the next BK_WAVES buckets, a wave each
+    auto sub = [](uint64_t e) -> uint32_t { return (uint32_t)e & ((1u << BK_SUB) - 1); };
+    for (int64_t c0 = b0; c0 < b1; c0 += BK_CHUNK) {
+        // the bounds of the next buckets: the outer two a wave each, those between a wave each
+        // where they are few (three steps of a 64-way search), else a thread each
+        const int nc = (int)min((int64_t)BK_CHUNK, b1 - c0);
         __syncthreads();
-        for (int w = wv; w <= BK_WAVES; w += BK_WAVES) {
-            const int64_t b = min(c0 + w, b1);
-            const int64_t at = b == 0 ? 0 : b == nb ? n : bucket_start(in.elem, n, 64 - bits, (uint64_t)b);
-            if (lane == 0) sh.bound[w] = at;
+        if (wv < 2) {
+            const int64_t b = c0 + (wv ? nc : 0);
+            const int64_t at = b == 0 ? 0 : b == nb ? n : bucket_start(in.key, n, 64 - bits, (uint64_t)b);
+            if (lane == 0) sh.bound[wv ? nc : 0] = at;
         }
         __syncthreads();
-        for (int c = 0; c < BK_WAVES && c0 + c < b1; c++) {
+        if (nc <= BK_WAVES + 1) {
+            const int64_t a = sh.bound[0], z = sh.bound[nc];
+            if (wv + 1 < nc) {
+                const int64_t at = a + bucket_start(in.key + a, z - a, 64 - bits, (uint64_t)(c0 + wv + 1));
+                if (lane == 0) sh.bound[wv + 1] = at;
+            }
+        }
+        for (int i = 1 + (int)threadIdx.x; i < nc && nc > BK_WAVES + 1; i += BK_THREADS) {
+            int64_t a = sh.bound[0], z = sh.bound[nc];
+            while (a < z) {
+                const int64_t mid = (a + z) >> 1;
+                if (in.key[mid] >> (64 - bits) < (uint64_t)(c0 + i)) a = mid + 1;
+                else z = mid;
+            }
+            sh.bound[i] = a;
+        }
+        if (threadIdx.x == 0) sh.bound[nc + 1] = sh.bound[nc];  // (an empty one after the last)
+        __syncthreads();
+        // MEMBERS: a bucket's records are loaded while the one before it is worked on
+        uint64_t nx[BK_KEEP], nv[BK_KEEP];
+        auto load = [&](int64_t lo, int64_t m, uint64_t *x, uint64_t *v) {
+#pragma unroll
+            for (int u = 0; u < BK_KEEP; u++) {
+                const int64_t i = threadIdx.x + u * BK_THREADS;
+                x[u] = i < m ? in.key[lo + i] : 0;
+                if (MEMBERS && EMIT) v[u] = i < m ? in.val[lo + i] : 0;
+            }
+        };
+        if (MEMBERS) load(sh.bound[0], sh.bound[1] - sh.bound[0], nx, nv);
+        for (int c = 0; c < nc; c++) {
             const int64_t lo = sh.bound[c], m = sh.bound[c + 1] - lo;
-            if (m < 2) continue;  // (uniform)
             const bool keep = m <= BK_KEEP * BK_THREADS;
-            uint64_t x[BK_KEEP];
-            if (keep) {
+            uint64_t x[BK_KEEP], v[BK_KEEP];
+            if (MEMBERS) {
 #pragma unroll
                 for (int u = 0; u < BK_KEEP; u++) {
-                    const int64_t i = threadIdx.x + u * BK_THREADS;
-                    x[u] = i < m ? in.elem[lo + i] : 0;
+                    x[u] = nx[u];
+                    v[u] = EMIT ? nv[u] : 0;
                 }
+                load(sh.bound[c + 1], sh.bound[c + 2] - sh.bound[c + 1], nx, nv);
+            } else if (keep) {
+                load(lo, m, x, v);
             }
+            if (m < 2) continue;  // (uniform)
+            int32_t ml[BK_KEEP], ks[BK_KEEP];
+            auto strings = [&](int u, bool need) {
+                ml[u] = need ? in.len[v[u] >> 32] : 0;
+                ks[u] = need ? in.kk[v[u] >> 32] : 0;
+            };
+            if (MEMBERS && EMIT)
+#pragma unroll
+                for (int u = 0; u < BK_KEEP; u++) strings(u, threadIdx.x + u * BK_THREADS < m);
             auto each = [&](auto f) {
                 if (keep) {
 #pragma unroll
                     for (int u = 0; u < BK_KEEP; u++)
                         if (threadIdx.x + u * BK_THREADS < m) f(x[u], (int64_t)threadIdx.x + u * BK_THREADS);
                 } else {
-                    for (int64_t i = threadIdx.x; i < m; i += BK_THREADS) f(in.elem[lo + i], i);
+                    for (int64_t i = threadIdx.x; i < m; i += BK_THREADS) f(in.key[lo + i], i);
                 }
             };
             {
                 const uint4 z = make_uint4(0u, 0u, 0u, 0u);
-                for (int i = threadIdx.x; i < (1 << (BK_SUB - 7)); i += BK_THREADS) {
-                    reinterpret_cast<uint4 *>(sh.seen)[i] = z;
-                    reinterpret_cast<uint4 *>(sh.again)[i] = z;
-                }
+                if (!MEMBERS)
+                    for (int i = threadIdx.x; i < (1 << (BK_SUB - 7)); i += BK_THREADS) {
+                        reinterpret_cast<uint4 *>(sh.seen)[i] = z;
+                        reinterpret_cast<uint4 *>(sh.again)[i] = z;
+                    }
                 for (int i = threadIdx.x; i < BK_SLOTS / 4; i += BK_THREADS)
                     reinterpret_cast<uint4 *>(sh.slot)[i] = z;
                 if (threadIdx.x < BK_LONGS) sh.lfill[threadIdx.x] = 0;
+                if (threadIdx.x < 64) sh.bin[threadIdx.x] = 0;
                 if (threadIdx.x == 0) sh.nlong = 0;
             }
             __syncthreads();
-            each([&](uint64_t e, int64_t) {
-                const uint32_t h = sub(e), bit = 1u << (h & 31);
-                if (atomicOr(&sh.seen[h >> 5], bit) & bit) atomicOr(&sh.again[h >> 5], bit);
-            });
-            __syncthreads();
-            auto member = [&](uint32_t h) { return ((sh.again[h >> 5] >> (h & 31)) & 1u) != 0; };
+            if (!MEMBERS) {
+                each([&](uint64_t e, int64_t) {
+                    const uint32_t h = sub(e), bit = 1u << (h & 31);
+                    if (atomicOr(&sh.seen[h >> 5], bit) & bit) atomicOr(&sh.again[h >> 5], bit);
+                });
+                __syncthreads();
+            }
+            auto member = [&](uint32_t h) { return MEMBERS || ((sh.again[h >> 5] >> (h & 31)) & 1u) != 0; };
             each([&](uint64_t e, int64_t) {
                 const uint32_t h = sub(e);
                 if (member(h)) atomicAdd(&sh.slot[h & (BK_SLOTS - 1)], 1u);
             });
             __syncthreads();
-            // slots to places: a thread's BK_SLOTS / BK_THREADS consecutive slots
+            // slots to places, those of one size together, the largest first: a thread's
+            // BK_SLOTS / BK_THREADS consecutive slots
             {
                 constexpr int PER = BK_SLOTS / BK_THREADS;
-                uint32_t v[PER], pre[PER], sum = 0;
+                uint32_t v[PER];
 #pragma unroll
                 for (int k = 0; k < PER; k++) {
                     v[k] = sh.slot[threadIdx.x * PER + k];
-                    pre[k] = sum;
-                    sum += v[k] > BK_LONG ? 0u : v[k];
+                    if (v[k] >= 2 && v[k] <= BK_LONG) atomicAdd(&sh.bin[BK_LONG - v[k]], v[k]);
                 }
-                uint32_t inc = sum;
-#pragma unroll
-                for (int d = 1; d < 64; d <<= 1) {
-                    const uint32_t y = (uint32_t)__shfl_up((int)inc, d, 64);
-                    if (lane >= d) inc += y;
-                }
-                if (lane == 63) sh.tmp[wv] = inc;
                 __syncthreads();
-                uint32_t base = inc - sum, total = 0;
-                for (int w = 0; w < BK_WAVES; w++) {
-                    if (w < wv) base += sh.tmp[w];
-                    total += sh.tmp[w];
+                if (wv == 0) {
+                    const uint32_t mine = sh.bin[lane];
+                    uint32_t inc = mine;
+#pragma unroll
+                    for (int d = 1; d < 64; d <<= 1) {
+                        const uint32_t y = (uint32_t)__shfl_up((int)inc, d, 64);
+                        if (lane >= d) inc += y;
+                    }
+                    sh.bin[lane] = inc - mine;
+                    if (lane == 63) sh.members = inc;
                 }
+                __syncthreads();
 #pragma unroll
                 for (int k = 0; k < PER; k++) {
-                    uint32_t word = min(base + pre[k], 0xFFFFu);
+                    uint32_t word = SLOT_LONE;
                     if (v[k] > BK_LONG) {
                         const uint32_t l = atomicAdd(&sh.nlong, 1u);
                         if (l < BK_LONGS) sh.lcount[l] = v[k];
-                        word |= SLOT_LONG | (min(l, (uint32_t)BK_LONGS - 1) << 16);
+                        word = SLOT_LONG | (min(l, (uint32_t)BK_LONGS - 1) << 16);
+                    } else if (v[k] >= 2) {
+                        word = min(atomicAdd(&sh.bin[BK_LONG - v[k]], v[k]), 0xFFFFu) | (v[k] << 16);
                     }
                     sh.slot[threadIdx.x * PER + k] = word;
                 }
-                if (threadIdx.x == 0) sh.members = total;
             }
             __syncthreads();
             const uint32_t M = sh.members, nl = sh.nlong;
@@ -240,14 +309,25 @@ __global__ __launch_bounds__(BK_THREADS) void k_bucket_pairs(BucketIn in, Bucket
                 __syncthreads();
                 continue;
             }
-            if (threadIdx.x < nl) {  // room for the long slots' records
-                const uint32_t cnt = sh.lcount[threadIdx.x];
-                const unsigned long long at = atomicAdd(o.xstate, (1ull << 40) | cnt);
-                const int64_t first = (int64_t)(at & ((1ull << 40) - 1)), d = (int64_t)(at >> 40);
+            if (nl && wv == 0) {  // room for the long slots' records
+                const uint32_t cnt = lane < (int)nl ? sh.lcount[lane] : 0u;
+                uint32_t inc = cnt;
+#pragma unroll
+                for (int d = 1; d < 64; d <<= 1) {
+                    const uint32_t y = (uint32_t)__shfl_up((int)inc, d, 64);
+                    if (lane >= d) inc += y;
+                }
+                unsigned long long at = 0;
+                if (lane == 63) at = atomicAdd(o.xstate, ((unsigned long long)nl << 40) | inc);
+                at = (unsigned long long)__shfl((long long)at, 63, 64);
+                const int64_t first = (int64_t)(at & ((1ull << 40) - 1)) + (inc - cnt);
+                const int64_t d = (int64_t)(at >> 40) + lane;
                 const bool room = first + cnt <= o.xcap && d < o.xslots && cnt < (1u << 24);
-                if (room) o.xslot[d] = make_ulonglong2((unsigned long long)first, cnt);
-                else *o.over = OVER_ROOM;
-                sh.lbase[threadIdx.x] = room ? first : -1;
+                if (lane < (int)nl) {
+                    if (room) o.xslot[d] = make_ulonglong2((unsigned long long)first, cnt);
+                    else *o.over = OVER_ROOM;
+                    sh.lbase[lane] = room ? first : -1;
+                }
             }
             if (nl) __syncthreads();
             // each member's place: among the short slots' (>= 0), or in its long slot
@@ -258,6 +338,7 @@ __global__ __launch_bounds__(BK_THREADS) void k_bucket_pairs(BucketIn in, Bucket
                 if (!member(h)) return NONE;
                 members++;
                 const uint32_t wd = sh.slot[h & (BK_SLOTS - 1)];
+                if (wd & SLOT_LONE) return NONE;
                 if (!(wd & SLOT_LONG)) return (int)(atomicAdd(&sh.slot[h & (BK_SLOTS - 1)], 1u) & 0xFFFFu);
                 const uint32_t l = (wd >> 16) & (BK_LONGS - 1);
                 if (sh.lbase[l] < 0) return NONE;
@@ -277,69 +358,94 @@ __global__ __launch_bounds__(BK_THREADS) void k_bucket_pairs(BucketIn in, Bucket
             };
             if (keep) {  // the loads of a thread's members in flight together
                 int p[BK_KEEP];
-                uint64_t v[BK_KEEP];
-                int32_t ml[BK_KEEP], ks[BK_KEEP];
 #pragma unroll
                 for (int u = 0; u < BK_KEEP; u++)
                     p[u] = threadIdx.x + u * BK_THREADS < m ? place(x[u]) : NONE;
+                if (!MEMBERS) {
 #pragma unroll
-                for (int u = 0; u < BK_KEEP; u++) {
-                    v[u] = 0;
-                    if (p[u] == NONE) continue;
-                    const int64_t r = NARROW ? (int64_t)(uint32_t)x[u]
-                                             : lo + threadIdx.x + u * BK_THREADS;
-                    if (NARROW) x[u] = in.key[r];
-                    if (EMIT) v[u] = in.val[r];
-                }
+                    for (int u = 0; u < BK_KEEP; u++)
+                        v[u] = EMIT && p[u] != NONE ? in.val[lo + threadIdx.x + u * BK_THREADS] : 0;
 #pragma unroll
-                for (int u = 0; u < BK_KEEP; u++) {
-                    ml[u] = ks[u] = 0;
-                    if (!EMIT || p[u] == NONE) continue;
-                    ml[u] = in.len[v[u] >> 32];
-                    ks[u] = in.kk[v[u] >> 32];
+                    for (int u = 0; u < BK_KEEP; u++) strings(u, EMIT && p[u] != NONE);
+                } else if (!EMIT) {
+#pragma unroll
+                    for (int u = 0; u < BK_KEEP; u++) strings(u, false);
                 }
 #pragma unroll
                 for (int u = 0; u < BK_KEEP; u++)
                     if (p[u] != NONE) put(p[u], x[u], v[u], ml[u], ks[u]);
             } else {
                 for (int64_t i = threadIdx.x; i < m; i += BK_THREADS) {
-                    const uint64_t e = in.elem[lo + i];
+                    const uint64_t e = in.key[lo + i];
                     const int p = place(e);
                     if (p == NONE) continue;
-                    const int64_t r = NARROW ? (int64_t)(uint32_t)e : lo + i;
-                    const uint64_t v = EMIT ? in.val[r] : 0;
-                    put(p, NARROW ? in.key[r] : e, v, EMIT ? in.len[v >> 32] : 0,
+                    const uint64_t v = EMIT ? in.val[lo + i] : 0;
+                    put(p, e, v, EMIT ? in.len[v >> 32] : 0,
                         EMIT ? in.kk[v >> 32] : 0);
                 }
             }
+            const uint32_t before = EMIT ? sh.nstage : 0;
             __syncthreads();
-            // members of short slots, one a lane, against those after them in their slot
-            for (int p0 = 64 * wv; p0 < (int)M; p0 += BK_THREADS) {
-                const int p = p0 + lane;
-                int e = 0, q = p + 1;
-                uint64_t kp = 0;
-                if (p < (int)M) {
-                    kp = sh.key[p];
-                    e = (int)(sh.slot[(uint32_t)(NARROW ? kp >> 32 : kp) & (BK_SLOTS - 1)] & 0xFFFFu);
-                }
-                uint32_t same = 0;
-                for (; __any(q < e); q++) {
-                    const bool eq = q < e && sh.key[q] == kp;
-                    same += eq ? 1u : 0u;
-                    if (EMIT) {
-                        int4 u = {}, v = {};
-                        if (eq) {
-                            u = sh.rec[p];
-                            v = sh.rec[q];
+            // Members of short slots, one a lane, each against the half of its slot that follows
+            // it (cyclically): lanes of one slot have the same number of tests, and neighbouring
+            // slots are of one size.
+            auto pairs = [&](int64_t out) {
+                for (int p0 = 64 * wv; p0 < (int)M; p0 += BK_THREADS) {
+                    const int p = p0 + lane;
+                    int first = 0, z = 0, nd = 0;
+                    uint64_t kp = 0;
+                    int4 u = {};
+                    if (p < (int)M) {
+                        kp = sh.key[p];
+                        if (EMIT) u = sh.rec[p];
+                        const uint32_t wd = sh.slot[(uint32_t)kp & (BK_SLOTS - 1)];
+                        z = (int)(wd >> 16);
+                        first = (int)(wd & 0xFFFFu) - z;
+                        nd = (z - 1) / 2 + (z % 2 == 0 && p - first < z / 2 ? 1 : 0);
+                        if (out < 0) {  // a group's first member in the slot, with another after it
+                            int q = p - 1;
+                            while (q >= first && sh.key[q] != kp) q--;
+                            if (q < first) {
+                                q = p + 1;
+                                while (q < first + z && sh.key[q] != kp) q++;
+                                groups += q < first + z ? 1 : 0;
+                            }
                         }
-                        emit(eq && u.x != v.x &&
-                                 (uint32_t)max(abs(u.y - v.y), abs(u.z - v.z)) <=
-                                     max((uint32_t)u.w, (uint32_t)v.w),
-                             u.x, v.x);
                     }
+                    uint32_t same = 0;
+                    int q = p;
+                    auto close = [&](const int4 &v) {
+                        return u.x != v.x && (uint32_t)max(abs(u.y - v.y), abs(u.z - v.z)) <=
+                                                 max((uint32_t)u.w, (uint32_t)v.w);
+                    };
+                    for (int d = 1; __any(d <= nd); d += 2) {
+                        const int q0 = q + 1 >= first + z ? first : q + 1;
+                        q = q0 + 1 >= first + z ? first : q0 + 1;
+                        const bool e0 = d <= nd && sh.key[q0] == kp, e1 = d < nd && sh.key[q] == kp;
+                        same += (e0 ? 1u : 0u) + (e1 ? 1u : 0u);
+                        if (EMIT) {
+                            const int4 v0 = sh.rec[e0 ? q0 : 0], v1 = sh.rec[e1 ? q : 0];
+                            emit(e0 && close(v0), e1 && close(v1), u.x, v0.x, v1.x, out);
+                        }
+                    }
+                    if (out < 0) tests += same;
                 }
-                tests += same;
-                groups += same == 1 ? 1 : 0;  // a group's last member but one
+            };
+            pairs(-1);
+            if (EMIT) {
+                __syncthreads();
+                const uint32_t staged = sh.nstage;
+                if (staged > BK_STAGE) {  // this bucket's straight to the output, in one piece
+                    __syncthreads();
+                    if (threadIdx.x == 0) {
+                        sh.sbase = atomicAdd(o.counter, (unsigned long long)(staged - before));
+                        sh.nstage = 0;
+                    }
+                    __syncthreads();
+                    pairs((int64_t)sh.sbase);
+                    __syncthreads();
+                    if (threadIdx.x == 0) sh.nstage = before;
+                }
             }
             // long slots: how often each of their (few) distinct keys occurs
             for (uint32_t l = 0; l < nl; l++) {
@@ -353,18 +459,18 @@ __global__ __launch_bounds__(BK_THREADS) void k_bucket_pairs(BucketIn in, Bucket
                         break;
                     }
                     if (threadIdx.x == 0) {
-                        sh.least = ~0u;
+                        sh.least = k ? ~0u : 0u;
                         sh.same = 0;
                     }
                     __syncthreads();
-                    uint32_t least = ~0u;  // the first record whose key is not among the k found
+                    uint32_t least = k ? ~0u : 0u;  // the first record whose key is not among the k found
                     for (uint32_t i = threadIdx.x; i < cnt && least == ~0u; i += BK_THREADS) {
                         const uint64_t y = o.xkey[first + i];
                         bool known = false;
                         for (int j = 0; j < k; j++) known = known || sh.found[j] == y;
                         if (!known) least = i;
                     }
-                    if (least != ~0u) atomicMin(&sh.least, least);
+                    if (k && least != ~0u) atomicMin(&sh.least, least);
                     __syncthreads();
                     const uint64_t y = o.xkey[first + sh.least];
                     uint32_t mine = 0;
@@ -408,6 +514,7 @@ __global__ __launch_bounds__(BK_THREADS) void k_bucket_pairs(BucketIn in, Bucket
 }
 
 // ustart[d] = the 64 x 64 tile pairs of the long slots before slot d; ustart[slots] = all.
+constexpr int LU_ITEMS = 8;
 __global__ __launch_bounds__(BK_THREADS) void k_long_units(const ulonglong2 *__restrict__ xslot,
                                                            int64_t xslots,
                                                            const unsigned long long *xstate,
@@ -415,31 +522,36 @@ __global__ __launch_bounds__(BK_THREADS) void k_long_units(const ulonglong2 *__r
     __shared__ uint64_t tmp[BK_WAVES];
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int64_t d = min(xslots, (int64_t)(*xstate >> 40));
-    const int64_t per = (d + BK_THREADS - 1) / BK_THREADS;
-    const int64_t i0 = min(d, (int64_t)threadIdx.x * per), i1 = min(d, i0 + per);
-    auto units = [&](int64_t i) -> uint64_t {
-        const uint64_t nt = (xslot[i].y + 63) / 64;
-        return nt * (nt + 1) / 2;
-    };
-    uint64_t sum = 0;
-    for (int64_t i = i0; i < i1; i++) sum += units(i);
-    uint64_t inc = sum;
-    for (int s = 1; s < 64; s <<= 1) {
-        const uint64_t y = (uint64_t)__shfl_up((long long)inc, s, 64);
-        if (lane >= s) inc += y;
+    uint64_t run = 0;  // the units of the slots before this chunk
+    for (int64_t c0 = 0; c0 < d; c0 += BK_THREADS * LU_ITEMS) {
+        const int64_t i0 = c0 + (int64_t)threadIdx.x * LU_ITEMS;
+        uint64_t v[LU_ITEMS], sum = 0;
+#pragma unroll
+        for (int k = 0; k < LU_ITEMS; k++) v[k] = i0 + k < d ? xslot[i0 + k].y : 0;
+#pragma unroll
+        for (int k = 0; k < LU_ITEMS; k++) {
+            const uint64_t nt = (v[k] + 63) / 64;
+            v[k] = sum;
+            sum += nt * (nt + 1) / 2;
+        }
+        uint64_t inc = sum;
+        for (int s = 1; s < 64; s <<= 1) {
+            const uint64_t y = (uint64_t)__shfl_up((long long)inc, s, 64);
+            if (lane >= s) inc += y;
+        }
+        __syncthreads();
+        if (lane == 63) tmp[wv] = inc;
+        __syncthreads();
+        uint64_t at = run + inc - sum;
+        for (int w = 0; w < BK_WAVES; w++) {
+            if (w < wv) at += tmp[w];
+            run += tmp[w];
+        }
+#pragma unroll
+        for (int k = 0; k < LU_ITEMS; k++)
+            if (i0 + k < d) ustart[i0 + k] = at + v[k];
     }
-    if (lane == 63) tmp[wv] = inc;
-    __syncthreads();
-    uint64_t run = inc - sum, total = 0;
-    for (int w = 0; w < BK_WAVES; w++) {
-        if (w < wv) run += tmp[w];
-        total += tmp[w];
-    }
-    for (int64_t i = i0; i < i1; i++) {
-        ustart[i] = run;
-        run += units(i);
-    }
-    if (threadIdx.x == 0) ustart[d] = total;
+    if (threadIdx.x == 0) ustart[d] = run;
 }
 
 // A wave takes a share of the tile pairs I <= J in order: lane l holds record 64 I + l, tile
@@ -549,16 +661,16 @@ static int bits_for(int64_t n, int64_t avg) {  // 2^bits buckets of about avg
 // bucket, one for up to 2^8, two for up to 2^16.
 static int bucket_passes(int bits) { return bits == 0 ? 0 : bits <= 8 ? 1 : 2; }
 
-bool bucket_join_fits(int64_t records, int64_t total) {
-    return records >= 2 && records <= BK_RECORDS_MAX && total < (1ll << 29);
+bool bucket_join_fits(int64_t records, bool members, int64_t total) {
+    return records >= 2 && records <= (members ? BK_MEMBERS_MAX : BK_RECORDS_MAX) && total < (1ll << 29);
 }
 
-BucketRecords bucket_records(uint64_t *key, uint64_t *val, int64_t cap, int64_t expect,
+BucketRecords bucket_records(uint64_t *key, uint64_t *val, int64_t cap, int64_t expect, bool members,
                              const int64_t *n_dev, Workspace &ws, hipStream_t s) {
     BucketRecords r;
     r.n = cap;
     r.n_dev = n_dev;
-    r.bits = std::min(16, bits_for(std::max<int64_t>(expect, 1), BK_AVG));
+    r.bits = std::min(16, bits_for(std::max<int64_t>(expect, 1), members ? BK_AVG_MEMBERS : BK_AVG));
     r.key = key;
     r.val = val;
     for (int p = bucket_passes(r.bits); p > 0; p--) {
@@ -568,7 +680,8 @@ BucketRecords bucket_records(uint64_t *key, uint64_t *val, int64_t cap, int64_t 
         r.val = vo;
     }
     const int64_t nb = 1ll << r.bits;
-    r.blocks = (int)std::min<int64_t>(nb, BK_BLOCKS);
+    r.blocks = (int)std::min<int64_t>(nb, members ? BK_MBLOCKS : BK_BLOCKS);
+    r.members = members;
     // the workgroups' sums; candidates, over, the long slots' state
     r.state = reinterpret_cast<uint64_t *>(ws.zeroed(6, s));
     r.part = ws.get_n<uint64_t>(3 * r.blocks);
@@ -587,12 +700,13 @@ void bucket_reset(const BucketRecords &r, hipStream_t s) { fill_u64(r.state, 0, 
 
 void bucket_pairs(const BucketRecords &r, const DevStrings &d, bool emit, uint64_t *out, int64_t cap,
                   bool longs, hipStream_t s, KTimer *kt) {
-    const BucketIn in{r.key, nullptr, r.val, r.n, r.n_dev, r.bits, d.len, d.kk};
+    const BucketIn in{r.key, r.val, r.n, r.n_dev, r.bits, d.len, d.kk};
     const BucketOut o{out, cap, r.counter, r.part, r.over, r.xkey, r.xrec, r.xcap, r.xslot, r.xslots,
                       r.counter + 2};
     int th = kt ? kt->begin(KTimer::EMIT, s) : -1;
-    hipLaunchKernelGGL((emit ? k_bucket_pairs<true, false> : k_bucket_pairs<false, false>),
-                       dim3((unsigned)r.blocks), dim3(BK_THREADS), 0, s, in, o);
+    hipLaunchKernelGGL((r.members ? emit ? k_bucket_pairs<true, true> : k_bucket_pairs<false, true>
+                                  : emit ? k_bucket_pairs<true, false> : k_bucket_pairs<false, false>),
+                       dim3((unsigned)r.blocks), dim3(r.members ? BK_MTHREADS : BK_THREADS), 0, s, in, o);
     MJ_LAUNCH_CHECK();
     if (emit && longs) {
         hipLaunchKernelGGL(k_long_units, dim3(1), dim3(BK_THREADS), 0, s, r.xslot, r.xslots,

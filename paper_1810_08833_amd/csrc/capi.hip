@@ -103,8 +103,8 @@ static bool use_members(const mj_ctx *ctx, int64_t records) {
 
 // Grouping by LDS buckets.  A context told to test every join's large groups by tile pairs
 // (tile_min 0) takes the path that has them.
-static bool use_buckets(const mj_ctx *ctx, int64_t records, int64_t total) {
-    return ctx->tile_min != 0 && bucket_join_fits(records, total);
+static bool use_buckets(const mj_ctx *ctx, int64_t records, bool members, int64_t total) {
+    return ctx->tile_min != 0 && bucket_join_fits(records, members, total);
 }
 
 extern "C" mj_status mj_ctx_set_streaming(mj_ctx *ctx, int mode) {
@@ -352,9 +352,9 @@ static mj_pairs *run_join(mj_ctx *ctx, const mj_strings *strings, const mj_param
     const uint64_t pass_tests = (uint64_t)ctx->pair_test_pass;
     // by LDS buckets where the buckets fit (their records grouped, not sorted further)
     BucketRecords br;
-    bool bucket = !members && use_buckets(ctx, R, d.total), longs = false;
+    bool bucket = use_buckets(ctx, M, members, d.total), longs = false;
     if (bucket) {
-        br = bucket_records(gkey, gval, R, R, nullptr, ws, s);
+        br = bucket_records(gkey, gval, M, M, members, nullptr, ws, s);
         bucket_pairs(br, d, false, nullptr, 0, false, s);
         std::vector<uint64_t> part(3 * br.blocks + 3);
         MJ_HIP(hipMemcpyAsync(ctx->pinned, br.part, (size_t)3 * br.blocks * 8, hipMemcpyDeviceToHost, s));
@@ -644,8 +644,9 @@ static bool plan_streamed(mj_ctx *ctx, const mj_params *params, const DevStrings
                                pl.scap, (int64_t)(1.1 * h.mem_per_bound * (double)pl.rcap) + 65536))
                          : pl.scap;
     pl.emit = h.emit;
-    pl.rexp = std::min<int64_t>(pl.scap, (int64_t)(h.rec_per_bound * (double)pl.rcap));
-    pl.bucket = h.bucket && !pl.members && use_buckets(ctx, pl.scap, d.total) &&
+    pl.rexp = std::min<int64_t>(
+        pl.mcap, (int64_t)((pl.members ? h.mem_per_bound : h.rec_per_bound) * (double)pl.rcap));
+    pl.bucket = h.bucket && use_buckets(ctx, pl.mcap, pl.members, d.total) &&
                 dedup_buckets_fit(pl.cexp, d.n, d.n);
     pl.longs = h.longs;
     return true;
@@ -680,7 +681,7 @@ static StreamedDev launch_streamed_main(mj_ctx *ctx, DevStrings &d, const Partit
     unsigned long long *c0 = nullptr;
     const uint32_t *u = nullptr;
     if (pl.bucket) {
-        br = bucket_records(gkey, gval, pl.mcap, pl.rexp, M_dev, ws, s);
+        br = bucket_records(gkey, gval, pl.mcap, pl.rexp, pl.members, M_dev, ws, s);
         if (tm) tm->mark();  // 2 sort
         c0 = br.counter;
         bucket_pairs(br, d, true, cand, pl.ccap, pl.longs, s, kt);

@@ -44,7 +44,8 @@ struct StreamedPlan {
     bool members = false;  // the member filter runs; mcap: room for its records
     int64_t mcap = 0;
     EmitHints emit;
-    // grouping, pair tests and dedup by LDS buckets; about how many records and candidates
+    // grouping, pair tests and dedup by LDS buckets; about how many records (of the member
+    // filter, where it runs) and candidates
     bool bucket = false, longs = false;
     int64_t rexp = 0, cexp = 0;
     int64_t vexp = 0;  // about how many distinct candidates

@@ -174,7 +174,7 @@ const uint32_t *compact_values_async(const uint64_t *values, const uint8_t *flag
                                      const uint32_t *n_dev, uint64_t *out, Workspace &ws,
                                      hipStream_t s);
 // Size of the pinned host buffer each context keeps for small device-to-host reads.
-constexpr size_t HOST_SCRATCH_BYTES = 32768;
+constexpr size_t HOST_SCRATCH_BYTES = 65536;
 
 // Stable sort of keys (and an optional payload) ascending, in place.  key_mask has a 1
 // at every bit that may be set in some key (the others must be zero in all keys).
@@ -389,15 +389,18 @@ void probe_emit(const Probe &p, const uint64_t *qval, const uint64_t *ival, cons
                 const DevStrings &id, uint64_t expect, uint64_t *out, int64_t cap, hipStream_t s);
 
 // bucket.hip
-// Joins of up to BK_RECORDS_MAX records over fewer than 2^29 symbols: grouping, pair tests
-// and dedup by buckets in LDS, a general path's results without its sorts.
-constexpr int64_t BK_RECORDS_MAX = (int64_t)1 << 23;
+// Joins of up to BK_RECORDS_MAX records, or of up to BK_MEMBERS_MAX that the member filter
+// kept, over fewer than 2^29 symbols: grouping, pair tests and dedup by buckets in LDS, a
+// general path's results without its sorts.  Two radix passes make at most 2^16 buckets: the
+// first limit leaves them 128 records each, the second 384 (half of what their LDS holds).
+constexpr int64_t BK_RECORDS_MAX = (int64_t)1 << 23, BK_MEMBERS_MAX = (int64_t)3 << 23;
 struct BucketRecords {
     uint64_t *key = nullptr, *val = nullptr;  // grouped by their top `bits` key bits
     int64_t n = 0;                            // records, or their capacity (n_dev)
     const int64_t *n_dev = nullptr;
     int bits = 0;
     int blocks = 0;
+    bool members = false;      // (nearly) all of them share their key
     uint64_t *part = nullptr;  // pair tests, groups and members by workgroup (3 * blocks words)
     // 3 words, zero at first: the candidates' number, over (set when a bucket does not fit:
     // nothing else is then worth reading) and the long slots' state (slots << 40 | records)
@@ -411,9 +414,10 @@ struct BucketRecords {
     ulonglong2 *xslot = nullptr;
     uint64_t *ustart = nullptr;
 };
-bool bucket_join_fits(int64_t records, int64_t total);
-// expect: how many records there may be (speed, and whether the buckets fit)
-BucketRecords bucket_records(uint64_t *key, uint64_t *val, int64_t cap, int64_t expect,
+bool bucket_join_fits(int64_t records, bool members, int64_t total);
+// expect: how many records there may be (speed, and whether the buckets fit); members: the
+// member filter kept them
+BucketRecords bucket_records(uint64_t *key, uint64_t *val, int64_t cap, int64_t expect, bool members,
                              const int64_t *n_dev, Workspace &ws, hipStream_t s);
 void bucket_reset(const BucketRecords &r, hipStream_t s);  // before a second bucket_pairs
 // emit: the candidates to out[0 .. cap), their number (which may exceed cap) added to

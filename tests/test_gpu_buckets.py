@@ -55,6 +55,9 @@ INPUTS = {
         shared_segments(2, 1, 31), shared_segments(3, 1, 32), shared_segments(4, 1, 33))), []), 4),
     "hundred_a_group": lambda: shared_segments(5, 4, 100),
     "tandem": lambda: tandem(6, 60),
+    "groups_of_62_to_65": lambda: dg.from_list(sum(([s.get(i) for i in range(s.n)] for s in (
+        shared_segments(8, 1, 62), shared_segments(9, 1, 63), shared_segments(10, 1, 64),
+        shared_segments(11, 1, 65))), []), 4),
     "many_buckets": lambda: shared_segments(7, 300, 10),
 }
 
@@ -84,3 +87,28 @@ def test_buckets_match_oracle(mj, name):
     got, _ = mj.join(dev(mj, T), p, ctx=ctx)
     _, want, _ = oracle.join(T.chars, T.offsets, oracle.make_params(5, 4, k=30, t_div=2))
     assert np.array_equal(got, want)
+
+
+@pytest.mark.parametrize("name", sorted(INPUTS))
+def test_member_buckets_match_oracle(mj, name):
+    """The same over the records that the member filter keeps (nearly all of them members), with
+    one distinct bucket limit that keeps every record."""
+    say("member_buckets", name)
+    S = INPUTS[name]()
+    want_c, want, _ = oracle.join(S.chars, S.offsets, oracle.make_params(5, 4, k=30, t_div=2))
+    p = mj.Params(q=5, k=30, t_div=2)
+    for limit in (0, 1):
+        ctx = mj.Context()
+        ctx.set_member_filter(1, limit)
+        cand, st = mj.candidates(dev(mj, S), p, ctx=ctx)
+        assert st["member_filter"] == 1 and np.array_equal(cand, want_c)
+        for mode in (0, 1, 1, 2, 2):
+            ctx.set_streaming(mode)
+            got, sj = mj.join(dev(mj, S), p, ctx=ctx)
+            assert np.array_equal(got, want), mode
+            for f in ("records", "groups", "pair_tests", "candidates"):
+                assert sj[f] == st[f], (mode, f)
+    plain, sp = mj.candidates(dev(mj, S), p)
+    assert np.array_equal(plain, want_c)
+    for f in ("records", "groups", "pair_tests", "candidates"):
+        assert sp[f] == st[f], f
