@@ -1039,9 +1039,16 @@ extern "C" mj_status mj_index_build(mj_ctx *ctx, const mj_strings *strings, cons
         ix->bits = d.bits;
         ix->total = d.total;
         ix->np = verify_planes(d.bits);
-        ix->offsets = (int64_t *)dev_alloc(((size_t)d.n + 1) * 8);
-        ix->len = (int32_t *)dev_alloc(((size_t)d.n + 1) * 4);
-        ix->kk = (int32_t *)dev_alloc(((size_t)d.n + 1) * 4);
+        ix->plane_words = plane_words_for(d.total);
+        const size_t tb = pp.pi_table ? (size_t)8 << (pp.q * d.bits) : 0;
+        size_t at[6] = {0, ((size_t)d.n + 1) * 8, ((size_t)d.n + 1) * 4, ((size_t)d.n + 1) * 4,
+                        (size_t)ix->np * ix->plane_words * 4, tb};
+        for (int i = 1; i < 6; i++) at[i] = at[i - 1] + ((at[i] + 255) & ~(size_t)255);
+        uint8_t *block = (uint8_t *)dev_alloc(at[5]);
+        ix->offsets = (int64_t *)block;
+        ix->len = (int32_t *)(block + at[1]);
+        ix->kk = (int32_t *)(block + at[2]);
+        ix->planes = (uint32_t *)(block + at[3]);
         MJ_HIP(hipMemcpyAsync(ix->offsets, d.offsets, ((size_t)d.n + 1) * 8, hipMemcpyDeviceToDevice, s));
         // the symbols are read from the caller's buffer during the build only: the index
         // keeps the verifier's bit planes, not the input
@@ -1053,8 +1060,6 @@ extern "C" mj_status mj_index_build(mj_ctx *ctx, const mj_strings *strings, cons
             MJ_HIP(hipMemcpyAsync(ix->len, di.len, (size_t)d.n * 4, hipMemcpyDeviceToDevice, s));
             MJ_HIP(hipMemcpyAsync(ix->kk, di.kk, (size_t)d.n * 4, hipMemcpyDeviceToDevice, s));
         }
-        ix->plane_words = plane_words_for(di.total);
-        ix->planes = (uint32_t *)dev_alloc((size_t)ix->np * ix->plane_words * 4);
         pack_planes(di, ix->np, ws, s, ix->planes);
         sorted_records(di, pk, halo, ix->rec, ws, s, ctx->pinned);
         ix->dir_bits = key_directory_bits(ix->rec.count);
@@ -1063,8 +1068,7 @@ extern "C" mj_status mj_index_build(mj_ctx *ctx, const mj_strings *strings, cons
         if (pp.pi_table) {
             // searches partition their queries with this table long after the caller's
             // copy may be gone: the index keeps its own
-            const size_t tb = (size_t)8 << (pp.q * d.bits);
-            ix->pi_table = (uint64_t *)dev_alloc(tb);
+            ix->pi_table = (uint64_t *)(block + at[4]);
             MJ_HIP(hipMemcpyAsync(ix->pi_table, pp.pi_table, tb, hipMemcpyDeviceToDevice, s));
             pp.pi_table = ix->pi_table;
         }
@@ -1082,11 +1086,7 @@ extern "C" mj_status mj_index_build(mj_ctx *ctx, const mj_strings *strings, cons
 extern "C" void mj_index_free(mj_index *ix) {
     if (!ix) return;
     (void)hipSetDevice(ix->device);
-    dev_free(ix->offsets, ix->alloc);
-    dev_free(ix->len, ix->alloc);
-    dev_free(ix->kk, ix->alloc);
-    dev_free(ix->planes, ix->alloc);
-    dev_free(ix->pi_table, ix->alloc);
+    dev_free(ix->offsets, ix->alloc);  // and what follows it in its block
     dev_free(ix->dir, ix->alloc);
     ix->rec.release();
     delete ix;

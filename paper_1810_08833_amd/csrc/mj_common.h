@@ -258,7 +258,7 @@ struct PartitionParams {
 // optionally the length.
 // Partition records.  With `ws` set the arrays come from that workspace (valid until
 // its release); otherwise they are owned allocations freed by release().
-struct RecBuf {
+struct RecBuf {  // (val and len in key's block)
     uint64_t *key = nullptr;
     uint64_t *val = nullptr;
     uint32_t *len = nullptr;

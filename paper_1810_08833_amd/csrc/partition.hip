@@ -1637,25 +1637,22 @@ void RecBuf::reserve(int64_t need, hipStream_t s) {
     if (need <= cap) return;
     int64_t nc = std::max<int64_t>(need, cap + cap / 2);
     auto get = [&](size_t bytes) -> void * { return ws ? ws->get(bytes) : dev_alloc(bytes, alloc); };
-    uint64_t *k2 = (uint64_t *)get((size_t)nc * 8);
-    uint64_t *v2 = (uint64_t *)get((size_t)nc * 8);
-    uint32_t *l2 = with_len ? (uint32_t *)get((size_t)nc * 4) : nullptr;
+    const int64_t pitch = (nc + 31) & ~(int64_t)31;  // one block: val and len start 256-byte aligned
+    uint64_t *k2 = (uint64_t *)get((size_t)pitch * (with_len ? 20 : 16));
+    uint64_t *v2 = k2 + pitch;
+    uint32_t *l2 = with_len ? (uint32_t *)(v2 + pitch) : nullptr;
     if (count > 0) {
         MJ_HIP(hipMemcpyAsync(k2, key, (size_t)count * 8, hipMemcpyDeviceToDevice, s));
         MJ_HIP(hipMemcpyAsync(v2, val, (size_t)count * 8, hipMemcpyDeviceToDevice, s));
         if (with_len) MJ_HIP(hipMemcpyAsync(l2, len, (size_t)count * 4, hipMemcpyDeviceToDevice, s));
         MJ_HIP(hipStreamSynchronize(s));
     }
-    if (!ws) {
-        dev_free(key, alloc); dev_free(val, alloc); dev_free(len, alloc);
-    }
+    if (!ws) dev_free(key, alloc);
     key = k2; val = v2; len = l2; cap = nc;
 }
 
 void RecBuf::release() {
-    if (!ws) {
-        dev_free(key, alloc); dev_free(val, alloc); dev_free(len, alloc);
-    }
+    if (!ws) dev_free(key, alloc);
     key = val = nullptr; len = nullptr; cap = count = 0;
 }
 
