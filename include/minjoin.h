@@ -133,13 +133,14 @@ typedef struct {
     int32_t verify_words;  /* band words per lane of the batched verifier */
     int32_t verify_blocks; /* most workgroups the batched verifier's persistent launch may
                               have (fewer when the pairs need fewer) */
-    int32_t streamed;      /* 1: the join sized its stages on the device (see mj_join);
+    int32_t streamed;      /* 1: the call sized its stages on the device (see mj_join; a
+                              search does so after one over an index of the same size);
                               2: the same, replayed from captured graphs */
     int32_t host_reads;    /* reads of device values the host waited for: 2 when
                               streamed, 0 (not counted) stage by stage */
-    int32_t member_filter; /* 1: only the records that may share their key went through
-                              the record sort (see mj_ctx_set_member_filter) */
-    int64_t members;       /* records sorted and grouped (records when member_filter is 0) */
+    int32_t member_filter; /* 1: only the records that may share their key were grouped
+                              (see mj_ctx_set_member_filter) */
+    int64_t members;       /* records grouped (records when member_filter is 0) */
 } mj_stats;
 
 /* ---- context ---------------------------------------------------------------- */
@@ -172,16 +173,15 @@ mj_status mj_ctx_set_pair_test_pass(mj_ctx *ctx, int64_t tests);
 /* Joins with at least min_records records (default 2^23; 0: every join; -1: none) first
  * keep only the records that may share their key with another one -- those whose key's top
  * 32 bits occur twice, found with two radix passes over 8-byte elements (ordering them by
- * the key's top 16 bits into buckets) and a per-bucket LDS bitmap -- and sort and group
- * those alone.  A bucket of more than bucket_limit records (0: the default, 65,536) is
+ * the key's top 16 bits into buckets) and a per-bucket LDS bitmap -- and group those alone.  A bucket of more than bucket_limit records (0: the default, 65,536) is
  * kept whole.  Results are the same either way (a record whose key occurs once forms no
  * group); the filter saves time when most records are unique.  EINVAL for a NULL context,
  * min_records < -1 or bucket_limit < 0. */
 mj_status mj_ctx_set_member_filter(mj_ctx *ctx, int64_t min_records, int32_t bucket_limit);
 /* Candidate emission by tile pairs (Alg. 3's pair tests within a bucket of D): in a join
  * whose groups of 64 records or more hold at least min_tile_pairs tile pairs of 64 x 64
- * records (default 32,768; 0: every join with such groups; -1: none), those groups' record
- * pairs are tested a tile pair per wavefront and the smaller groups' test by test; else
+ * records (default 32,768; 0: every join with such groups, none of which then groups in LDS
+ * buckets; -1: none), those groups' record pairs are tested a tile pair per wavefront and the smaller groups' test by test; else
  * every group's test by test.  Results are the same either way (the same pairs are tested
  * with the same filter); tile pairs save time when there are many of them.  A streamed
  * join follows the choice of the last join of its shape.  EINVAL for a NULL context or
@@ -264,7 +264,8 @@ mj_status mj_index_build(mj_ctx *ctx, const mj_strings *strings, const mj_params
                          void *stream, mj_index **out);
 void mj_index_free(mj_index *index);
 int64_t mj_index_records(const mj_index *index);
-/* Device memory the index holds, in bytes (records, planes, lengths, thresholds, offsets). */
+/* Device memory the index holds, in bytes (records and their key directory, planes, lengths,
+ * thresholds, offsets). */
 int64_t mj_index_bytes(const mj_index *index);
 
 /* queries: borrowed; qparams->k / k_per_string give each query's K, qparams->verifier and
