@@ -123,7 +123,8 @@ struct BucketOut {
 // candidates straight to the output and slots in key order 1.47 ms.  7.0 M unfiltered records
 // (0.41 M groups): 142 us, in key order 170.
 template <bool EMIT, bool MEMBERS>
-__global__ __launch_bounds__(MEMBERS ? BK_MTHREADS : BK_THREADS) void k_bucket_pairs(BucketIn in, BucketOut o) {
+__global__ __launch_bounds__(MEMBERS ? BK_MTHREADS : BK_THREADS) void k_bucket_pairs(BucketIn in,
+                                                                                    BucketOut o) {
     using Shared = BucketShared<MEMBERS>;
     constexpr int BK_THREADS = Shared::THREADS, BK_WAVES = Shared::WAVES, BK_SLOTS = Shared::SLOTS;
     constexpr int BK_KEEP = MEMBERS ? BK_MKEEP : mj::BK_KEEP;

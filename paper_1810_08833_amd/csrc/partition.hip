@@ -1920,6 +1920,7 @@ int64_t partition_records(const DevStrings &d, const PartitionParams &p, int32_t
     // other position); their ranks are 32-bit
     if ((int64_t)d.n + d.total / 2 + 2 > 0xFFFFFFF0LL)
         throw Error(MJ_ECAPACITY, "more than 2^32 partitions per repetition");
+    // the counts' read-back
     if ((size_t)reps * 4 + 4 > 8192) throw Error(MJ_EINVAL, "too many repetitions");
 
     // phase 1: anchors of every repetition (Pi seeded with seed + rho), their counts

@@ -18,7 +18,8 @@
 // rank j, j + QUEUES, j + 2 QUEUES, ... in that order, each with a counter on a line of
 // its own: device-scope atomics on one address serialise across the chip, so a single
 // counter bumped at every refill would pace the whole launch.  A wave starts on the
-// sub-queue its number selects and moves to the next one when it finds its own dry.
+// sub-queue its number selects; one that it finds dry it leaves for the next that has pairs,
+// read from all counters at once.
 // The number of lanes per pair G is chosen per (band words, alphabet planes) by timing
 // the candidate configurations once per context.
 #include <string.h>
@@ -1104,8 +1105,9 @@ int64_t verify_pairs_batched(const uint64_t *pairs, int64_t n, const DevStrings 
         }
     }
     if (best_g == 0 && (left < TUNE_MIN_PAIRS || !tune)) {
-        // a small call leaves most of the chip idle: the shortest path per pair; timing the choices would cost more than the work.  Without a
-        // tuning table (latency-first callers) the same fixed choice.
+        // a small call leaves most of the chip idle: the shortest path per pair, since timing
+        // the choices would cost more than the work.  Without a tuning table (latency-first
+        // callers) the same fixed choice.
         best_g = verify_small_call_lanes(cmax);
         best_blocks = 512;
     }
@@ -1184,8 +1186,8 @@ int64_t verify_pairs_batched(const uint64_t *pairs, int64_t n, const DevStrings 
 // The batched verification with the pair count on the device (*n_dev <= cap): pairs
 // longest first, then the persistent launch in the configuration the context timed for this
 // band size (the caller makes sure one is known: `cmax` words of band from the largest K),
-// no host read.  expect: how many pairs there may be (speed only).  flags[n .. cap) are not written; the band-cell count and the window error
-// word go to cells_out[0..1] (device).
+// no host read.  expect: how many pairs there may be (speed only).  flags[n .. cap) are not
+// written; the band-cell count and the window error word go to cells_out[0..1] (device).
 void verify_pairs_batched_streamed(const uint64_t *pairs, int64_t cap, const uint32_t *n_dev,
                                    const DevStrings &A, const DevStrings &B, int kmode, int cmax,
                                    uint8_t *flags, Workspace &ws, hipStream_t s, KTimer *kt,
