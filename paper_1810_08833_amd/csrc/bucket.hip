@@ -62,8 +62,9 @@ __device__ __forceinline__ int64_t bucket_start(const uint64_t *__restrict__ key
 // number among them (16 .. 29), and whether it is a long one or has fewer than two members.
 constexpr uint32_t SLOT_LONG = 1u << 31, SLOT_LONE = 1u << 30;
 // Why a bucket does not fit (*over): its short slots' members, its long slots, the room for
-// their records, a long slot's distinct keys; the dedup's part of equal leading bits.
-enum : uint32_t { OVER_MEMBERS = 1, OVER_SLOTS, OVER_ROOM, OVER_DISTINCT, OVER_DEDUP };
+// their records, a long slot's distinct keys; the dedup's part of equal leading bits; the long
+// slots' tile pairs.
+enum : uint32_t { OVER_MEMBERS = 1, OVER_SLOTS, OVER_ROOM, OVER_DISTINCT, OVER_DEDUP, OVER_UNITS };
 
 template <bool MEMBERS>
 struct BucketShared {
@@ -106,10 +107,10 @@ struct BucketOut {
     ulonglong2 *xslot;
     int64_t xslots;
     unsigned long long *xstate;
+    uint64_t max_units;  // tile pairs of the long slots that are taken on
 };
 
-// For inputs of fewer than 2^29 symbols (32-bit filter).  EMIT false: everything but the short
-// slots' candidates (the counts that size the output).  MEMBERS: the records are those the
+// For inputs of fewer than 2^29 symbols (32-bit filter).  MEMBERS: the records are those the
 // member filter kept, so no bitmaps are needed.
 //
 // A bucket is a chain of short steps between barriers, so what bounds the kernel is how many
@@ -122,7 +123,7 @@ struct BucketOut {
 // the two more sort passes, the repair, the groups and the emission took 1.9 ms; with a wave's
 // candidates straight to the output and slots in key order 1.47 ms.  7.0 M unfiltered records
 // (0.41 M groups): 142 us, in key order 170.
-template <bool EMIT, bool MEMBERS>
+template <bool MEMBERS>
 __global__ __launch_bounds__(MEMBERS ? BK_MTHREADS : BK_THREADS) void k_bucket_pairs(BucketIn in,
                                                                                     BucketOut o) {
     using Shared = BucketShared<MEMBERS>;
@@ -204,7 +205,7 @@ __global__ __launch_bounds__(MEMBERS ? BK_MTHREADS : BK_THREADS) void k_bucket_p
             for (int u = 0; u < BK_KEEP; u++) {
                 const int64_t i = threadIdx.x + u * BK_THREADS;
                 x[u] = i < m ? in.key[lo + i] : 0;
-                if (MEMBERS && EMIT) v[u] = i < m ? in.val[lo + i] : 0;
+                if (MEMBERS) v[u] = i < m ? in.val[lo + i] : 0;
             }
         };
         if (MEMBERS) load(sh.bound[0], sh.bound[1] - sh.bound[0], nx, nv);
@@ -216,7 +217,7 @@ __global__ __launch_bounds__(MEMBERS ? BK_MTHREADS : BK_THREADS) void k_bucket_p
 #pragma unroll
                 for (int u = 0; u < BK_KEEP; u++) {
                     x[u] = nx[u];
-                    v[u] = EMIT ? nv[u] : 0;
+                    v[u] = nv[u];
                 }
                 load(sh.bound[c + 1], sh.bound[c + 2] - sh.bound[c + 1], nx, nv);
             } else if (keep) {
@@ -228,7 +229,7 @@ __global__ __launch_bounds__(MEMBERS ? BK_MTHREADS : BK_THREADS) void k_bucket_p
                 ml[u] = need ? in.len[v[u] >> 32] : 0;
                 ks[u] = need ? in.kk[v[u] >> 32] : 0;
             };
-            if (MEMBERS && EMIT)
+            if (MEMBERS)
 #pragma unroll
                 for (int u = 0; u < BK_KEEP; u++) strings(u, threadIdx.x + u * BK_THREADS < m);
             auto each = [&](auto f) {
@@ -349,12 +350,12 @@ __global__ __launch_bounds__(MEMBERS ? BK_MTHREADS : BK_THREADS) void k_bucket_p
                 const int4 rc = make_int4((int32_t)(v >> 32), ml, 2 * (int32_t)(uint32_t)v - ml, ks);
                 if (p >= 0) {
                     sh.key[p] = k;
-                    if (EMIT) sh.rec[p] = rc;
+                    sh.rec[p] = rc;
                 } else {
                     const uint32_t q = (uint32_t)(-1 - p);
                     const int64_t lp = sh.lbase[q >> 24] + (q & 0xFFFFFFu);
                     o.xkey[lp] = k;
-                    if (EMIT) o.xrec[lp] = rc;
+                    o.xrec[lp] = rc;
                 }
             };
             if (keep) {  // the loads of a thread's members in flight together
@@ -365,12 +366,9 @@ __global__ __launch_bounds__(MEMBERS ? BK_MTHREADS : BK_THREADS) void k_bucket_p
                 if (!MEMBERS) {
 #pragma unroll
                     for (int u = 0; u < BK_KEEP; u++)
-                        v[u] = EMIT && p[u] != NONE ? in.val[lo + threadIdx.x + u * BK_THREADS] : 0;
+                        v[u] = p[u] != NONE ? in.val[lo + threadIdx.x + u * BK_THREADS] : 0;
 #pragma unroll
-                    for (int u = 0; u < BK_KEEP; u++) strings(u, EMIT && p[u] != NONE);
-                } else if (!EMIT) {
-#pragma unroll
-                    for (int u = 0; u < BK_KEEP; u++) strings(u, false);
+                    for (int u = 0; u < BK_KEEP; u++) strings(u, p[u] != NONE);
                 }
 #pragma unroll
                 for (int u = 0; u < BK_KEEP; u++)
@@ -380,12 +378,11 @@ __global__ __launch_bounds__(MEMBERS ? BK_MTHREADS : BK_THREADS) void k_bucket_p
                     const uint64_t e = in.key[lo + i];
                     const int p = place(e);
                     if (p == NONE) continue;
-                    const uint64_t v = EMIT ? in.val[lo + i] : 0;
-                    put(p, e, v, EMIT ? in.len[v >> 32] : 0,
-                        EMIT ? in.kk[v >> 32] : 0);
+                    const uint64_t v = in.val[lo + i];
+                    put(p, e, v, in.len[v >> 32], in.kk[v >> 32]);
                 }
             }
-            const uint32_t before = EMIT ? sh.nstage : 0;
+            const uint32_t before = sh.nstage;
             __syncthreads();
             // Members of short slots, one a lane, each against the half of its slot that follows
             // it (cyclically): lanes of one slot have the same number of tests, and neighbouring
@@ -398,7 +395,7 @@ __global__ __launch_bounds__(MEMBERS ? BK_MTHREADS : BK_THREADS) void k_bucket_p
                     int4 u = {};
                     if (p < (int)M) {
                         kp = sh.key[p];
-                        if (EMIT) u = sh.rec[p];
+                        u = sh.rec[p];
                         const uint32_t wd = sh.slot[(uint32_t)kp & (BK_SLOTS - 1)];
                         z = (int)(wd >> 16);
                         first = (int)(wd & 0xFFFFu) - z;
@@ -424,29 +421,25 @@ __global__ __launch_bounds__(MEMBERS ? BK_MTHREADS : BK_THREADS) void k_bucket_p
                         q = q0 + 1 >= first + z ? first : q0 + 1;
                         const bool e0 = d <= nd && sh.key[q0] == kp, e1 = d < nd && sh.key[q] == kp;
                         same += (e0 ? 1u : 0u) + (e1 ? 1u : 0u);
-                        if (EMIT) {
-                            const int4 v0 = sh.rec[e0 ? q0 : 0], v1 = sh.rec[e1 ? q : 0];
-                            emit(e0 && close(v0), e1 && close(v1), u.x, v0.x, v1.x, out);
-                        }
+                        const int4 v0 = sh.rec[e0 ? q0 : 0], v1 = sh.rec[e1 ? q : 0];
+                        emit(e0 && close(v0), e1 && close(v1), u.x, v0.x, v1.x, out);
                     }
                     if (out < 0) tests += same;
                 }
             };
             pairs(-1);
-            if (EMIT) {
+            __syncthreads();
+            const uint32_t staged = sh.nstage;
+            if (staged > BK_STAGE) {  // this bucket's straight to the output, in one piece
                 __syncthreads();
-                const uint32_t staged = sh.nstage;
-                if (staged > BK_STAGE) {  // this bucket's straight to the output, in one piece
-                    __syncthreads();
-                    if (threadIdx.x == 0) {
-                        sh.sbase = atomicAdd(o.counter, (unsigned long long)(staged - before));
-                        sh.nstage = 0;
-                    }
-                    __syncthreads();
-                    pairs((int64_t)sh.sbase);
-                    __syncthreads();
-                    if (threadIdx.x == 0) sh.nstage = before;
+                if (threadIdx.x == 0) {
+                    sh.sbase = atomicAdd(o.counter, (unsigned long long)(staged - before));
+                    sh.nstage = 0;
                 }
+                __syncthreads();
+                pairs((int64_t)sh.sbase);
+                __syncthreads();
+                if (threadIdx.x == 0) sh.nstage = before;
             }
             // long slots: how often each of their (few) distinct keys occurs
             for (uint32_t l = 0; l < nl; l++) {
@@ -489,11 +482,11 @@ __global__ __launch_bounds__(MEMBERS ? BK_MTHREADS : BK_THREADS) void k_bucket_p
                 }
             }
             __syncthreads();
-            if (EMIT) flush(false);
+            flush(false);
         }
     }
     __syncthreads();
-    if (EMIT) flush(true);
+    flush(true);
     // this workgroup's sums
     for (int d = 32; d >= 1; d >>= 1) {
         tests += (uint64_t)__shfl_down((long long)tests, d, 64);
@@ -567,6 +560,10 @@ __global__ __launch_bounds__(64 * LP_WAVES) void k_long_pairs(const uint64_t *__
     const int64_t slots = min(o.xslots, (int64_t)(*o.xstate >> 40));
     if (slots == 0 || *o.over) return;
     const uint64_t units = ustart[slots];
+    if (units > o.max_units) {  // more than a pass of tests: the general path counts them first
+        if (blockIdx.x == 0 && threadIdx.x == 0) *o.over = OVER_UNITS;
+        return;
+    }
     const uint64_t waves = (uint64_t)gridDim.x * LP_WAVES, w = (uint64_t)blockIdx.x * LP_WAVES + wv;
     uint64_t u = units * w / waves;
     const uint64_t uend = units * (w + 1) / waves;
@@ -667,7 +664,7 @@ bool bucket_join_fits(int64_t records, bool members, int64_t total) {
 }
 
 BucketRecords bucket_records(uint64_t *key, uint64_t *val, int64_t cap, int64_t expect, bool members,
-                             const int64_t *n_dev, Workspace &ws, hipStream_t s) {
+                             int64_t pass, const int64_t *n_dev, Workspace &ws, hipStream_t s) {
     BucketRecords r;
     r.n = cap;
     r.n_dev = n_dev;
@@ -683,6 +680,9 @@ BucketRecords bucket_records(uint64_t *key, uint64_t *val, int64_t cap, int64_t 
     const int64_t nb = 1ll << r.bits;
     r.blocks = (int)std::min<int64_t>(nb, members ? BK_MBLOCKS : BK_BLOCKS);
     r.members = members;
+    // a tile pair of one key has 1,000 tests or more on average; slots of several keys may have
+    // fewer, up to this many tile pairs (2^20, about 5 ms, for the default pass)
+    r.max_units = (uint64_t)std::max<int64_t>(1024, pass / 256);
     // the workgroups' sums; candidates, over, the long slots' state
     r.state = reinterpret_cast<uint64_t *>(ws.zeroed(6, s));
     r.part = ws.get_n<uint64_t>(3 * r.blocks);
@@ -699,17 +699,15 @@ BucketRecords bucket_records(uint64_t *key, uint64_t *val, int64_t cap, int64_t 
 
 void bucket_reset(const BucketRecords &r, hipStream_t s) { fill_u64(r.state, 0, 3, s); }
 
-void bucket_pairs(const BucketRecords &r, const DevStrings &d, bool emit, uint64_t *out, int64_t cap,
-                  bool longs, hipStream_t s, KTimer *kt) {
+void bucket_pairs(const BucketRecords &r, const DevStrings &d, uint64_t *out, int64_t cap, bool longs,
+                  hipStream_t s, KTimer *kt) {
     const BucketIn in{r.key, r.val, r.n, r.n_dev, r.bits, d.len, d.kk};
     const BucketOut o{out, cap, r.counter, r.part, r.over, r.xkey, r.xrec, r.xcap, r.xslot, r.xslots,
-                      r.counter + 2};
+                      r.counter + 2, r.max_units};
     int th = kt ? kt->begin(KTimer::EMIT, s) : -1;
-    hipLaunchKernelGGL((r.members ? emit ? k_bucket_pairs<true, true> : k_bucket_pairs<false, true>
-                                  : emit ? k_bucket_pairs<true, false> : k_bucket_pairs<false, false>),
-                       dim3((unsigned)r.blocks), dim3(r.members ? BK_MTHREADS : BK_THREADS), 0, s, in, o);
+    hipLaunchKernelGGL((r.members ? k_bucket_pairs<true> : k_bucket_pairs<false>), dim3((unsigned)r.blocks), dim3(r.members ? BK_MTHREADS : BK_THREADS), 0, s, in, o);
     MJ_LAUNCH_CHECK();
-    if (emit && longs) {
+    if (longs) {
         hipLaunchKernelGGL(k_long_units, dim3(1), dim3(BK_THREADS), 0, s, r.xslot, r.xslots,
                            r.counter + 2, r.ustart);
         MJ_LAUNCH_CHECK();

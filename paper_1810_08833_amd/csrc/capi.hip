@@ -352,10 +352,21 @@ static mj_pairs *run_join(mj_ctx *ctx, const mj_strings *strings, const mj_param
     const uint64_t pass_tests = (uint64_t)ctx->pair_test_pass;
     // by LDS buckets where the buckets fit (their records grouped, not sorted further)
     BucketRecords br;
-    bool bucket = use_buckets(ctx, M, members, d.total), longs = false;
+    bool bucket = use_buckets(ctx, M, members, d.total), longs = false, sorted = false;
+    uint64_t *cand = nullptr;
+    int64_t c0 = 0;
+    auto emit = [&](int64_t cap, bool lng) {
+        cand = ws.get_n<uint64_t>(cap + 1);
+        bucket_pairs(br, d, cand, cap, lng, s, &ctx->kt);
+    };
     if (bucket) {
-        br = bucket_records(gkey, gval, M, M, members, nullptr, ws, s);
-        bucket_pairs(br, d, false, nullptr, 0, false, s);
+        br = bucket_records(gkey, gval, M, M, members, ctx->pair_test_pass, nullptr, ws, s);
+        tm.mark();  // 2 sort
+        sorted = true;
+        // room for a candidate a record; more of them, and the tests run again with their number
+        // (counting first cost 85 us of 1.07 ms at 7.8 M records, besides its read)
+        const int64_t cap = std::max<int64_t>(M, 65536);
+        emit(cap, true);
         std::vector<uint64_t> part(3 * br.blocks + 3);
         MJ_HIP(hipMemcpyAsync(ctx->pinned, br.part, (size_t)3 * br.blocks * 8, hipMemcpyDeviceToHost, s));
         MJ_HIP(hipMemcpyAsync(ctx->pinned + 3 * br.blocks, br.state, 24, hipMemcpyDeviceToHost, s));
@@ -365,28 +376,22 @@ static mj_pairs *run_join(mj_ctx *ctx, const mj_strings *strings, const mj_param
             g.tests += part[3 * b];
             g.groups += (int64_t)part[3 * b + 1];
         }
+        c0 = (int64_t)part[3 * br.blocks];
         longs = (part[3 * br.blocks + 2] >> 40) != 0;
         if ((uint32_t)part[3 * br.blocks + 1] || g.tests > pass_tests) {
             bucket = false;
             g = GroupInfo();
+        } else if (c0 > cap) {
+            bucket_reset(br, s);
+            emit(c0, longs);
         }
     }
     if (!bucket && M > 1) {
         sort_records(gkey, gval, M, ws, s, ctx->pinned);
     }
-    tm.mark();  // 2 sort
+    if (!sorted) tm.mark();  // 2 sort
     if (!bucket) g = find_groups(gkey, M, ws, s, ctx->pinned);
     if (bucket) {
-        const int64_t cap = (int64_t)g.tests;
-        uint64_t *cand = ws.get_n<uint64_t>(cap + 1);
-        int64_t c0 = 0;
-        auto emit = [&]() {
-            bucket_reset(br, s);
-            bucket_pairs(br, d, true, cand, cap, longs, s, &ctx->kt);
-            c0 = (int64_t)read_back<uint64_t>((const uint64_t *)br.counter, s, ctx->pinned);
-            if (c0 > cap) throw Error(MJ_ECAPACITY, "candidate buffer overflow");
-        };
-        if (cap > 0) emit();
         ctx->last_c0 = c0;
         tm.mark();  // 3 group + filter
         bool done = false;
@@ -405,7 +410,8 @@ static mj_pairs *run_join(mj_ctx *ctx, const mj_strings *strings, const mj_param
                     MJ_HIP(hipMemcpyAsync(uniq, res, (size_t)C * 8, hipMemcpyDeviceToDevice, s));
                 }
             } else {
-                emit();  // the candidates as they were
+                bucket_reset(br, s);
+                emit(c0, longs);  // the candidates as they were
             }
         }
         if (!done) C = dedup_pairs(cand, c0, d.n, d.n, ws, s, ctx->pinned, &uniq, upto != 1);
@@ -681,10 +687,11 @@ static StreamedDev launch_streamed_main(mj_ctx *ctx, DevStrings &d, const Partit
     unsigned long long *c0 = nullptr;
     const uint32_t *u = nullptr;
     if (pl.bucket) {
-        br = bucket_records(gkey, gval, pl.mcap, pl.rexp, pl.members, M_dev, ws, s);
+        br = bucket_records(gkey, gval, pl.mcap, pl.rexp, pl.members, ctx->pair_test_pass, M_dev, ws,
+                            s);
         if (tm) tm->mark();  // 2 sort
         c0 = br.counter;
-        bucket_pairs(br, d, true, cand, pl.ccap, pl.longs, s, kt);
+        bucket_pairs(br, d, cand, pl.ccap, pl.longs, s, kt);
         if (tm) tm->mark();  // 3 group + filter
         u = dedup_buckets(cand, pl.ccap, pl.cexp, c0, d.n, d.n, br.over, ws, s, &uniq);
     } else {

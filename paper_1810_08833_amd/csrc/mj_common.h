@@ -413,18 +413,19 @@ struct BucketRecords {
     int64_t xcap = 0, xslots = 0;
     ulonglong2 *xslot = nullptr;
     uint64_t *ustart = nullptr;
+    uint64_t max_units = 0;  // more tile pairs of the long slots than this: does not fit
 };
 bool bucket_join_fits(int64_t records, bool members, int64_t total);
 // expect: how many records there may be (speed, and whether the buckets fit); members: the
 // member filter kept them
+// pass: record-pair tests that a pass may have
 BucketRecords bucket_records(uint64_t *key, uint64_t *val, int64_t cap, int64_t expect, bool members,
-                             const int64_t *n_dev, Workspace &ws, hipStream_t s);
+                             int64_t pass, const int64_t *n_dev, Workspace &ws, hipStream_t s);
 void bucket_reset(const BucketRecords &r, hipStream_t s);  // before a second bucket_pairs
-// emit: the candidates to out[0 .. cap), their number (which may exceed cap) added to
-// *r.counter; else the counts alone.  longs: there may be long slots (slots << 40 is not 0
-// after a count).
-void bucket_pairs(const BucketRecords &r, const DevStrings &d, bool emit, uint64_t *out, int64_t cap,
-                  bool longs, hipStream_t s, KTimer *kt = nullptr);
+// The candidates to out[0 .. cap), their number (which may exceed cap) added to *r.counter.
+// longs: there may be long slots (if not, *r.state's slots << 40 say whether there were).
+void bucket_pairs(const BucketRecords &r, const DevStrings &d, uint64_t *out, int64_t cap, bool longs,
+                  hipStream_t s, KTimer *kt = nullptr);
 // Whether about `expect` pairs can be deduplicated by buckets.
 bool dedup_buckets_fit(int64_t expect, int32_t n_first, int32_t n_second);
 // The distinct pairs of pairs[0 .. min(cap, *count)), sorted, in *result (workspace, room for

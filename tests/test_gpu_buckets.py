@@ -112,3 +112,24 @@ def test_member_buckets_match_oracle(mj, name):
     assert np.array_equal(plain, want_c)
     for f in ("records", "groups", "pair_tests", "candidates"):
         assert sp[f] == st[f], f
+
+
+def test_more_candidates_than_records(mj):
+    """A first join with more candidates than the room its tests start with (65,536, or one a
+    record): strings of one repeated unit."""
+    say("candidates beyond the first room")
+    S = tandem(12, 420)
+    want_c, want, _ = oracle.join(S.chars, S.offsets, oracle.make_params(5, 4, k=30, t_div=2))
+    p = mj.Params(q=5, k=30, t_div=2)
+    general = mj.Context()
+    general.set_tile_emission(0)
+    _, st_g = mj.candidates(dev(mj, S), p, ctx=general)
+    ctx = mj.Context()
+    cand, st = mj.candidates(dev(mj, S), p, ctx=ctx)
+    assert np.array_equal(cand, want_c) and st["pair_tests"] == st_g["pair_tests"] > 65536
+    for limit in (1024, 1 << 20):  # tile pairs beyond a pass: the general path, in passes
+        ctx = mj.Context()
+        ctx.set_pair_test_pass(limit)
+        for _ in range(2):
+            got, _ = mj.join(dev(mj, S), p, ctx=ctx)
+            assert np.array_equal(got, want)
