@@ -19,6 +19,7 @@
 // whose buckets do not fit their LDS is seen by its counts and goes by the general path.
 #include <algorithm>
 
+#include "bucket_plan.h"
 #include "mj_common.h"
 
 namespace mj {
@@ -38,7 +39,6 @@ constexpr int BK_LONGS = 64;    // such slots of a bucket
 constexpr int BK_DISTINCT = 32; // distinct keys of such a slot
 constexpr int BK_BLOCKS = 1024; // four workgroups of 39 KB a CU
 constexpr int BK_MBLOCKS = 1536; // six of 28 KB
-constexpr int DD_CAP = 4096, DD_LOG = 13, DD_AVG = 3072, DD_PARTS = 12;
 static_assert(2 * DD_CAP == 1 << DD_LOG, "dedup table");
 
 // First index in [0, n) whose key's top bits are >= b, by the whole wave: a 64-way search.
@@ -649,16 +649,6 @@ __global__ __launch_bounds__(64 * LP_WAVES) void k_long_pairs(const uint64_t *__
     if (staged) drain();
 }
 
-static int bits_for(int64_t n, int64_t avg) {  // 2^bits buckets of about avg
-    int b = 0;
-    while (((n + avg - 1) / avg) > (1ll << b)) b++;
-    return b;
-}
-
-// Radix passes by the top bits that put the elements of a bucket together: none for one
-// bucket, one for up to 2^8, two for up to 2^16.
-static int bucket_passes(int bits) { return bits == 0 ? 0 : bits <= 8 ? 1 : 2; }
-
 bool bucket_join_fits(int64_t records, bool members, int64_t total) {
     return records >= 2 && records <= (members ? BK_MEMBERS_MAX : BK_RECORDS_MAX) && total < (1ll << 29);
 }
@@ -874,25 +864,17 @@ __global__ __launch_bounds__(256) void k_dedup_gather(const uint64_t *__restrict
     if (b + 1 == gridDim.x && threadIdx.x == 0) *u_dev = before + mine;
 }
 
-static int id_bits(int32_t count) {
-    int b = 0;
-    while (b < 32 && (1ull << b) < (uint64_t)std::max(count, 1)) b++;
-    return b;
-}
-
-constexpr int DD_BITS_MAX = 14;
-
 bool dedup_buckets_fit(int64_t expect, int32_t n_first, int32_t n_second) {
-    const int bits = expect <= DD_CAP * 3 / 4 ? 0 : bits_for(expect, DD_AVG);
-    return bits <= DD_BITS_MAX && id_bits(n_first) + id_bits(n_second) - bits <= 31;
+    return dedup_plan(expect, n_first, n_second).fits;
 }
 
 const uint32_t *dedup_buckets(uint64_t *pairs, int64_t cap, int64_t expect,
                               const unsigned long long *count, int32_t n_first, int32_t n_second,
                               uint32_t *over, Workspace &ws, hipStream_t s, uint64_t **result) {
     cap = std::max<int64_t>(cap, 1);
-    const int bs = id_bits(n_second), kb = id_bits(n_first) + bs;
-    const int bits = expect <= DD_CAP * 3 / 4 ? 0 : bits_for(expect, DD_AVG);
+    const DedupPlan plan = dedup_plan(expect, n_first, n_second);
+    const int bs = plan.bs, kb = plan.kb, bits = plan.bits;
+    if (!plan.fits) throw Error(MJ_ECAPACITY, "pairs beyond the dedup's buckets");
     uint64_t *res = ws.get_n<uint64_t>(cap + 1);
     uint32_t *u = ws.get_n<uint32_t>(2);
     *result = res;

@@ -1,0 +1,49 @@
+"""The dedup of candidates whose distinct pairs are far from evenly spread, against the oracle: few
+long strings (more candidates than there are pair keys)."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_1810_08833_amd import datagen as dg
+from tests.test_gpu_parity import dev, say
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def mj():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_1810_08833_amd as m
+    return m
+
+
+def few_long(seed, n, length):
+    """Near-copies of one string: n (n - 1) / 2 pairs, each found through thousands of records."""
+    rng = np.random.default_rng(seed)
+    x = rng.integers(0, 4, length).astype(np.uint8)
+    out = []
+    for _ in range(n):
+        y = x.copy()
+        at = rng.integers(0, length, 9)
+        y[at] = rng.integers(0, 4, 9)
+        out.append(y)
+    return dg.from_list(out, 4)
+
+
+@pytest.mark.parametrize("n,length", [(2, 60000), (3, 60000), (9, 20000)])
+def test_more_candidates_than_keys(mj, n, length):
+    say("more candidates than keys", n)
+    S = few_long(n, n, length)
+    kw = dict(t_fixed=length // 4)
+    op = oracle.make_params(6, 4, k=40, t_div=1, **kw)
+    want_c, want, _ = oracle.join(S.chars, S.offsets, op)
+    p = mj.Params(q=6, k=40, t_div=1, **kw)
+    ctx = mj.Context()
+    cand, st = mj.candidates(dev(mj, S), p, ctx=ctx)
+    assert np.array_equal(cand, want_c) and st["pair_tests"] > 12288
+    for mode in (0, 1, 1, 2, 2):
+        ctx.set_streaming(mode)
+        got, _ = mj.join(dev(mj, S), p, ctx=ctx)
+        assert np.array_equal(got, want), mode
