@@ -107,6 +107,20 @@ static bool use_buckets(const mj_ctx *ctx, int64_t records, bool members, int64_
     return ctx->tile_min != 0 && bucket_join_fits(records, members, total);
 }
 
+// The context's memo of the parameters, a new one if they are others than the last call's.
+static BucketMemo &bucket_memo(mj_ctx *ctx, const mj_strings *st, const mj_params *p) {
+    BucketMemo &m = ctx->buckets;
+    if (m.key.q != p->q || m.key.t_div != p->t_div || m.key.t_fixed != p->t_fixed ||
+        m.key.reps != p->reps || m.key.seed != p->seed || m.key.k != p->k || m.sigma != st->sigma ||
+        m.packing != st->packing) {
+        m = BucketMemo();
+        m.key = *p;
+        m.sigma = st->sigma;
+        m.packing = st->packing;
+    }
+    return m;
+}
+
 extern "C" mj_status mj_ctx_set_streaming(mj_ctx *ctx, int mode) {
     if (!ctx) return fail(MJ_EINVAL, "ctx is NULL");
     if (mode < 0 || mode > 2) return fail(MJ_EINVAL, "streaming mode must be 0, 1 or 2");
@@ -352,6 +366,7 @@ static mj_pairs *run_join(mj_ctx *ctx, const mj_strings *strings, const mj_param
     const uint64_t pass_tests = (uint64_t)ctx->pair_test_pass;
     // by LDS buckets where the buckets fit (their records grouped, not sorted further)
     BucketRecords br;
+    BucketMemo &memo = bucket_memo(ctx, strings, params);
     bool bucket = use_buckets(ctx, M, members, d.total), longs = false, sorted = false;
     uint64_t *cand = nullptr;
     int64_t c0 = 0;
@@ -395,14 +410,15 @@ static mj_pairs *run_join(mj_ctx *ctx, const mj_strings *strings, const mj_param
         ctx->last_c0 = c0;
         tm.mark();  // 3 group + filter
         bool done = false;
-        if (c0 > 0 && dedup_buckets_fit(c0, d.n, d.n)) {
+        if (c0 > 0 && dedup_buckets_fit(c0, d.n, d.n) && !memo.dedup.skip()) {
             uint64_t *res = nullptr;
-            const uint32_t *u = dedup_buckets(cand, c0, c0, br.counter, d.n, d.n, br.over, ws, s, &res);
+            const uint32_t *u = dedup_buckets(cand, c0, c0, br.counter, d.n, d.n, br.dedup_over, ws, s, &res);
             MJ_HIP(hipMemcpyAsync(ctx->pinned, u, 4, hipMemcpyDeviceToHost, s));
-            MJ_HIP(hipMemcpyAsync(ctx->pinned + 1, br.over, 4, hipMemcpyDeviceToHost, s));
+            MJ_HIP(hipMemcpyAsync(ctx->pinned + 1, br.dedup_over, 4, hipMemcpyDeviceToHost, s));
             MJ_HIP(hipStreamSynchronize(s));
             done = (uint32_t)ctx->pinned[1] == 0;
             if (done) {
+                memo.dedup.fitted();
                 C = (int64_t)(uint32_t)ctx->pinned[0];
                 uniq = res;
                 if (upto == 1) {  // the caller's
@@ -410,12 +426,12 @@ static mj_pairs *run_join(mj_ctx *ctx, const mj_strings *strings, const mj_param
                     MJ_HIP(hipMemcpyAsync(uniq, res, (size_t)C * 8, hipMemcpyDeviceToDevice, s));
                 }
             } else {
+                memo.dedup.failed();
                 bucket_reset(br, s);
                 emit(c0, longs);  // the candidates as they were
             }
         }
         if (!done) C = dedup_pairs(cand, c0, d.n, d.n, ws, s, ctx->pinned, &uniq, upto != 1);
-        bucket = done || c0 == 0;
     } else if (g.tests <= pass_tests) {
         int64_t cap = (int64_t)g.tests;
         uint64_t *cand = ws.get_n<uint64_t>(cap + 1);
@@ -499,9 +515,9 @@ static mj_pairs *run_join(mj_ctx *ctx, const mj_strings *strings, const mj_param
 // final one, no stage waits for the host.  Returns nullptr when a capacity was exceeded
 // (the caller then runs the join stage by stage, which sizes everything exactly).
 
-// What the host reads at the end of a streamed join or search: the counts, in dst[0 .. 14].
+// What the host reads at the end of a streamed join or search: the counts, in dst[0 .. 15].
 // slot: the group counts of a join by the general path; part, state: of one by LDS buckets
-// (see BucketRecords); tests, over: of a search.
+// (see BucketRecords); tests, over (of its dedup): of a search.
 struct Collect {
     const int64_t *R;
     const uint64_t *slot;
@@ -544,8 +560,9 @@ __device__ void collect(const Collect &c, uint32_t outn, uint64_t *dst) {
     dst[10] = (uint64_t)*c.M;
     dst[11] = c.slot ? c.slot[3] : 0;
     dst[12] = c.slot ? c.slot[4] : 0;
-    dst[13] = c.state ? (uint32_t)c.state[1] : c.over ? *c.over : 0;
+    dst[13] = c.state ? (uint32_t)c.state[1] : 0;
     dst[14] = c.state ? c.state[2] >> 40 : 0;
+    dst[15] = c.state ? c.state[1] >> 32 : c.over ? *c.over : 0;
 }
 
 __global__ void k_collect(Collect c, const uint32_t *outn, uint64_t *dst) { collect(c, *outn, dst); }
@@ -652,8 +669,8 @@ static bool plan_streamed(mj_ctx *ctx, const mj_params *params, const DevStrings
     pl.emit = h.emit;
     pl.rexp = std::min<int64_t>(
         pl.mcap, (int64_t)((pl.members ? h.mem_per_bound : h.rec_per_bound) * (double)pl.rcap));
-    pl.bucket = h.bucket && use_buckets(ctx, pl.mcap, pl.members, d.total) &&
-                dedup_buckets_fit(pl.cexp, d.n, d.n);
+    pl.bucket = h.bucket && use_buckets(ctx, pl.mcap, pl.members, d.total);
+    pl.dedup = pl.bucket && dedup_buckets_fit(pl.cexp, d.n, d.n) && !ctx->buckets.dedup.skip();
     pl.longs = h.longs;
     return true;
 }
@@ -693,7 +710,8 @@ static StreamedDev launch_streamed_main(mj_ctx *ctx, DevStrings &d, const Partit
         c0 = br.counter;
         bucket_pairs(br, d, cand, pl.ccap, pl.longs, s, kt);
         if (tm) tm->mark();  // 3 group + filter
-        u = dedup_buckets(cand, pl.ccap, pl.cexp, c0, d.n, d.n, br.over, ws, s, &uniq);
+        u = pl.dedup ? dedup_buckets(cand, pl.ccap, pl.cexp, c0, d.n, d.n, br.dedup_over, ws, s, &uniq)
+                     : dedup_pairs_streamed(cand, pl.ccap, c0, d.n, d.n, ws, s, &uniq);
     } else {
         sort_records(gkey, gval, pl.mcap, ws, s, ctx->pinned, M_dev);
         if (tm) tm->mark();  // 2 sort
@@ -714,7 +732,7 @@ static StreamedDev launch_streamed_main(mj_ctx *ctx, DevStrings &d, const Partit
     const Collect cl{R_dev, g.slot, c0, u, cells, d.symbol_err, M_dev, br.part, br.state, br.blocks,
                      nullptr, nullptr};
     collect_output(cl, uniq, flags, pl.ccap, pl.vexp, dv.outbuf, res, ws, s);
-    MJ_HIP(hipMemcpyAsync(ctx->pinned, res, 15 * 8, hipMemcpyDeviceToHost, s));
+    MJ_HIP(hipMemcpyAsync(ctx->pinned, res, 16 * 8, hipMemcpyDeviceToHost, s));
     return dv;
 }
 
@@ -723,7 +741,7 @@ static StreamedDev launch_streamed_main(mj_ctx *ctx, DevStrings &d, const Partit
 static mj_pairs *finish_streamed(mj_ctx *ctx, const StreamedPlan &pl, const StreamedDev &dv,
                                  const DevStrings &d, const PartitionParams &pp, hipStream_t s,
                                  mj_stats *stats) {
-    uint64_t hv[15];
+    uint64_t hv[16];
     memcpy(hv, ctx->pinned, sizeof(hv));
     const int64_t R = (int64_t)hv[0], c0h = (int64_t)hv[4], C = (int64_t)hv[5], nout = (int64_t)hv[6];
     const int64_t M = (int64_t)hv[10];
@@ -732,8 +750,12 @@ static mj_pairs *finish_streamed(mj_ctx *ctx, const StreamedPlan &pl, const Stre
     // long slots not looked for are pairs not tested
     const bool missed = pl.bucket && hv[14] && !pl.longs;
     if (pl.bucket && hv[14]) ctx->stream.longs = true;
+    if (pl.dedup && !hv[13]) {  // (a bucket that does not fit leaves candidates out)
+        if (hv[15]) ctx->buckets.dedup.failed();
+        else ctx->buckets.dedup.fitted();
+    }
     // more than the room left: stage by stage
-    if (hv[13] || missed || c0h > pl.ccap || R > pl.scap || M > pl.mcap) return nullptr;
+    if (hv[13] || hv[15] || missed || c0h > pl.ccap || R > pl.scap || M > pl.mcap) return nullptr;
     if (M > 1 && (hv[1] & 0xFFFFFFFFu) != (hv[1] >> 32)) throw Error(MJ_EDEVICE, "group boundary mismatch");
     if (hv[8]) throw Error(MJ_ECAPACITY, "a pair's band exceeds the verifier window");
     mj_pairs *out = new mj_pairs();
@@ -914,6 +936,7 @@ extern "C" mj_status mj_join(mj_ctx *ctx, const mj_strings *strings, const mj_pa
     AllocScope as(ctx->ws.alloc);
     hipStream_t s = (hipStream_t)stream;
     const bool batched = params->verifier == MJ_VERIFY_BATCHED;
+    (void)bucket_memo(ctx, strings, params);
     if (batched && ctx->streaming && !ctx->no_tuning && hints_match(ctx->stream, strings, params)) {
         mj_pairs *r = ctx->streaming == 2 ? run_join_graph(ctx, strings, params, s, stats)
                                           : run_join_streamed(ctx, strings, params, s, stats);
@@ -1179,13 +1202,13 @@ static mj_pairs *run_search_streamed(mj_ctx *ctx, const mj_index *ix, DevStrings
     const Collect cl{R_dev, nullptr, pr.counter, u, cells, qd.symbol_err, R_dev, nullptr, nullptr, 0,
                      pr.tests, over};
     collect_output(cl, uniq, flags, ccap, (int64_t)vexp, outbuf, res, ws, s);
-    MJ_HIP(hipMemcpyAsync(ctx->pinned, res, 15 * 8, hipMemcpyDeviceToHost, s));
+    MJ_HIP(hipMemcpyAsync(ctx->pinned, res, 16 * 8, hipMemcpyDeviceToHost, s));
     MJ_HIP(hipStreamSynchronize(s));
-    uint64_t hv[15];
+    uint64_t hv[16];
     memcpy(hv, ctx->pinned, sizeof(hv));
     const int64_t R = (int64_t)hv[0], c0 = (int64_t)hv[4], C = (int64_t)hv[5], nout = (int64_t)hv[6];
     if (hv[9]) throw Error(MJ_EINVAL, "a symbol code is not below sigma");
-    if (hv[13] || c0 > ccap) return nullptr;
+    if (hv[15] || c0 > ccap) return nullptr;
     if (hv[8]) throw Error(MJ_ECAPACITY, "a pair's band exceeds the verifier window");
     mj_pairs *out = new mj_pairs();
     out->alloc = t_dev_alloc;

@@ -1,9 +1,27 @@
 // Objects behind the opaque handles of the C-ABI (shared by capi.hip and server.hip).
 #pragma once
 
+#include <algorithm>
+
 #include "mj_common.h"
 
 using namespace mj;
+
+// A way that did not fit the inputs of a call is left for the next calls of the kind, four times
+// as many each time it does not fit again (inputs change, and trying costs a part of a call).
+struct Backoff {
+    int wait = 0, len = 0;
+    bool skip() { return wait > 0 && wait-- > 0; }
+    void failed() { wait = len = len ? std::min(4 * len, 4096) : 16; }
+    void fitted() { len = 0; }
+};
+
+// What the joins and candidate calls of the same parameters found about the LDS buckets.
+struct BucketMemo {
+    mj_params key{};
+    int32_t sigma = 0, packing = 0;
+    Backoff dedup;  // the dedup's buckets
+};
 
 // What a join of the batched path learned for the next join with the same parameters:
 // how many candidates (before the dedup) per record it emitted, the emission layout, and
@@ -46,7 +64,7 @@ struct StreamedPlan {
     EmitHints emit;
     // grouping, pair tests and dedup by LDS buckets; about how many records (of the member
     // filter, where it runs) and candidates
-    bool bucket = false, longs = false;
+    bool bucket = false, longs = false, dedup = false;
     int64_t rexp = 0, cexp = 0;
     int64_t vexp = 0;  // about how many distinct candidates
 };
@@ -87,6 +105,7 @@ struct mj_ctx {
     int streaming = 1;  // 0 stage by stage, 1 streamed, 2 streamed and captured (mj_ctx_set_streaming)
     StreamHints stream;
     SearchHints search;
+    BucketMemo buckets;
     JoinGraph graph;
     hipStream_t cap_stream = nullptr;  // the stream graphs are captured on
     int streamed_joins = 0, stream_fallbacks = 0;

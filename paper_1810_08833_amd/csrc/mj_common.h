@@ -402,11 +402,12 @@ struct BucketRecords {
     int blocks = 0;
     bool members = false;      // (nearly) all of them share their key
     uint64_t *part = nullptr;  // pair tests, groups and members by workgroup (3 * blocks words)
-    // 3 words, zero at first: the candidates' number, over (set when a bucket does not fit:
-    // nothing else is then worth reading) and the long slots' state (slots << 40 | records)
+    // 3 words, zero at first: the candidates' number, over (low half: set when a bucket does not
+    // fit, and nothing else is then worth reading; high half: a bucket of the dedup does not) and
+    // the long slots' state (slots << 40 | records)
     uint64_t *state = nullptr;
     unsigned long long *counter = nullptr;
-    uint32_t *over = nullptr;
+    uint32_t *over = nullptr, *dedup_over = nullptr;
     // records of the long slots, the slots, and their tile pairs' prefix
     uint64_t *xkey = nullptr;
     int4 *xrec = nullptr;

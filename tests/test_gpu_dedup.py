@@ -1,5 +1,6 @@
 """The dedup of candidates whose distinct pairs are far from evenly spread, against the oracle: few
-long strings (more candidates than there are pair keys)."""
+long strings (more candidates than there are pair keys), a cluster of neighbouring strings (all its
+pairs in a few buckets)."""
 import numpy as np
 import pytest
 
@@ -47,3 +48,36 @@ def test_more_candidates_than_keys(mj, n, length):
         ctx.set_streaming(mode)
         got, _ = mj.join(dev(mj, S), p, ctx=ctx)
         assert np.array_equal(got, want), mode
+
+
+def test_cluster_of_neighbours(mj):
+    """Most pairs are of strings 5,000 to 5,699: their dedup is left to the sort, at its speed.  (By
+    buckets each of them went over its 100,000 pairs and more 64 times.)"""
+    say("dedup of a cluster of neighbours")
+    rng = np.random.default_rng(77)
+    base = rng.integers(0, 4, 300).astype(np.uint8)
+    strs = [rng.integers(0, 4, 300).astype(np.uint8) for _ in range(20000)]
+    for i in range(5000, 5700):
+        strs[i] = base.copy()
+        at = rng.integers(0, 300, 4)
+        strs[i][at] = rng.integers(0, 4, 4)
+    S = dg.from_list(strs, 4)
+    want_c, want, _ = oracle.join(S.chars, S.offsets, oracle.make_params(5, 4, k=10, t_div=2))
+    p = mj.Params(q=5, k=10, t_div=2)
+    general = mj.Context()
+    general.set_tile_emission(0)
+    general.set_streaming(0)
+    ctx = mj.Context()
+    for _ in range(4):
+        cand, st = mj.candidates(dev(mj, S), p, ctx=ctx)
+        assert np.array_equal(cand, want_c)
+        _, sg = mj.candidates(dev(mj, S), p, ctx=general)
+    assert st["stage_ms"]["dedup"] < 4 * sg["stage_ms"]["dedup"] + 0.5
+    for mode in (0, 1, 1, 1, 2, 2):
+        ctx.set_streaming(mode)
+        got, sj = mj.join(dev(mj, S), p, ctx=ctx)
+        assert np.array_equal(got, want), mode
+    assert sj["streamed"] == 2
+    ctx.set_streaming(1)
+    _, sj = mj.join(dev(mj, S), p, ctx=ctx)
+    assert sj["streamed"] == 1 and sj["stage_ms"]["dedup"] < 4 * sg["stage_ms"]["dedup"] + 0.5
