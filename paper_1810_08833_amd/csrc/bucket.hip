@@ -26,10 +26,7 @@ namespace mj {
 
 constexpr int BK_THREADS = 512, BK_WAVES = BK_THREADS / 64;
 constexpr int BK_MTHREADS = 256;  // of a workgroup where all records are members
-constexpr int BK_AVG = 1024;    // records of a bucket aimed at (keys are hashes)
-constexpr int BK_AVG_MEMBERS = 384;  // where (nearly) all of them are members: half of BK_CAP
 constexpr int BK_KEEP = 4, BK_MKEEP = 2;  // of a bucket's records each thread keeps in registers
-constexpr int BK_CAP = 768;     // members of a bucket in short slots
 constexpr int BK_SUB = 15;      // key bits of a bucket's bitmaps; log2 BK_SLOTS of them number the slot
 constexpr int BK_SLOTS = 2048, BK_MSLOTS = 1024;
 constexpr int BK_STAGE = 512;  // candidates staged before they take room in the output
@@ -61,11 +58,6 @@ __device__ __forceinline__ int64_t bucket_start(const uint64_t *__restrict__ key
 // A slot's word: the place of its next member (bits 0 .. 15), its size or, of a long slot, its
 // number among them (16 .. 29), and whether it is a long one or has fewer than two members.
 constexpr uint32_t SLOT_LONG = 1u << 31, SLOT_LONE = 1u << 30;
-// Why a bucket does not fit (*over): its short slots' members, its long slots, the room for
-// their records, a long slot's distinct keys; the dedup's part of equal leading bits; the long
-// slots' tile pairs.
-enum : uint32_t { OVER_MEMBERS = 1, OVER_SLOTS, OVER_ROOM, OVER_DISTINCT, OVER_DEDUP, OVER_UNITS };
-
 template <bool MEMBERS>
 struct BucketShared {
     static constexpr int THREADS = MEMBERS ? BK_MTHREADS : BK_THREADS, WAVES = THREADS / 64;
@@ -654,11 +646,12 @@ bool bucket_join_fits(int64_t records, bool members, int64_t total) {
 }
 
 BucketRecords bucket_records(uint64_t *key, uint64_t *val, int64_t cap, int64_t expect, bool members,
-                             int64_t pass, const int64_t *n_dev, Workspace &ws, hipStream_t s) {
+                             bool fine, int64_t pass, const int64_t *n_dev, Workspace &ws,
+                             hipStream_t s) {
     BucketRecords r;
     r.n = cap;
     r.n_dev = n_dev;
-    r.bits = std::min(16, bits_for(std::max<int64_t>(expect, 1), members ? BK_AVG_MEMBERS : BK_AVG));
+    r.bits = record_bits(expect, members || fine);
     r.key = key;
     r.val = val;
     for (int p = bucket_passes(r.bits); p > 0; p--) {

@@ -1,5 +1,5 @@
-// How many LDS buckets a dedup takes, and whether it can: host arithmetic without a device, so
-// that a test can walk all of it.
+// How many LDS buckets the records and the dedup take, and whether they can: host arithmetic
+// without a device, so that a test can walk all of it.
 #pragma once
 
 #include <stdint.h>
@@ -7,6 +7,11 @@
 #include <algorithm>
 
 namespace mj {
+
+constexpr int BK_AVG = 1024;    // records of a bucket aimed at (keys are hashes)
+constexpr int BK_AVG_MEMBERS = 384;  // where (nearly) all of them are members: half of BK_CAP
+constexpr int BK_CAP = 768;     // members of a bucket in short slots
+constexpr int BK_BITS_MAX = 16; // bucket bits (two radix passes)
 
 constexpr int DD_CAP = 4096, DD_LOG = 13, DD_AVG = 3072, DD_PARTS = 12;
 constexpr int DD_BITS_MAX = 14;  // bucket bits
@@ -17,6 +22,21 @@ inline int bits_for(int64_t n, int64_t avg) {  // 2^bits buckets of about avg
     int b = 0;
     while (((n + avg - 1) / avg) > (1ll << b)) b++;
     return b;
+}
+
+// Bucket bits of `expect` records; small: of buckets of BK_AVG_MEMBERS.
+inline int record_bits(int64_t expect, bool small) {
+    return std::min(BK_BITS_MAX, bits_for(std::max<int64_t>(expect, 1), small ? BK_AVG_MEMBERS : BK_AVG));
+}
+
+// Whether records of which this many share their key want the small buckets (now: have them).  A
+// bucket of 512 to 1,024 records holds about members / 2^bits members, and what its LDS holds (768)
+// has to be some deviations more, since the members come in groups (of ten: a deviation is 3
+// sqrt(members)): 485 K records, all members, in buckets of 947 took the general path after the
+// buckets' (candidates 0.85 ms, 0.77 without trying them), in smaller buckets 0.68.  The lower limit
+// keeps the choice from swinging.
+inline bool small_buckets_pay(int64_t records, int64_t members, bool now) {
+    return members >> record_bits(records, false) > (now ? 300 : 560);
 }
 
 // Radix passes by the top bits that put the elements of a bucket together: none for one

@@ -5,6 +5,7 @@
 #include <algorithm>
 #include <string>
 
+#include "bucket_plan.h"
 #include "capi_internal.h"
 
 using namespace mj;
@@ -367,7 +368,7 @@ static mj_pairs *run_join(mj_ctx *ctx, const mj_strings *strings, const mj_param
     // by LDS buckets where the buckets fit (their records grouped, not sorted further)
     BucketRecords br;
     BucketMemo &memo = bucket_memo(ctx, strings, params);
-    bool bucket = use_buckets(ctx, M, members, d.total), longs = false, sorted = false;
+    bool bucket = use_buckets(ctx, M, members, d.total) && !memo.group.skip(), longs = true, sorted = false;
     uint64_t *cand = nullptr;
     int64_t c0 = 0;
     auto emit = [&](int64_t cap, bool lng) {
@@ -375,30 +376,48 @@ static mj_pairs *run_join(mj_ctx *ctx, const mj_strings *strings, const mj_param
         bucket_pairs(br, d, cand, cap, lng, s, &ctx->kt);
     };
     if (bucket) {
-        br = bucket_records(gkey, gval, M, M, members, ctx->pair_test_pass, nullptr, ws, s);
-        tm.mark();  // 2 sort
-        sorted = true;
         // room for a candidate a record; more of them, and the tests run again with their number
         // (counting first cost 85 us of 1.07 ms at 7.8 M records, besides its read)
         const int64_t cap = std::max<int64_t>(M, 65536);
-        emit(cap, true);
-        std::vector<uint64_t> part(3 * br.blocks + 3);
-        MJ_HIP(hipMemcpyAsync(ctx->pinned, br.part, (size_t)3 * br.blocks * 8, hipMemcpyDeviceToHost, s));
-        MJ_HIP(hipMemcpyAsync(ctx->pinned + 3 * br.blocks, br.state, 24, hipMemcpyDeviceToHost, s));
-        MJ_HIP(hipStreamSynchronize(s));
-        memcpy(part.data(), ctx->pinned, part.size() * 8);
-        for (int b = 0; b < br.blocks; b++) {
-            g.tests += part[3 * b];
-            g.groups += (int64_t)part[3 * b + 1];
-        }
-        c0 = (int64_t)part[3 * br.blocks];
-        longs = (part[3 * br.blocks + 2] >> 40) != 0;
-        if ((uint32_t)part[3 * br.blocks + 1] || g.tests > pass_tests) {
-            bucket = false;
+        int64_t shared = 0;  // records that may share their key
+        uint32_t over = 0;
+        for (bool fine = memo.fine && !members;; fine = true) {
+            br = bucket_records(gkey, gval, M, M, members, fine, ctx->pair_test_pass, nullptr, ws, s);
+            if (!sorted) tm.mark();  // 2 sort
+            sorted = true;
+            emit(cap, true);
+            std::vector<uint64_t> part(3 * br.blocks + 3);
+            MJ_HIP(hipMemcpyAsync(ctx->pinned, br.part, (size_t)3 * br.blocks * 8, hipMemcpyDeviceToHost, s));
+            MJ_HIP(hipMemcpyAsync(ctx->pinned + 3 * br.blocks, br.state, 24, hipMemcpyDeviceToHost, s));
+            MJ_HIP(hipStreamSynchronize(s));
+            memcpy(part.data(), ctx->pinned, part.size() * 8);
             g = GroupInfo();
-        } else if (c0 > cap) {
-            bucket_reset(br, s);
-            emit(c0, longs);
+            shared = 0;
+            for (int b = 0; b < br.blocks; b++) {
+                g.tests += part[3 * b];
+                g.groups += (int64_t)part[3 * b + 1];
+                shared += (int64_t)part[3 * b + 2];
+            }
+            c0 = (int64_t)part[3 * br.blocks];
+            longs = (part[3 * br.blocks + 2] >> 40) != 0;
+            over = (uint32_t)part[3 * br.blocks + 1];
+            // too many members in a bucket: smaller buckets, where there are any
+            if (over != OVER_MEMBERS || members || record_bits(M, true) <= br.bits) {
+                memo.fine = !over && !members && small_buckets_pay(M, shared, fine);
+                break;
+            }
+        }
+        if (over || g.tests > pass_tests) {
+            bucket = false;
+            longs = true;
+            g = GroupInfo();
+            memo.group.failed();
+        } else {
+            memo.group.fitted();
+            if (c0 > cap) {
+                bucket_reset(br, s);
+                emit(c0, longs);
+            }
         }
     }
     if (!bucket && M > 1) {
@@ -469,7 +488,6 @@ static mj_pairs *run_join(mj_ctx *ctx, const mj_strings *strings, const mj_param
     }
     ctx->last_R = R;
     ctx->last_M = M;
-    ctx->last_bucket = bucket;
     ctx->last_longs = longs;
     ctx->last_small_tests = g.small_tests;
     ctx->last_units = g.units;
@@ -515,9 +533,10 @@ static mj_pairs *run_join(mj_ctx *ctx, const mj_strings *strings, const mj_param
 // final one, no stage waits for the host.  Returns nullptr when a capacity was exceeded
 // (the caller then runs the join stage by stage, which sizes everything exactly).
 
-// What the host reads at the end of a streamed join or search: the counts, in dst[0 .. 15].
+// What the host reads at the end of a streamed join or search: the counts, in dst[0 .. RES_WORDS).
 // slot: the group counts of a join by the general path; part, state: of one by LDS buckets
 // (see BucketRecords); tests, over (of its dedup): of a search.
+constexpr int RES_WORDS = 17;
 struct Collect {
     const int64_t *R;
     const uint64_t *slot;
@@ -535,15 +554,17 @@ struct Collect {
 // by one wave
 __device__ void collect(const Collect &c, uint32_t outn, uint64_t *dst) {
     const int lane = threadIdx.x & 63;
-    uint64_t tests = 0, groups = 0;
+    uint64_t tests = 0, groups = 0, shared = 0;
     if (c.part) {
         for (int b = lane; b < c.blocks; b += 64) {
             tests += c.part[3 * b];
             groups += c.part[3 * b + 1];
+            shared += c.part[3 * b + 2];
         }
         for (int d = 32; d >= 1; d >>= 1) {
             tests += (uint64_t)__shfl_down((long long)tests, d, 64);
             groups += (uint64_t)__shfl_down((long long)groups, d, 64);
+            shared += (uint64_t)__shfl_down((long long)shared, d, 64);
         }
     }
     if (lane != 0) return;
@@ -562,6 +583,7 @@ __device__ void collect(const Collect &c, uint32_t outn, uint64_t *dst) {
     dst[12] = c.slot ? c.slot[4] : 0;
     dst[13] = c.state ? (uint32_t)c.state[1] : 0;
     dst[14] = c.state ? c.state[2] >> 40 : 0;
+    dst[16] = shared;
     dst[15] = c.state ? c.state[1] >> 32 : c.over ? *c.over : 0;
 }
 
@@ -669,7 +691,8 @@ static bool plan_streamed(mj_ctx *ctx, const mj_params *params, const DevStrings
     pl.emit = h.emit;
     pl.rexp = std::min<int64_t>(
         pl.mcap, (int64_t)((pl.members ? h.mem_per_bound : h.rec_per_bound) * (double)pl.rcap));
-    pl.bucket = h.bucket && use_buckets(ctx, pl.mcap, pl.members, d.total);
+    pl.bucket = use_buckets(ctx, pl.mcap, pl.members, d.total) && !ctx->buckets.group.skip();
+    pl.fine = ctx->buckets.fine && !pl.members;
     pl.dedup = pl.bucket && dedup_buckets_fit(pl.cexp, d.n, d.n) && !ctx->buckets.dedup.skip();
     pl.longs = h.longs;
     return true;
@@ -704,8 +727,8 @@ static StreamedDev launch_streamed_main(mj_ctx *ctx, DevStrings &d, const Partit
     unsigned long long *c0 = nullptr;
     const uint32_t *u = nullptr;
     if (pl.bucket) {
-        br = bucket_records(gkey, gval, pl.mcap, pl.rexp, pl.members, ctx->pair_test_pass, M_dev, ws,
-                            s);
+        br = bucket_records(gkey, gval, pl.mcap, pl.rexp, pl.members, pl.fine, ctx->pair_test_pass,
+                            M_dev, ws, s);
         if (tm) tm->mark();  // 2 sort
         c0 = br.counter;
         bucket_pairs(br, d, cand, pl.ccap, pl.longs, s, kt);
@@ -728,11 +751,11 @@ static StreamedDev launch_streamed_main(mj_ctx *ctx, DevStrings &d, const Partit
                                   params->verify_lanes, ctx->stream.candidates, &cells);
     if (tm) tm->mark();  // 5 verify
     dv.outbuf = ws.get_n<uint64_t>(pl.ccap + 1);
-    uint64_t *res = ws.get_n<uint64_t>(16);
+    uint64_t *res = ws.get_n<uint64_t>(RES_WORDS);
     const Collect cl{R_dev, g.slot, c0, u, cells, d.symbol_err, M_dev, br.part, br.state, br.blocks,
                      nullptr, nullptr};
     collect_output(cl, uniq, flags, pl.ccap, pl.vexp, dv.outbuf, res, ws, s);
-    MJ_HIP(hipMemcpyAsync(ctx->pinned, res, 16 * 8, hipMemcpyDeviceToHost, s));
+    MJ_HIP(hipMemcpyAsync(ctx->pinned, res, RES_WORDS * 8, hipMemcpyDeviceToHost, s));
     return dv;
 }
 
@@ -741,18 +764,27 @@ static StreamedDev launch_streamed_main(mj_ctx *ctx, DevStrings &d, const Partit
 static mj_pairs *finish_streamed(mj_ctx *ctx, const StreamedPlan &pl, const StreamedDev &dv,
                                  const DevStrings &d, const PartitionParams &pp, hipStream_t s,
                                  mj_stats *stats) {
-    uint64_t hv[16];
+    uint64_t hv[RES_WORDS];
     memcpy(hv, ctx->pinned, sizeof(hv));
     const int64_t R = (int64_t)hv[0], c0h = (int64_t)hv[4], C = (int64_t)hv[5], nout = (int64_t)hv[6];
     const int64_t M = (int64_t)hv[10];
     if (hv[9]) throw Error(MJ_EINVAL, "a symbol code is not below sigma");
-    if (hv[13]) ctx->stream.bucket = false;  // a bucket that does not fit: the general path
+    BucketMemo &memo = ctx->buckets;
+    if (pl.bucket && hv[13] == OVER_MEMBERS && !pl.members && !pl.fine) {
+        memo.fine = true;  // stage by stage, in smaller buckets
+    } else if (pl.bucket && hv[13]) {
+        memo.group.failed();  // the general path
+        memo.fine = false;
+    } else if (pl.bucket) {
+        memo.group.fitted();
+        memo.fine = !pl.members && small_buckets_pay(R, (int64_t)hv[16], pl.fine);
+    }
     // long slots not looked for are pairs not tested
     const bool missed = pl.bucket && hv[14] && !pl.longs;
     if (pl.bucket && hv[14]) ctx->stream.longs = true;
     if (pl.dedup && !hv[13]) {  // (a bucket that does not fit leaves candidates out)
-        if (hv[15]) ctx->buckets.dedup.failed();
-        else ctx->buckets.dedup.fitted();
+        if (hv[15]) memo.dedup.failed();
+        else memo.dedup.fitted();
     }
     // more than the room left: stage by stage
     if (hv[13] || hv[15] || missed || c0h > pl.ccap || R > pl.scap || M > pl.mcap) return nullptr;
@@ -958,7 +990,6 @@ extern "C" mj_status mj_join(mj_ctx *ctx, const mj_strings *strings, const mj_pa
         h.verify_lanes = params->verify_lanes;
         h.cand_per_record = std::max(had, (double)ctx->last_c0 / (double)std::max<int64_t>(ctx->last_rcap, 1));
         h.longs = (had > 0.0 && h.longs) || ctx->last_longs;
-        h.bucket = ctx->last_bucket;
         h.rec_per_bound = (double)ctx->last_R / (double)std::max<int64_t>(ctx->last_rcap, 1);
         h.mem_per_bound = (double)ctx->last_M / (double)std::max<int64_t>(ctx->last_rcap, 1);
         h.emit = emit_hints((uint64_t)stats->pair_tests, ctx->last_small_tests, ctx->last_units,
@@ -1198,13 +1229,13 @@ static mj_pairs *run_search_streamed(mj_ctx *ctx, const mj_index *ix, DevStrings
                                   qparams->verify_lanes, (int64_t)vexp, &cells);
     tm.mark();  // 5 verify
     uint64_t *outbuf = ws.get_n<uint64_t>(ccap + 1);
-    uint64_t *res = ws.get_n<uint64_t>(16);
+    uint64_t *res = ws.get_n<uint64_t>(RES_WORDS);
     const Collect cl{R_dev, nullptr, pr.counter, u, cells, qd.symbol_err, R_dev, nullptr, nullptr, 0,
                      pr.tests, over};
     collect_output(cl, uniq, flags, ccap, (int64_t)vexp, outbuf, res, ws, s);
-    MJ_HIP(hipMemcpyAsync(ctx->pinned, res, 16 * 8, hipMemcpyDeviceToHost, s));
+    MJ_HIP(hipMemcpyAsync(ctx->pinned, res, RES_WORDS * 8, hipMemcpyDeviceToHost, s));
     MJ_HIP(hipStreamSynchronize(s));
-    uint64_t hv[16];
+    uint64_t hv[RES_WORDS];
     memcpy(hv, ctx->pinned, sizeof(hv));
     const int64_t R = (int64_t)hv[0], c0 = (int64_t)hv[4], C = (int64_t)hv[5], nout = (int64_t)hv[6];
     if (hv[9]) throw Error(MJ_EINVAL, "a symbol code is not below sigma");

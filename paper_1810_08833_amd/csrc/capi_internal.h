@@ -20,7 +20,8 @@ struct Backoff {
 struct BucketMemo {
     mj_params key{};
     int32_t sigma = 0, packing = 0;
-    Backoff dedup;  // the dedup's buckets
+    Backoff group, dedup;  // the records' buckets, the dedup's
+    bool fine = false;     // smaller buckets of records: most of them share their key
 };
 
 // What a join of the batched path learned for the next join with the same parameters:
@@ -39,8 +40,7 @@ struct StreamHints {
     EmitHints emit;
     int verify_g = 0, verify_blocks = 0;
     int64_t candidates = 0;      // distinct candidates
-    bool bucket = false;         // grouped by LDS buckets, which all fitted
-    bool longs = false;          // some of whose slots were long
+    bool longs = true;           // LDS buckets may have long slots (not known yet, or seen)
 };
 
 // The same for searches: rates per record bound of the last search of the context, for an
@@ -64,7 +64,7 @@ struct StreamedPlan {
     EmitHints emit;
     // grouping, pair tests and dedup by LDS buckets; about how many records (of the member
     // filter, where it runs) and candidates
-    bool bucket = false, longs = false, dedup = false;
+    bool bucket = false, longs = false, dedup = false, fine = false;
     int64_t rexp = 0, cexp = 0;
     int64_t vexp = 0;  // about how many distinct candidates
 };
@@ -113,7 +113,7 @@ struct mj_ctx {
     // pair tests of the small groups and tile pairs of the large ones
     int64_t last_c0 = 0, last_R = 0, last_rcap = 0, last_M = 0;
     uint64_t last_small_tests = 0, last_units = 0;
-    bool last_bucket = false, last_longs = false;
+    bool last_longs = true;  // as StreamHints::longs
 };
 
 struct mj_pairs {

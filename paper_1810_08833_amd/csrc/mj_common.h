@@ -416,12 +416,17 @@ struct BucketRecords {
     uint64_t *ustart = nullptr;
     uint64_t max_units = 0;  // more tile pairs of the long slots than this: does not fit
 };
+// Why a bucket does not fit (*over): its short slots' members, its long slots, the room for
+// their records, a long slot's distinct keys; the dedup's part of equal leading bits; the long
+// slots' tile pairs.
+enum : uint32_t { OVER_MEMBERS = 1, OVER_SLOTS, OVER_ROOM, OVER_DISTINCT, OVER_DEDUP, OVER_UNITS };
 bool bucket_join_fits(int64_t records, bool members, int64_t total);
 // expect: how many records there may be (speed, and whether the buckets fit); members: the
-// member filter kept them
-// pass: record-pair tests that a pass may have
+// member filter kept them; fine: buckets as small as theirs, most records being members all the
+// same; pass: record-pair tests that a pass may have
 BucketRecords bucket_records(uint64_t *key, uint64_t *val, int64_t cap, int64_t expect, bool members,
-                             int64_t pass, const int64_t *n_dev, Workspace &ws, hipStream_t s);
+                             bool fine, int64_t pass, const int64_t *n_dev, Workspace &ws,
+                             hipStream_t s);
 void bucket_reset(const BucketRecords &r, hipStream_t s);  // before a second bucket_pairs
 // The candidates to out[0 .. cap), their number (which may exceed cap) added to *r.counter.
 // longs: there may be long slots (if not, *r.state's slots << 40 say whether there were).
