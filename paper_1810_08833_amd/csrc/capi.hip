@@ -656,7 +656,6 @@ static bool plan_streamed(mj_ctx *ctx, const mj_params *params, const DevStrings
                           const PartitionParams &pp, const SetupInfo &si, StreamedPlan &pl) {
     const StreamHints &h = ctx->stream;
     pl.si = si;
-    pl.vexp = h.candidates;
     pl.cmax = (int)((std::min<int64_t>(params->k >= 0 ? params->k : si.kmax, 0x3FFFFFFF) + 31) >> 5);
     if (pl.cmax > persist_max_c()) return false;
     const int np = verify_planes(d.bits);
@@ -672,6 +671,7 @@ static bool plan_streamed(mj_ctx *ctx, const mj_params *params, const DevStrings
     if (!ctx->tune.best_blocks[ci][np / 2 - 1])
         ctx->tune.best_blocks[ci][np / 2 - 1] = h.verify_blocks ? h.verify_blocks : 512;
     pl.rcap = std::max<int64_t>(si.rec_bound * pp.reps, 2);
+    pl.vexp = (int64_t)(h.verified_per_record * (double)pl.rcap);
     // the stages after the partition are sized by the last join's records per bound, with
     // room (more records than that: the join runs again stage by stage)
     pl.scap = std::max<int64_t>(
@@ -748,7 +748,7 @@ static StreamedDev launch_streamed_main(mj_ctx *ctx, DevStrings &d, const Partit
     uint8_t *flags = ws.get_n<uint8_t>(pl.ccap + 4);
     unsigned long long *cells = nullptr;
     verify_pairs_batched_streamed(uniq, pl.ccap, u, d, d, 0, pl.cmax, flags, ws, s, kt, ctx->tune,
-                                  params->verify_lanes, ctx->stream.candidates, &cells);
+                                  params->verify_lanes, pl.vexp, &cells);
     if (tm) tm->mark();  // 5 verify
     dv.outbuf = ws.get_n<uint64_t>(pl.ccap + 1);
     uint64_t *res = ws.get_n<uint64_t>(RES_WORDS);
@@ -821,7 +821,7 @@ static mj_pairs *finish_streamed(mj_ctx *ctx, const StreamedPlan &pl, const Stre
                                            0.99 * ctx->stream.cand_per_record);
     ctx->stream.rec_per_bound = (double)R / (double)pl.rcap;
     ctx->stream.mem_per_bound = (double)M / (double)pl.rcap;
-    ctx->stream.candidates = C;
+    ctx->stream.verified_per_record = (double)C / (double)pl.rcap;
     ctx->stream.emit = emit_hints((uint64_t)hv[3], (uint64_t)hv[11], (uint64_t)hv[12], M, d.n,
                                   ctx->tile_min);
     return out;
@@ -996,7 +996,7 @@ extern "C" mj_status mj_join(mj_ctx *ctx, const mj_strings *strings, const mj_pa
                             stats->members, strings->n, ctx->tile_min);
         h.verify_g = ctx->tune.last_g;
         h.verify_blocks = ctx->tune.last_blocks;
-        h.candidates = stats->candidates;
+        h.verified_per_record = (double)stats->candidates / (double)std::max<int64_t>(ctx->last_rcap, 1);
     }
     return MJ_OK;
     MJ_API_END

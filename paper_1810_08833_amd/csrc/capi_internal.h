@@ -39,7 +39,7 @@ struct StreamHints {
     double mem_per_bound = 1;    // records kept by the member filter per record bound
     EmitHints emit;
     int verify_g = 0, verify_blocks = 0;
-    int64_t candidates = 0;      // distinct candidates
+    double verified_per_record = 0;  // distinct candidates per record bound
     bool longs = true;           // LDS buckets may have long slots (not known yet, or seen)
 };
 
