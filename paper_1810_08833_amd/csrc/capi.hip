@@ -536,7 +536,7 @@ static mj_pairs *run_join(mj_ctx *ctx, const mj_strings *strings, const mj_param
 // What the host reads at the end of a streamed join or search: the counts, in dst[0 .. RES_WORDS).
 // slot: the group counts of a join by the general path; part, state: of one by LDS buckets
 // (see BucketRecords); tests, over (of its dedup): of a search.
-constexpr int RES_WORDS = 17;
+constexpr int RES_WORDS = 18;
 struct Collect {
     const int64_t *R;
     const uint64_t *slot;
@@ -549,6 +549,7 @@ struct Collect {
     int blocks;
     const uint64_t *tests;
     const uint32_t *over;
+    const uint32_t *left;  // pairs verified after the block filter
 };
 
 // by one wave
@@ -584,6 +585,7 @@ __device__ void collect(const Collect &c, uint32_t outn, uint64_t *dst) {
     dst[13] = c.state ? (uint32_t)c.state[1] : 0;
     dst[14] = c.state ? c.state[2] >> 40 : 0;
     dst[16] = shared;
+    dst[17] = c.left ? *c.left : 0;
     dst[15] = c.state ? c.state[1] >> 32 : c.over ? *c.over : 0;
 }
 
@@ -753,7 +755,7 @@ static StreamedDev launch_streamed_main(mj_ctx *ctx, DevStrings &d, const Partit
     dv.outbuf = ws.get_n<uint64_t>(pl.ccap + 1);
     uint64_t *res = ws.get_n<uint64_t>(RES_WORDS);
     const Collect cl{R_dev, g.slot, c0, u, cells, d.symbol_err, M_dev, br.part, br.state, br.blocks,
-                     nullptr, nullptr};
+                     nullptr, nullptr, nullptr};
     collect_output(cl, uniq, flags, pl.ccap, pl.vexp, dv.outbuf, res, ws, s);
     MJ_HIP(hipMemcpyAsync(ctx->pinned, res, RES_WORDS * 8, hipMemcpyDeviceToHost, s));
     return dv;
@@ -1199,6 +1201,12 @@ static mj_pairs *run_search_streamed(mj_ctx *ctx, const mj_index *ix, DevStrings
     const int64_t ccap = (int64_t)room;
     VerifyTuning tune;  // (the context's own table is for calls that time their choices)
     const int ci = std::min(cmax, 63), npi = ix->np / 2 - 1;
+    // enough pairs to time the verifier's choices on, none timed yet: stage by stage, which does.
+    // (4,000 queries of an index of 40,000 strings, 24 K candidates of 25 or 37 letters: verified in
+    // 0.31 ms by the choice for small calls, 0.26 by the one timed.)
+    if (!qparams->verify_lanes && !ctx->no_tuning && !ctx->tune.best_g[ci][npi] &&
+        verify_tunes((int64_t)(h.left_per_record * (double)rcap)))
+        return nullptr;
     const int g = qparams->verify_lanes == -2 ? VERIFY_BIDIR
                 : qparams->verify_lanes == -3 ? VERIFY_CLASSES
                 : qparams->verify_lanes ? qparams->verify_lanes
@@ -1225,13 +1233,14 @@ static mj_pairs *run_search_streamed(mj_ctx *ctx, const mj_index *ix, DevStrings
     tm.mark();  // 4 dedup
     uint8_t *flags = ws.get_n<uint8_t>(ccap + 4);
     unsigned long long *cells = nullptr;
+    const uint32_t *left = nullptr;
     verify_pairs_batched_streamed(uniq, ccap, u, qd, id, 1, cmax, flags, ws, s, &ctx->kt, tune,
-                                  qparams->verify_lanes, (int64_t)vexp, &cells);
+                                  qparams->verify_lanes, (int64_t)vexp, &cells, &left);
     tm.mark();  // 5 verify
     uint64_t *outbuf = ws.get_n<uint64_t>(ccap + 1);
     uint64_t *res = ws.get_n<uint64_t>(RES_WORDS);
     const Collect cl{R_dev, nullptr, pr.counter, u, cells, qd.symbol_err, R_dev, nullptr, nullptr, 0,
-                     pr.tests, over};
+                     pr.tests, over, left};
     collect_output(cl, uniq, flags, ccap, (int64_t)vexp, outbuf, res, ws, s);
     MJ_HIP(hipMemcpyAsync(ctx->pinned, res, RES_WORDS * 8, hipMemcpyDeviceToHost, s));
     MJ_HIP(hipStreamSynchronize(s));
@@ -1269,6 +1278,7 @@ static mj_pairs *run_search_streamed(mj_ctx *ctx, const mj_index *ix, DevStrings
     h.cand_per_record = std::max((double)c0 / (double)rcap, 0.99 * h.cand_per_record);
     h.tests_per_record = (double)hv[3] / (double)rcap;
     h.verified_per_record = (double)C / (double)rcap;
+    h.left_per_record = (double)hv[17] / (double)rcap;
     return out;
 }
 
@@ -1364,6 +1374,7 @@ extern "C" mj_status mj_search(mj_ctx *ctx, const mj_index *ix, const mj_strings
         h.cand_per_record = std::max((double)c0 / bound, same ? 0.99 * h.cand_per_record : 0.0);
         h.tests_per_record = (double)tests / bound;
         h.verified_per_record = (double)C / bound;
+        h.left_per_record = C ? (double)ctx->tune.last_left / bound : 0.0;
         h.valid = true;
         h.n = ix->n;
         h.records = ix->rec.count;

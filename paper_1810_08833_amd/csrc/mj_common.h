@@ -463,7 +463,11 @@ struct VerifyTuning {
     int best_g[64][4] = {};
     int best_blocks[64][4] = {};
     int last_g = 0, last_nwl = 0, last_blocks = 0;
+    int64_t last_left = 0;  // pairs of the last call, or (known where it had no choice timed yet)
+                            // those the block filter left
 };
+// Whether a call with so many pairs to verify times the choices where none is known.
+bool verify_tunes(int64_t pairs);
 // uniform_k >= 0 promises that every pair's K equals it and that all ids are valid (pairs
 // produced by the library): the pass that finds the largest K is skipped.  With
 // cells_defer set (two words of pinned host memory) the band-cell count and an error word
@@ -484,6 +488,6 @@ void verify_pairs_batched_streamed(const uint64_t *pairs, int64_t cap, const uin
                                    const DevStrings &A, const DevStrings &B, int kmode, int cmax,
                                    uint8_t *flags, Workspace &ws, hipStream_t s, KTimer *kt,
                                    const VerifyTuning &tune, int force_lanes, int64_t expect,
-                                   unsigned long long **cells_out);
+                                   unsigned long long **cells_out, const uint32_t **left_out = nullptr);
 
 }  // namespace mj

@@ -791,6 +791,7 @@ int ring_words_per_lane(int cmax) { return nwl_for(cmax + 1, RING); }
 
 // Calls with fewer pairs use a fixed configuration instead of timing the choices.
 constexpr int64_t TUNE_MIN_PAIRS = 4096;
+bool verify_tunes(int64_t pairs) { return pairs >= TUNE_MIN_PAIRS; }
 
 // ---------------------------------------------------------------- longest-first order
 constexpr int LPT_BINS = 4096;
@@ -1168,6 +1169,7 @@ int64_t verify_pairs_batched(const uint64_t *pairs, int64_t n, const DevStrings 
         tune->last_g = best_g;
         tune->last_nwl = nwl_for(nw, best_g);
         tune->last_blocks = best_blocks;
+        tune->last_left = left;
     }
     if (cells_defer) {
         // the caller reads both words after its next synchronisation of the stream:
@@ -1187,12 +1189,13 @@ int64_t verify_pairs_batched(const uint64_t *pairs, int64_t n, const DevStrings 
 // longest first, then the persistent launch in the configuration the context timed for this
 // band size (the caller makes sure one is known: `cmax` words of band from the largest K),
 // no host read.  expect: how many pairs there may be (speed only).  flags[n .. cap) are not
-// written; the band-cell count and the window error word go to cells_out[0..1] (device).
+// written; the band-cell count and the window error word go to cells_out[0..1] (device), the
+// number of pairs the block filter left to *left_out (device).
 void verify_pairs_batched_streamed(const uint64_t *pairs, int64_t cap, const uint32_t *n_dev,
                                    const DevStrings &A, const DevStrings &B, int kmode, int cmax,
                                    uint8_t *flags, Workspace &ws, hipStream_t s, KTimer *kt,
                                    const VerifyTuning &tune, int force_lanes, int64_t expect,
-                                   unsigned long long **cells_out) {
+                                   unsigned long long **cells_out, const uint32_t **left_out) {
     const int np = verify_planes(std::max(A.bits, B.bits));
     VSet va = vset(A), vb = vset(B);
     cap = std::max<int64_t>(cap, 1);
@@ -1205,6 +1208,7 @@ void verify_pairs_batched_streamed(const uint64_t *pairs, int64_t cap, const uin
     *cells_out = cells;
     uint32_t *off = ws.get_n<uint32_t>(LPT_BINS + 1);
     int64_t *order = ws.get_n<int64_t>(cap);
+    if (left_out) *left_out = off + LPT_BINS;
     if (cmax > persist_max_c())
         throw Error(MJ_ECAPACITY, "threshold K above the batched verifier's band limit (K <= 2047)");
     const int nw = cmax + 1;

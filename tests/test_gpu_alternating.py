@@ -53,3 +53,29 @@ def test_small_and_large_joins(mj):
         if call:  # (the first large one may go stage by stage)
             assert st["streamed"] == 1
         assert 2 * st["band_cells"] < unfiltered["band_cells"], call
+
+
+@pytest.mark.parametrize("sigma,rate,tunes", [(25, 0.01, True), (4, 0.01, True), (4, 0.08, False)])
+def test_large_searches_after_a_small_one(mj, sigma, rate, tunes):
+    """The verifier's choices are timed once a search has pairs enough, also where the context's
+    first searches had few, and where the block filter leaves few the searches stay streamed."""
+    say("large searches after a small one", sigma, rate)
+    I = far_copies(5 + sigma, 900, copies=6, length=700, sigma=sigma, rate=rate)
+    kw = dict(t_div=2)
+    ctx = mj.Context()
+    index = mj.Index(dev(mj, I), mj.Params(q=4, k=64, **kw), ctx=ctx)
+    op = oracle.make_params(4, sigma, k=64, **kw)
+    few = I.subset([0])
+    many = I.subset(np.arange(0, I.n, 3))
+    streamed = []
+    for Q in (few, few, many, many, many, few, many):
+        _, want = oracle.search(I.chars, I.offsets, op, Q.chars, Q.offsets, op)
+        got, st = index.search(dev(mj, Q), k=64)
+        assert np.array_equal(got, want)
+        streamed.append(st["streamed"])
+    assert st["candidates"] > 4096
+    assert streamed[:2] == [0, 1]
+    if tunes:
+        assert streamed[2] == 0
+    assert streamed[4:] == [1, 1, 1]
+    index.close()
