@@ -1197,7 +1197,7 @@ static mj_pairs *run_search_streamed(mj_ctx *ctx, const mj_index *ix, DevStrings
     const int64_t rcap = std::max<int64_t>(si.rec_bound * qp.reps, 2);
     const double cexp = h.cand_per_record * (double)rcap, vexp = h.verified_per_record * (double)rcap;
     const double room = 1.25 * cexp + (double)std::max<int64_t>(4096, std::min<int64_t>(65536, rcap));
-    if (room > 2e9 || !dedup_buckets_fit((int64_t)cexp, qd.n, ix->n)) return nullptr;
+    if (room > 2e9) return nullptr;
     const int64_t ccap = (int64_t)room;
     VerifyTuning tune;  // (the context's own table is for calls that time their choices)
     const int ci = std::min(cmax, 63), npi = ix->np / 2 - 1;
@@ -1229,7 +1229,10 @@ static mj_pairs *run_search_streamed(mj_ctx *ctx, const mj_index *ix, DevStrings
     tm.mark();  // 3 probe + filter
     uint64_t *uniq = nullptr;
     uint32_t *over = ws.zeroed(2, s);
-    const uint32_t *u = dedup_buckets(cand, ccap, (int64_t)cexp, pr.counter, qd.n, ix->n, over, ws, s, &uniq);
+    const bool dedup = dedup_buckets_fit((int64_t)cexp, qd.n, ix->n) && !h.dedup.skip();
+    const uint32_t *u =
+        dedup ? dedup_buckets(cand, ccap, (int64_t)cexp, pr.counter, qd.n, ix->n, over, ws, s, &uniq)
+              : dedup_pairs_streamed(cand, ccap, pr.counter, qd.n, ix->n, ws, s, &uniq);
     tm.mark();  // 4 dedup
     uint8_t *flags = ws.get_n<uint8_t>(ccap + 4);
     unsigned long long *cells = nullptr;
@@ -1248,6 +1251,10 @@ static mj_pairs *run_search_streamed(mj_ctx *ctx, const mj_index *ix, DevStrings
     memcpy(hv, ctx->pinned, sizeof(hv));
     const int64_t R = (int64_t)hv[0], c0 = (int64_t)hv[4], C = (int64_t)hv[5], nout = (int64_t)hv[6];
     if (hv[9]) throw Error(MJ_EINVAL, "a symbol code is not below sigma");
+    if (dedup) {
+        if (hv[15]) h.dedup.failed();
+        else h.dedup.fitted();
+    }
     if (hv[15] || c0 > ccap) return nullptr;
     if (hv[8]) throw Error(MJ_ECAPACITY, "a pair's band exceeds the verifier window");
     mj_pairs *out = new mj_pairs();

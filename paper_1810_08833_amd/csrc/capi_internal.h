@@ -52,6 +52,7 @@ struct SearchHints {
     int32_t verify_lanes = 0;
     double cand_per_record = 0, tests_per_record = 0, verified_per_record = 0;
     double left_per_record = 0;  // pairs that the block filter left
+    Backoff dedup;  // the dedup's LDS buckets
 };
 
 // Sizes of a streamed join, fixed by the set-up read-back and the hints of the last join,

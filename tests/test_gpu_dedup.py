@@ -1,6 +1,6 @@
 """The dedup of candidates whose distinct pairs are far from evenly spread, against the oracle: few
 long strings (more candidates than there are pair keys), a cluster of neighbouring strings (all its
-pairs in a few buckets)."""
+pairs in a few buckets), few queries with most of the candidates."""
 import numpy as np
 import pytest
 
@@ -81,3 +81,34 @@ def test_cluster_of_neighbours(mj):
     ctx.set_streaming(1)
     _, sj = mj.join(dev(mj, S), p, ctx=ctx)
     assert sj["streamed"] == 1 and sj["stage_ms"]["dedup"] < 4 * sg["stage_ms"]["dedup"] + 0.5
+
+
+def test_few_queries_with_most_candidates(mj):
+    """Four of 256 queries find 30,000 near-copies, all in one of the dedup's buckets: the next
+    searches leave their dedup to the sort instead of running twice."""
+    say("few queries with most of the candidates")
+    rng = np.random.default_rng(78)
+    base = rng.integers(0, 4, 120).astype(np.uint8)
+
+    def copy(edits):
+        x = base.copy()
+        at = rng.integers(0, len(x), edits)
+        x[at] = rng.integers(0, 4, edits)
+        return x
+
+    I = dg.from_list([copy(1) for _ in range(30000)] +
+                     [rng.integers(0, 4, 120).astype(np.uint8) for _ in range(2000)], 4)
+    Q = dg.from_list([copy(1) if i in (100, 101, 102, 103) else rng.integers(0, 4, 120).astype(np.uint8)
+                      for i in range(256)], 4)
+    op = oracle.make_params(5, 4, k=10, t_div=4)
+    _, want = oracle.search(I.chars, I.offsets, op, Q.chars, Q.offsets, op)
+    ctx = mj.Context()
+    index = mj.Index(dev(mj, I), mj.Params(q=5, k=10, t_div=4), ctx=ctx)
+    streamed = []
+    for _ in range(5):
+        got, st = index.search(dev(mj, Q), k=10)
+        assert np.array_equal(got, want)
+        streamed.append(st["streamed"])
+    assert st["candidates"] > 80000
+    assert streamed[2:] == [1, 1, 1]
+    index.close()
