@@ -1195,6 +1195,7 @@ static mj_pairs *run_search_streamed(mj_ctx *ctx, const mj_index *ix, DevStrings
     const int cmax = (int)((std::min<int64_t>(qparams->k >= 0 ? qparams->k : si.kmax, 0x3FFFFFFF) + 31) >> 5);
     if (cmax > persist_max_c()) return nullptr;
     const int64_t rcap = std::max<int64_t>(si.rec_bound * qp.reps, 2);
+    if (rcap > PROBE_RECORDS_MAX) return nullptr;
     const double cexp = h.cand_per_record * (double)rcap, vexp = h.verified_per_record * (double)rcap;
     const double room = 1.25 * cexp + (double)std::max<int64_t>(4096, std::min<int64_t>(65536, rcap));
     if (room > 2e9) return nullptr;
@@ -1255,7 +1256,7 @@ static mj_pairs *run_search_streamed(mj_ctx *ctx, const mj_index *ix, DevStrings
         if (hv[15]) h.dedup.failed();
         else h.dedup.fitted();
     }
-    if (hv[15] || c0 > ccap) return nullptr;
+    if (hv[15] || c0 > ccap || hv[3] > PROBE_TESTS_MAX) return nullptr;
     if (hv[8]) throw Error(MJ_ECAPACITY, "a pair's band exceeds the verifier window");
     mj_pairs *out = new mj_pairs();
     out->alloc = t_dev_alloc;
@@ -1347,7 +1348,7 @@ extern "C" mj_status mj_search(mj_ctx *ctx, const mj_index *ix, const mj_strings
     if (rb.count > 0 && ix->rec.count > 0) {
         const Probe pr = probe_ranges(rb.key, rb.count, nullptr, ix->rec.key, ix->dir, ix->dir_bits, ws, s);
         tests = read_back<uint64_t>(pr.tests, s, ctx->pinned);
-        if (tests > (uint64_t)0x7FFFFFFF)
+        if (tests > PROBE_TESTS_MAX)
             throw Error(MJ_ECAPACITY, "record-pair tests exceed 2^31");
         if (tests) {
             cand = ws.get_n<uint64_t>(tests + 1);

@@ -1184,6 +1184,7 @@ __global__ __launch_bounds__(EMIT_BLOCK) void k_probe_emit(const uint64_t *__res
 
 Probe probe_ranges(const uint64_t *qkey, int64_t RQ, const int64_t *RQ_dev, const uint64_t *ikey,
                    const uint32_t *dir, int bits, Workspace &ws, hipStream_t s) {
+    if (RQ > PROBE_RECORDS_MAX) throw Error(MJ_ECAPACITY, "search with more than 2^32 query records");
     Probe p;
     p.RQ = RQ;
     p.RQ_dev = RQ_dev;

@@ -381,6 +381,9 @@ struct Probe {
     uint64_t *tests = nullptr;       // their sum (device)
     unsigned long long *counter = nullptr;  // candidates emitted (device)
 };
+// Limits of one search: query records (their count is read as one 32-bit word), record-pair tests.
+constexpr int64_t PROBE_RECORDS_MAX = 0xFFFFFFF0LL;
+constexpr uint64_t PROBE_TESTS_MAX = 0x7FFFFFFF;
 Probe probe_ranges(const uint64_t *qkey, int64_t RQ, const int64_t *RQ_dev, const uint64_t *ikey,
                    const uint32_t *dir, int bits, Workspace &ws, hipStream_t s);
 // The pairs through the filter to out[0 .. cap), their number (which may exceed cap) to
