@@ -189,7 +189,9 @@ mj_status mj_ctx_set_member_filter(mj_ctx *ctx, int64_t min_records, int32_t buc
 mj_status mj_ctx_set_tile_emission(mj_ctx *ctx, int64_t min_tile_pairs);
 
 /* How joins after the first (see mj_join) run: 0 stage by stage, each stage sized exactly
- * from a read-back (the least memory); 1 streamed (the default: stages sized on the device
+ * from a read-back (the least memory: beside the records, 16 bytes each, about 56 bytes a
+ * record where they are grouped in LDS buckets, 32 and the sort's run lists where they are
+ * sorted, as a call does that cannot get the former); 1 streamed (the default: stages sized on the device
  * from capacities, two host reads); 2 streamed and captured into two HIP graphs (the
  * set-up and everything after it), replayed while the strings' pointers and sizes, the
  * parameters and the set-up's results stay the same.  Captured joins give no kernel times
@@ -212,8 +214,8 @@ const char *mj_version(void);
  * context runs streamed: every stage after the per-string set-up is sized on the device
  * (records by a bound from the set-up, candidates by the last join's rate, the verifier in
  * the configuration the context timed), so the host waits twice -- for the set-up and for
- * the result.  When a capacity turns out too small, the join runs again stage by stage
- * (which sizes every stage from read-backs) and the result is the same.  EINVAL on bad arguments (q < 1, q*b > 64,
+ * the result.  When a capacity turns out too small, or device memory runs out, the join runs again stage
+ * by stage (which sizes every stage from read-backs) and the result is the same.  EINVAL on bad arguments (q < 1, q*b > 64,
  * t_div < 1, K < -1, sigma outside 2..256, offsets decreasing, a symbol code >= sigma,
  * verifier or verify_lanes not one of the listed values); ECAPACITY when a
  * documented limit is exceeded: a candidate whose threshold K is above 2047; ENOMEM when

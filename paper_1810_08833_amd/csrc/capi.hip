@@ -333,9 +333,10 @@ struct Released {
 };
 
 // ---------------------------------------------------------------- join pipeline
-// Runs the join up to `upto`: 1 = candidates, 2 = output.  Fills stats.
-static mj_pairs *run_join(mj_ctx *ctx, const mj_strings *strings, const mj_params *params,
-                          hipStream_t s, int upto, mj_stats *stats) {
+// Runs the join up to `upto`: 1 = candidates, 2 = output.  Fills stats.  buckets: LDS buckets may
+// be tried.
+static mj_pairs *run_join_by(mj_ctx *ctx, const mj_strings *strings, const mj_params *params,
+                             hipStream_t s, int upto, mj_stats *stats, bool buckets) {
     Workspace &ws = ctx->ws;
     Released rel{ws};
     StageTimer tm(ctx, s);
@@ -368,7 +369,9 @@ static mj_pairs *run_join(mj_ctx *ctx, const mj_strings *strings, const mj_param
     // by LDS buckets where the buckets fit (their records grouped, not sorted further)
     BucketRecords br;
     BucketMemo &memo = bucket_memo(ctx, strings, params);
-    bool bucket = use_buckets(ctx, M, members, d.total) && !memo.group.skip(), longs = true, sorted = false;
+    bool bucket = buckets && use_buckets(ctx, M, members, d.total) && !memo.group.skip();
+    bool longs = true, sorted = false;
+    ctx->tried_buckets = bucket;
     uint64_t *cand = nullptr;
     int64_t c0 = 0;
     auto emit = [&](int64_t cap, bool lng) {
@@ -524,6 +527,26 @@ static mj_pairs *run_join(mj_ctx *ctx, const mj_strings *strings, const mj_param
     }
     tm.fill(stats);
     return out;
+}
+
+// After a call that ran out of device memory: waits for what it launched and returns its blocks.
+static void after_enomem(mj_ctx *ctx, hipStream_t s) {
+    MJ_HIP(hipStreamSynchronize(s));
+    ctx->ws.free_idle();
+}
+
+// Without LDS buckets where they run out of device memory: the sort's scratch is the smaller.
+static mj_pairs *run_join(mj_ctx *ctx, const mj_strings *strings, const mj_params *params,
+                          hipStream_t s, int upto, mj_stats *stats) {
+    ctx->tried_buckets = false;
+    try {
+        return run_join_by(ctx, strings, params, s, upto, stats, true);
+    } catch (const Error &e) {
+        if (e.status != MJ_ENOMEM || !ctx->tried_buckets) throw;
+    }
+    after_enomem(ctx, s);
+    ctx->buckets.group.failed();
+    return run_join_by(ctx, strings, params, s, upto, stats, false);
 }
 
 // ---------------------------------------------------------------- streamed join
@@ -972,8 +995,15 @@ extern "C" mj_status mj_join(mj_ctx *ctx, const mj_strings *strings, const mj_pa
     const bool batched = params->verifier == MJ_VERIFY_BATCHED;
     (void)bucket_memo(ctx, strings, params);
     if (batched && ctx->streaming && !ctx->no_tuning && hints_match(ctx->stream, strings, params)) {
-        mj_pairs *r = ctx->streaming == 2 ? run_join_graph(ctx, strings, params, s, stats)
-                                          : run_join_streamed(ctx, strings, params, s, stats);
+        mj_pairs *r = nullptr;
+        try {
+            r = ctx->streaming == 2 ? run_join_graph(ctx, strings, params, s, stats)
+                                    : run_join_streamed(ctx, strings, params, s, stats);
+        } catch (const Error &e) {
+            if (e.status != MJ_ENOMEM) throw;
+            if (ctx->streaming == 2) graph_drop(ctx);
+            after_enomem(ctx, s);  // stage by stage takes the least
+        }
         if (r) {
             ctx->streamed_joins++;
             *out = r;
@@ -1290,24 +1320,9 @@ static mj_pairs *run_search_streamed(mj_ctx *ctx, const mj_index *ix, DevStrings
     return out;
 }
 
-extern "C" mj_status mj_search(mj_ctx *ctx, const mj_index *ix, const mj_strings *queries,
-                               const mj_params *qparams, void *stream, mj_pairs **out,
-                               mj_stats *stats) {
-    if (!ctx || !ix || !out) return fail(MJ_EINVAL, "ctx/index/out is NULL");
-    MJ_API_BEGIN
-    check_strings(queries);
-    if (!qparams) throw Error(MJ_EINVAL, "qparams is NULL");
-    if (queries->sigma > ix->sigma || queries->sigma < 2)
-        throw Error(MJ_EINVAL, "query alphabet must not exceed the index alphabet");
-    if (queries->packing == MJ_PACK_2BIT && ix->bits > 2)
-        throw Error(MJ_EINVAL, "2-bit packed queries need an index over at most 4 symbols");
-    if (qparams->k < -1 || (qparams->k == -1 && !qparams->k_per_string))
-        throw Error(MJ_EINVAL, "bad query threshold");
-    if (qparams->k > 2047) throw Error(MJ_ECAPACITY, "threshold K exceeds the verifier's band limit (K <= 2047)");
-    check_verifier(qparams);
-    MJ_HIP(hipSetDevice(ctx->device));
-    AllocScope as(ctx->ws.alloc);
-    hipStream_t s = (hipStream_t)stream;
+// streamed: sized by the last search's rates; nullptr when they do not serve.
+static mj_pairs *run_search(mj_ctx *ctx, const mj_index *ix, const mj_strings *queries,
+                            const mj_params *qparams, hipStream_t s, mj_stats *stats, bool streamed) {
     Workspace &ws = ctx->ws;
     Released rel{ws};
     StageTimer tm(ctx, s);
@@ -1322,19 +1337,11 @@ extern "C" mj_status mj_search(mj_ctx *ctx, const mj_index *ix, const mj_strings
     int32_t halo = prepare_strings(qd, qp, ws, s, ctx->pinned, &si);
     pack_planes(qd, ix->np, ws, s);
     tm.mark();  // 0 setup
-    const bool batched = qparams->verifier == MJ_VERIFY_BATCHED;
     SearchHints &h = ctx->search;
-    if (batched && ctx->streaming && h.valid && h.n == ix->n && h.records == ix->rec.count &&
-        h.verify_lanes == qparams->verify_lanes && ix->rec.count > 0 && qd.n > 0) {
+    if (streamed) {
         mj_pairs *r = run_search_streamed(ctx, ix, qd, qp, si, qparams, tm, s, stats);
-        if (r) {
-            tm.fill(stats);
-            *out = r;
-            return MJ_OK;
-        }
-        tm = StageTimer(ctx, s);  // stage by stage: its times from here on
-        tm.mark();
-        if (stats) memset(stats, 0, sizeof(*stats));
+        if (r) tm.fill(stats);
+        return r;
     }
     RecBuf rb;
     rb.ws = &ws;
@@ -1375,7 +1382,7 @@ extern "C" mj_status mj_search(mj_ctx *ctx, const mj_index *ix, const mj_strings
         stats->band_cells = cells;
         stats->positions = qd.total * qp.reps;
     }
-    if (batched) {
+    if (qparams->verifier == MJ_VERIFY_BATCHED) {
         // what the next search's stages are sized by
         const double bound = (double)std::max<int64_t>(si.rec_bound * qp.reps, 2);
         const bool same = h.valid && h.n == ix->n && h.records == ix->rec.count;
@@ -1389,7 +1396,40 @@ extern "C" mj_status mj_search(mj_ctx *ctx, const mj_index *ix, const mj_strings
         h.verify_lanes = qparams->verify_lanes;
     }
     tm.fill(stats);
-    *out = res;
+    return res;
+}
+
+extern "C" mj_status mj_search(mj_ctx *ctx, const mj_index *ix, const mj_strings *queries,
+                               const mj_params *qparams, void *stream, mj_pairs **out,
+                               mj_stats *stats) {
+    if (!ctx || !ix || !out) return fail(MJ_EINVAL, "ctx/index/out is NULL");
+    MJ_API_BEGIN
+    check_strings(queries);
+    if (!qparams) throw Error(MJ_EINVAL, "qparams is NULL");
+    if (queries->sigma > ix->sigma || queries->sigma < 2)
+        throw Error(MJ_EINVAL, "query alphabet must not exceed the index alphabet");
+    if (queries->packing == MJ_PACK_2BIT && ix->bits > 2)
+        throw Error(MJ_EINVAL, "2-bit packed queries need an index over at most 4 symbols");
+    if (qparams->k < -1 || (qparams->k == -1 && !qparams->k_per_string))
+        throw Error(MJ_EINVAL, "bad query threshold");
+    if (qparams->k > 2047) throw Error(MJ_ECAPACITY, "threshold K exceeds the verifier's band limit (K <= 2047)");
+    check_verifier(qparams);
+    MJ_HIP(hipSetDevice(ctx->device));
+    AllocScope as(ctx->ws.alloc);
+    hipStream_t s = (hipStream_t)stream;
+    const SearchHints &h = ctx->search;
+    mj_pairs *r = nullptr;
+    if (qparams->verifier == MJ_VERIFY_BATCHED && ctx->streaming && h.valid && h.n == ix->n &&
+        h.records == ix->rec.count && h.verify_lanes == qparams->verify_lanes && ix->rec.count > 0 &&
+        queries->n > 0) {
+        try {
+            r = run_search(ctx, ix, queries, qparams, s, stats, true);
+        } catch (const Error &e) {
+            if (e.status != MJ_ENOMEM) throw;
+            after_enomem(ctx, s);  // stage by stage takes the least
+        }
+    }
+    *out = r ? r : run_search(ctx, ix, queries, qparams, s, stats, false);
     return MJ_OK;
     MJ_API_END
 }

@@ -116,6 +116,7 @@ struct mj_ctx {
     int64_t last_c0 = 0, last_R = 0, last_rcap = 0, last_M = 0;
     uint64_t last_small_tests = 0, last_units = 0;
     bool last_longs = true;  // as StreamHints::longs
+    bool tried_buckets = false;  // by the stage-by-stage join at hand
 };
 
 struct mj_pairs {

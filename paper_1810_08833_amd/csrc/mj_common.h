@@ -92,6 +92,7 @@ class Workspace {
     void begin_zeroed(size_t words, hipStream_t s);
     uint32_t *zeroed(size_t words, hipStream_t s);
     void release_all();
+    void free_idle();  // returns the blocks no call uses (their stream work must be complete)
     size_t bytes_held() const { return held_; }
     // bytes of the blocks the last call used (measured by release_all)
     size_t last_call_bytes() const { return last_used_; }

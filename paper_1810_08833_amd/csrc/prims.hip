@@ -121,15 +121,19 @@ void *Workspace::get(size_t bytes) {
     } catch (const Error &) {
         // free idle blocks and retry once (the stream work of earlier calls is complete:
         // every entry point synchronises before it returns)
-        for (auto it = blocks_.begin(); it != blocks_.end();) {
-            if (!it->used) { dev_free(it->p, alloc); held_ -= it->n; it = blocks_.erase(it); }
-            else ++it;
-        }
+        free_idle();
         p = dev_alloc(bytes, alloc);
     }
     blocks_.push_back({p, bytes, true, holding_});
     held_ += bytes;
     return p;
+}
+
+void Workspace::free_idle() {
+    for (auto it = blocks_.begin(); it != blocks_.end();) {
+        if (!it->used) { dev_free(it->p, alloc); held_ -= it->n; it = blocks_.erase(it); }
+        else ++it;
+    }
 }
 
 void Workspace::begin_zeroed(size_t words, hipStream_t s) {

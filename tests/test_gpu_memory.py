@@ -1,0 +1,105 @@
+"""Joins, candidate calls and searches on a context whose allocator has no more memory than the
+general path, stage by stage, needs: whatever takes more gives way to it."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_1810_08833_amd import datagen as dg
+from tests.test_gpu_alternating import far_copies
+from tests.test_gpu_parity import dev, say
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def mj():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_1810_08833_amd as m
+    return m
+
+
+def limited(mj, limit=None):
+    """An allocator that has `limit` bytes (None: all there are) and notes the most it gave out."""
+    import torch
+    a = mj.TorchAllocator(torch.cuda.current_device())
+    give, take = a._alloc_cb, a._free_cb
+    a.peak = 0
+    a.refused = 0
+
+    def alloc(nbytes, user):
+        if limit is not None and sum(a.live.values()) + nbytes > limit:
+            a.refused += 1
+            return None
+        p = give(nbytes, user)
+        a.peak = max(a.peak, sum(a.live.values()))
+        return p
+
+    a.limited_cb = mj.ALLOC_FN(alloc)
+    a.struct = mj.MjAllocator(a.limited_cb, take, None)
+    return a
+
+
+@pytest.mark.parametrize("member_filter", [-1, 1])
+def test_join_within_the_general_path_memory(mj, member_filter):
+    say("join, memory of the general path, member filter", member_filter)
+    S = far_copies(31, 300, copies=6, length=3000, rate=0.01)
+    p = mj.Params(q=5, k=64, t_div=1, reps=2)
+    want_c, want, _ = oracle.join(S.chars, S.offsets, oracle.make_params(5, 4, k=64, t_div=1, reps=2))
+
+    def context(alloc):
+        c = mj.Context(allocator=alloc)
+        c.set_member_filter(member_filter)
+        return c
+
+    free = limited(mj)
+    general = context(free)
+    general.set_tile_emission(0)
+    general.set_streaming(0)
+    got, _ = mj.join(dev(mj, S), p, ctx=general)
+    assert np.array_equal(got, want)
+    general.close()
+    tight = limited(mj, free.peak)
+    ctx = context(tight)
+    for mode in (0, 0, 1, 1, 2, 2):
+        ctx.set_streaming(mode)
+        got, _ = mj.join(dev(mj, S), p, ctx=ctx)
+        assert np.array_equal(got, want), mode
+    ctx.close()
+    assert tight.refused > 0 and not tight.live
+    # candidates of a fresh context
+    free = limited(mj)
+    general = context(free)
+    general.set_tile_emission(0)
+    got, _ = mj.candidates(dev(mj, S), p, ctx=general)
+    assert np.array_equal(got, want_c)
+    general.close()
+    ctx = context(limited(mj, free.peak))
+    for _ in range(2):
+        got, _ = mj.candidates(dev(mj, S), p, ctx=ctx)
+        assert np.array_equal(got, want_c)
+    ctx.close()
+
+
+def test_search_within_the_stagewise_memory(mj):
+    say("search, memory of the stage-by-stage one")
+    I = far_copies(32, 300, copies=6, length=1000, rate=0.01)
+    Q = I.subset(np.arange(0, I.n, 2))
+    op = oracle.make_params(5, 4, k=64, t_div=1)
+    _, want = oracle.search(I.chars, I.offsets, op, Q.chars, Q.offsets, op)
+    free = limited(mj)
+    ctx = mj.Context(allocator=free)
+    ctx.set_streaming(0)
+    index = mj.Index(dev(mj, I), mj.Params(q=5, k=64, t_div=1), ctx=ctx)
+    got, _ = index.search(dev(mj, Q), k=64)
+    assert np.array_equal(got, want)
+    index.close()
+    ctx.close()
+    ctx = mj.Context(allocator=limited(mj, free.peak))
+    index = mj.Index(dev(mj, I), mj.Params(q=5, k=64, t_div=1), ctx=ctx)
+    for _ in range(4):
+        got, _ = index.search(dev(mj, Q), k=64)
+        assert np.array_equal(got, want)
+    index.close()
+    ctx.close()
