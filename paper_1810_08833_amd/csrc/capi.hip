@@ -1228,7 +1228,12 @@ static mj_pairs *run_search_streamed(mj_ctx *ctx, const mj_index *ix, DevStrings
     if (rcap > PROBE_RECORDS_MAX) return nullptr;
     const double cexp = h.cand_per_record * (double)rcap, vexp = h.verified_per_record * (double)rcap;
     const double room = 1.25 * cexp + (double)std::max<int64_t>(4096, std::min<int64_t>(65536, rcap));
-    if (room > 2e9) return nullptr;
+    // About 64 bytes each.  The rate may be that of a few queries with many candidates (it falls
+    // slowly), so the room is bounded by what the queries themselves take, and within a server's
+    // estimate of a batch.
+    const double spare = (double)(ctx->no_tuning ? 4 << 20 : 64 << 20) + 32.0 * (double)qd.total +
+                         4096.0 * (double)qd.n;
+    if (room > 2e9 || 64.0 * room > spare) return nullptr;
     const int64_t ccap = (int64_t)room;
     VerifyTuning tune;  // (the context's own table is for calls that time their choices)
     const int ci = std::min(cmax, 63), npi = ix->np / 2 - 1;

@@ -103,3 +103,29 @@ def test_search_within_the_stagewise_memory(mj):
         assert np.array_equal(got, want)
     index.close()
     ctx.close()
+
+
+def test_many_queries_after_a_frequent_one(mj):
+    """One query with 100 candidates a record, then 1,500 of none: the first one's rate
+    does not size the second search (it took 6.8 GB)."""
+    say("search, many queries after a frequent one")
+    rng = np.random.default_rng(35)
+    base = rng.integers(0, 4, 120).astype(np.uint8)
+    I = dg.from_list([base] * 6000 + [rng.integers(0, 4, 120).astype(np.uint8) for _ in range(500)], 4)
+    rest = dg.from_list([rng.integers(0, 4, 120).astype(np.uint8) for _ in range(1500)], 4)
+    op = oracle.make_params(5, 4, k=10, t_div=1)
+    alloc = limited(mj)
+    ctx = mj.Context(allocator=alloc)
+    index = mj.Index(dev(mj, I), mj.Params(q=5, k=10, t_div=1), ctx=ctx)
+    one = dg.from_list([base], 4)
+    for _ in range(2):
+        got, st = index.search(dev(mj, one), k=10)
+        assert np.array_equal(got, np.arange(6000, dtype=np.uint64)) and st["candidates"] >= 6000
+    assert st["streamed"] == 1
+    _, want = oracle.search(I.chars, I.offsets, op, rest.chars, rest.offsets, op)
+    for _ in range(2):
+        got, _ = index.search(dev(mj, rest), k=10)
+        assert np.array_equal(got, want)
+    assert alloc.peak < 1 << 30
+    index.close()
+    ctx.close()
