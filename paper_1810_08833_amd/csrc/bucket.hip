@@ -29,13 +29,11 @@ constexpr int BK_MTHREADS = 256;  // of a workgroup where all records are member
 constexpr int BK_KEEP = 4, BK_MKEEP = 2;  // of a bucket's records each thread keeps in registers
 constexpr int BK_SUB = 15;      // key bits of a bucket's bitmaps; log2 BK_SLOTS of them number the slot
 constexpr int BK_SLOTS = 2048, BK_MSLOTS = 1024;
-constexpr int BK_STAGE = 512;  // candidates staged before they take room in the output
+constexpr int BK_STAGE = 512;   // candidates staged before they take room in the output
 constexpr int BK_LONG = 63;     // slots of more records are set aside
 constexpr int BK_CHUNK = 64;    // buckets whose bounds are found together
 constexpr int BK_LONGS = 64;    // such slots of a bucket
 constexpr int BK_DISTINCT = 32; // distinct keys of such a slot
-constexpr int BK_BLOCKS = 1024; // four workgroups of 39 KB a CU
-constexpr int BK_MBLOCKS = 1536; // six of 28 KB
 static_assert(2 * DD_CAP == 1 << DD_LOG, "dedup table");
 
 // First index in [0, n) whose key's top bits are >= b, by the whole wave: a 64-way search.
@@ -107,14 +105,16 @@ struct BucketOut {
 //
 // A bucket is a chain of short steps between barriers, so what bounds the kernel is how many
 // workgroups a CU holds and what each step waits for: the next bucket's records and this one's
-// lengths are loaded ahead (MEMBERS: 256 threads, six workgroups of 28 KB a CU), the bounds of
-// 64 buckets found at once, and short slots laid out by size, so that a wave's lanes have about
+// lengths are loaded ahead (MEMBERS: 256 threads; a CU's registers hold four such workgroups, or
+// two of 512 threads, and the grid is that many: half a round more, six a CU, left the device half
+// empty at the end), the bounds of 64 buckets found at once, and short slots laid out by size, so that a wave's lanes have about
 // as many tests each.  Room in the output is taken in pieces of 256 candidates or more, since
 // one address takes 80 M atomics a second; a bucket of more than the stage holds is tested twice.
-// 17.3 M members, 256 M tests, 10.1 M candidates: 0.70 ms and 0.27 ms for the long slots, where
-// the two more sort passes, the repair, the groups and the emission took 1.9 ms; with a wave's
-// candidates straight to the output and slots in key order 1.47 ms.  7.0 M unfiltered records
-// (0.41 M groups): 142 us, in key order 170.
+// 17.3 M members, 256 M tests, 10.1 M candidates: 0.98 ms with the long slots' 0.27, with as many
+// workgroups as fit at once 0.86, where the two more sort passes, the repair, the groups and the
+// emission took 1.9 ms; with a wave's candidates straight to the output and slots in key order
+// 1.74 ms.  7.0 M unfiltered records (0.41 M groups): 167 us with twice the workgroups that fit,
+// 159 with those.
 template <bool MEMBERS>
 __global__ __launch_bounds__(MEMBERS ? BK_MTHREADS : BK_THREADS) void k_bucket_pairs(BucketIn in,
                                                                                     BucketOut o) {
@@ -661,7 +661,11 @@ BucketRecords bucket_records(uint64_t *key, uint64_t *val, int64_t cap, int64_t 
         r.val = vo;
     }
     const int64_t nb = 1ll << r.bits;
-    r.blocks = (int)std::min<int64_t>(nb, members ? BK_MBLOCKS : BK_BLOCKS);
+    // as many workgroups as the device holds at once (their registers leave room for two of 512
+    // threads a CU, or four of 256), each with an equal share of the buckets
+    r.blocks = (int)(nb <= 256 ? nb
+                               : std::min<int64_t>(nb, members ? resident_grid(k_bucket_pairs<true>, BK_MTHREADS)
+                                                               : resident_grid(k_bucket_pairs<false>, BK_THREADS)));
     r.members = members;
     // a tile pair of one key has 1,000 tests or more on average; slots of several keys may have
     // fewer, up to this many tile pairs (2^20, about 5 ms, for the default pass)

@@ -77,6 +77,16 @@ constexpr uint64_t RESULT_POOL_KEEP = 1ull << 30;
 void *result_alloc(size_t bytes, const mj_allocator &a, hipStream_t s);
 void result_free(void *p, const mj_allocator &a, hipStream_t s);
 
+// Persistent grid of a kernel: the workgroups that fit the device at once.
+template <class K>
+inline unsigned resident_grid(K kern, int threads) {
+    int dev = 0, cus = 0, per = 0;
+    MJ_HIP(hipGetDevice(&dev));
+    MJ_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+    MJ_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, kern, threads, 0));
+    return (unsigned)std::max(1, cus * std::max(1, per));
+}
+
 // ---------------------------------------------------------------- workspace
 // Grow-only cache of device blocks; blocks handed out during one call are released
 // together at its end and reused by the next call.  Blocks come from `alloc` (the

@@ -1827,16 +1827,6 @@ static int64_t *scan_tiles(const std::vector<uint32_t *> &tcount, int reps, int6
     return base;
 }
 
-// Persistent grid of a kernel: the workgroups that fit the device at once.
-template <class K>
-static unsigned resident_grid(K kern, int threads) {
-    int dev = 0, cus = 0, per = 0;
-    MJ_HIP(hipGetDevice(&dev));
-    MJ_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-    MJ_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, kern, threads, 0));
-    return (unsigned)std::max(1, cus * std::max(1, per));
-}
-
 // Records of every repetition.  bm_all / pre_all hold the repetitions' anchor bitmaps and
 // tile count prefixes one after another (strides nw + 1 and ntiles + 1); rbase their first
 // record indices (device).  Several repetitions: the tile kernel, which takes the symbols
