@@ -199,6 +199,22 @@ mj_status mj_ctx_set_tile_emission(mj_ctx *ctx, int64_t min_tile_pairs);
  * NULL context or another mode. */
 mj_status mj_ctx_set_streaming(mj_ctx *ctx, int mode);
 
+/* How the context's last join or candidates call grouped its records, for inspection:
+ * MJ_GROUP_BUCKETS in LDS buckets (else sorted), MJ_GROUP_DEDUP its pairs deduplicated in
+ * LDS buckets too (else sorted); and, in bits 8 up, why the call left buckets that it
+ * tried (0: it left none): MJ_LEFT_*.  -1 for a NULL context. */
+enum { MJ_GROUP_BUCKETS = 1, MJ_GROUP_DEDUP = 2 };
+enum {
+    MJ_LEFT_MEMBERS = 1,  /* a bucket's records that may share their key */
+    MJ_LEFT_SLOTS = 2,    /* a bucket's frequent keys */
+    MJ_LEFT_ROOM = 3,     /* the room for the records of frequent keys */
+    MJ_LEFT_DISTINCT = 4, /* keys that share a frequent key's slot */
+    MJ_LEFT_DEDUP = 5,    /* pairs of one dedup bucket */
+    MJ_LEFT_TESTS = 6,    /* more record-pair tests than a pass */
+    MJ_LEFT_MEMORY = 7,   /* device memory */
+};
+int mj_ctx_grouping(const mj_ctx *ctx);
+
 /* Thread-local description of the last error (never NULL). */
 const char *mj_last_error(void);
 

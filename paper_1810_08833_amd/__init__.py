@@ -22,6 +22,7 @@ LIB_PATH = os.path.join(_HERE, "libminjoin.so")
 
 MJ_OK, MJ_EINVAL, MJ_ENOMEM, MJ_EDEVICE, MJ_ECAPACITY = 0, 1, 2, 3, 4
 VERIFY_BATCHED, VERIFY_PLAIN = 0, 1
+LEFT_MEMBERS, LEFT_SLOTS, LEFT_ROOM, LEFT_DISTINCT, LEFT_DEDUP, LEFT_TESTS, LEFT_MEMORY = range(1, 8)
 STATUS_NAMES = {0: "MJ_OK", 1: "MJ_EINVAL", 2: "MJ_ENOMEM", 3: "MJ_EDEVICE", 4: "MJ_ECAPACITY"}
 KERNELS = ["anchors", "records", "emit", "verify"]
 STAGES = ["setup", "partition", "sort", "group_filter", "dedup", "verify", "output", "unused"]
@@ -86,7 +87,7 @@ class MjReply(ctypes.Structure):
 
 
 EXPORTS = ["mj_ctx_create", "mj_ctx_destroy", "mj_ctx_set_streaming", "mj_ctx_set_pair_test_pass",
-           "mj_ctx_set_member_filter", "mj_ctx_set_tile_emission",
+           "mj_ctx_set_member_filter", "mj_ctx_set_tile_emission", "mj_ctx_grouping",
            "mj_last_error", "mj_version", "mj_join",
            "mj_partition", "mj_candidates", "mj_verify", "mj_index_build", "mj_index_free",
            "mj_index_records", "mj_index_bytes", "mj_search", "mj_pairs_count", "mj_pairs_device",
@@ -124,6 +125,8 @@ def load_library(path: str = LIB_PATH):
     L.mj_ctx_set_member_filter.restype = ctypes.c_int
     L.mj_ctx_set_tile_emission.argtypes = [VP, ctypes.c_int64]
     L.mj_ctx_set_tile_emission.restype = ctypes.c_int
+    L.mj_ctx_grouping.argtypes = [VP]
+    L.mj_ctx_grouping.restype = ctypes.c_int
     L.mj_last_error.restype = ctypes.c_char_p
     L.mj_version.restype = ctypes.c_char_p
     L.mj_join.argtypes = [VP, P(MjStrings), P(MjParams), VP, P(VP), P(MjStats)]
@@ -251,6 +254,12 @@ class Context:
         default) are kept whole."""
         _check(load_library().mj_ctx_set_member_filter(self.handle, int(min_records),
                                                        int(bucket_limit)))
+
+    def grouping(self):
+        """How the last join or candidates call grouped its records: (in LDS buckets, dedup in
+        LDS buckets, why it left buckets that it tried: an MJ_LEFT_* value, 0 if it left none)."""
+        v = load_library().mj_ctx_grouping(self.handle)
+        return bool(v & 1), bool(v & 2), v >> 8
 
     def close(self):
         if self.handle:

@@ -108,6 +108,8 @@ static bool use_buckets(const mj_ctx *ctx, int64_t records, bool members, int64_
     return ctx->tile_min != 0 && bucket_join_fits(records, members, total);
 }
 
+extern "C" int mj_ctx_grouping(const mj_ctx *ctx) { return ctx ? ctx->grouping | (ctx->left << 8) : -1; }
+
 // The context's memo of the parameters, a new one if they are others than the last call's.
 static BucketMemo &bucket_memo(mj_ctx *ctx, const mj_strings *st, const mj_params *p) {
     BucketMemo &m = ctx->buckets;
@@ -413,9 +415,11 @@ static mj_pairs *run_join_by(mj_ctx *ctx, const mj_strings *strings, const mj_pa
         if (over || g.tests > pass_tests) {
             bucket = false;
             longs = true;
+            ctx->left = over ? (int)over : MJ_LEFT_TESTS;
             g = GroupInfo();
             memo.group.failed();
         } else {
+            ctx->grouping |= MJ_GROUP_BUCKETS;
             memo.group.fitted();
             if (c0 > cap) {
                 bucket_reset(br, s);
@@ -441,6 +445,7 @@ static mj_pairs *run_join_by(mj_ctx *ctx, const mj_strings *strings, const mj_pa
             done = (uint32_t)ctx->pinned[1] == 0;
             if (done) {
                 memo.dedup.fitted();
+                ctx->grouping |= MJ_GROUP_DEDUP;
                 C = (int64_t)(uint32_t)ctx->pinned[0];
                 uniq = res;
                 if (upto == 1) {  // the caller's
@@ -449,6 +454,7 @@ static mj_pairs *run_join_by(mj_ctx *ctx, const mj_strings *strings, const mj_pa
                 }
             } else {
                 memo.dedup.failed();
+                ctx->left = MJ_LEFT_DEDUP;
                 bucket_reset(br, s);
                 emit(c0, longs);  // the candidates as they were
             }
@@ -539,6 +545,7 @@ static void after_enomem(mj_ctx *ctx, hipStream_t s) {
 static mj_pairs *run_join(mj_ctx *ctx, const mj_strings *strings, const mj_params *params,
                           hipStream_t s, int upto, mj_stats *stats) {
     ctx->tried_buckets = false;
+    ctx->grouping = 0;
     try {
         return run_join_by(ctx, strings, params, s, upto, stats, true);
     } catch (const Error &e) {
@@ -546,6 +553,8 @@ static mj_pairs *run_join(mj_ctx *ctx, const mj_strings *strings, const mj_param
     }
     after_enomem(ctx, s);
     ctx->buckets.group.failed();
+    ctx->grouping = 0;
+    ctx->left = MJ_LEFT_MEMORY;
     return run_join_by(ctx, strings, params, s, upto, stats, false);
 }
 
@@ -811,6 +820,8 @@ static mj_pairs *finish_streamed(mj_ctx *ctx, const StreamedPlan &pl, const Stre
         if (hv[15]) memo.dedup.failed();
         else memo.dedup.fitted();
     }
+    ctx->grouping = (pl.bucket ? MJ_GROUP_BUCKETS : 0) | (pl.dedup ? MJ_GROUP_DEDUP : 0);
+    ctx->left = hv[13] ? (int)hv[13] : (int)hv[15];
     // more than the room left: stage by stage
     if (hv[13] || hv[15] || missed || c0h > pl.ccap || R > pl.scap || M > pl.mcap) return nullptr;
     if (M > 1 && (hv[1] & 0xFFFFFFFFu) != (hv[1] >> 32)) throw Error(MJ_EDEVICE, "group boundary mismatch");
@@ -994,6 +1005,7 @@ extern "C" mj_status mj_join(mj_ctx *ctx, const mj_strings *strings, const mj_pa
     hipStream_t s = (hipStream_t)stream;
     const bool batched = params->verifier == MJ_VERIFY_BATCHED;
     (void)bucket_memo(ctx, strings, params);
+    ctx->left = 0;
     if (batched && ctx->streaming && !ctx->no_tuning && hints_match(ctx->stream, strings, params)) {
         mj_pairs *r = nullptr;
         try {
@@ -1042,6 +1054,7 @@ extern "C" mj_status mj_candidates(mj_ctx *ctx, const mj_strings *strings, const
     check_params(params, strings->sigma, true);
     MJ_HIP(hipSetDevice(ctx->device));
     AllocScope as(ctx->ws.alloc);
+    ctx->left = 0;
     *out = run_join(ctx, strings, params, (hipStream_t)stream, 1, stats);
     return MJ_OK;
     MJ_API_END

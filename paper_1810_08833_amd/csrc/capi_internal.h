@@ -117,6 +117,7 @@ struct mj_ctx {
     uint64_t last_small_tests = 0, last_units = 0;
     bool last_longs = true;  // as StreamHints::longs
     bool tried_buckets = false;  // by the stage-by-stage join at hand
+    int grouping = 0, left = 0;  // of the last join or candidates call (mj_ctx_grouping)
 };
 
 struct mj_pairs {

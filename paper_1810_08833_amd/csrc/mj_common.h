@@ -433,7 +433,14 @@ struct BucketRecords {
 // Why a bucket does not fit (*over): its short slots' members, its long slots, the room for
 // their records, a long slot's distinct keys; the dedup's part of equal leading bits; the long
 // slots' tile pairs.
-enum : uint32_t { OVER_MEMBERS = 1, OVER_SLOTS, OVER_ROOM, OVER_DISTINCT, OVER_DEDUP, OVER_UNITS };
+enum : uint32_t {
+    OVER_MEMBERS = MJ_LEFT_MEMBERS,
+    OVER_SLOTS = MJ_LEFT_SLOTS,
+    OVER_ROOM = MJ_LEFT_ROOM,
+    OVER_DISTINCT = MJ_LEFT_DISTINCT,
+    OVER_DEDUP = MJ_LEFT_DEDUP,
+    OVER_UNITS = MJ_LEFT_TESTS
+};
 bool bucket_join_fits(int64_t records, bool members, int64_t total);
 // expect: how many records there may be (speed, and whether the buckets fit); members: the
 // member filter kept them; fine: buckets as small as theirs, most records being members all the

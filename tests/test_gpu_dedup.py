@@ -50,10 +50,7 @@ def test_more_candidates_than_keys(mj, n, length):
         assert np.array_equal(got, want), mode
 
 
-def test_cluster_of_neighbours(mj):
-    """Most pairs are of strings 5,000 to 5,699: their dedup is left to the sort, at its speed.  (By
-    buckets each of them went over its 100,000 pairs and more 64 times.)"""
-    say("dedup of a cluster of neighbours")
+def neighbours():
     rng = np.random.default_rng(77)
     base = rng.integers(0, 4, 300).astype(np.uint8)
     strs = [rng.integers(0, 4, 300).astype(np.uint8) for _ in range(20000)]
@@ -61,7 +58,14 @@ def test_cluster_of_neighbours(mj):
         strs[i] = base.copy()
         at = rng.integers(0, 300, 4)
         strs[i][at] = rng.integers(0, 4, 4)
-    S = dg.from_list(strs, 4)
+    return dg.from_list(strs, 4)
+
+
+def test_cluster_of_neighbours(mj):
+    """Most pairs are of strings 5,000 to 5,699: their dedup is left to the sort, at its speed.  (By
+    buckets each of them went over its 100,000 pairs and more 64 times.)"""
+    say("dedup of a cluster of neighbours")
+    S = neighbours()
     want_c, want, _ = oracle.join(S.chars, S.offsets, oracle.make_params(5, 4, k=10, t_div=2))
     p = mj.Params(q=5, k=10, t_div=2)
     general = mj.Context()

@@ -6,6 +6,7 @@ import pytest
 import oracle
 from paper_1810_08833_amd import datagen as dg
 from tests.test_gpu_alternating import far_copies
+from tests.test_gpu_bucket_sizes import near_copies
 from tests.test_gpu_parity import dev, say
 
 pytestmark = pytest.mark.gpu
@@ -44,7 +45,7 @@ def limited(mj, limit=None):
 @pytest.mark.parametrize("member_filter", [-1, 1])
 def test_join_within_the_general_path_memory(mj, member_filter):
     say("join, memory of the general path, member filter", member_filter)
-    S = far_copies(31, 300, copies=6, length=3000, rate=0.01)
+    S = near_copies(3, 2000, 2)
     p = mj.Params(q=5, k=64, t_div=1, reps=2)
     want_c, want, _ = oracle.join(S.chars, S.offsets, oracle.make_params(5, 4, k=64, t_div=1, reps=2))
 
