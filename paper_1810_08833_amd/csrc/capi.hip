@@ -1152,6 +1152,7 @@ extern "C" mj_status mj_index_build(mj_ctx *ctx, const mj_strings *strings, cons
         for (int i = 1; i < 6; i++) at[i] = at[i - 1] + ((at[i] + 255) & ~(size_t)255);
         uint8_t *block = (uint8_t *)dev_alloc(at[5]);
         ix->offsets = (int64_t *)block;
+        ix->block_bytes = at[5];
         ix->len = (int32_t *)(block + at[1]);
         ix->kk = (int32_t *)(block + at[2]);
         ix->planes = (uint32_t *)(block + at[3]);
@@ -1202,11 +1203,8 @@ extern "C" int64_t mj_index_records(const mj_index *ix) { return ix ? ix->rec.co
 
 extern "C" int64_t mj_index_bytes(const mj_index *ix) {
     if (!ix) return 0;
-    int64_t b = ((int64_t)ix->n + 1) * (8 + 4 + 4);  // offsets, lengths, thresholds
-    b += (int64_t)ix->np * ix->plane_words * 4;
-    b += ix->rec.cap * (8 + 8 + (ix->rec.with_len ? 4 : 0));
+    int64_t b = (int64_t)ix->block_bytes + (int64_t)ix->rec.bytes;
     if (ix->dir) b += (((int64_t)1 << ix->dir_bits) + 1) * 4;
-    if (ix->pi_table) b += (int64_t)8 << (ix->pp.q * ix->bits);
     return b;
 }
 

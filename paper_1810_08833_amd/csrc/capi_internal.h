@@ -139,6 +139,7 @@ struct mj_index {
     // the strings' arrays and pi_table are one block, offsets first: every allocation costs about
     // 15 us and every free, which waits for the device, 60
     int64_t *offsets = nullptr;
+    size_t block_bytes = 0;
     int32_t *len = nullptr, *kk = nullptr;
     uint32_t *planes = nullptr;
     int64_t plane_words = 0;

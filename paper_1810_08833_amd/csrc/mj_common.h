@@ -274,6 +274,7 @@ struct RecBuf {  // (val and len in key's block)
     uint64_t *val = nullptr;
     uint32_t *len = nullptr;
     int64_t cap = 0, count = 0;
+    size_t bytes = 0;  // of the block
     bool with_len = false;
     Workspace *ws = nullptr;
     mj_allocator alloc{};  // owned arrays (ws == nullptr): the allocator that made them

@@ -1638,7 +1638,8 @@ void RecBuf::reserve(int64_t need, hipStream_t s) {
     int64_t nc = std::max<int64_t>(need, cap + cap / 2);
     auto get = [&](size_t bytes) -> void * { return ws ? ws->get(bytes) : dev_alloc(bytes, alloc); };
     const int64_t pitch = (nc + 31) & ~(int64_t)31;  // one block: val and len start 256-byte aligned
-    uint64_t *k2 = (uint64_t *)get((size_t)pitch * (with_len ? 20 : 16));
+    const size_t size = (size_t)pitch * (with_len ? 20 : 16);
+    uint64_t *k2 = (uint64_t *)get(size);
     uint64_t *v2 = k2 + pitch;
     uint32_t *l2 = with_len ? (uint32_t *)(v2 + pitch) : nullptr;
     if (count > 0) {
@@ -1648,12 +1649,12 @@ void RecBuf::reserve(int64_t need, hipStream_t s) {
         MJ_HIP(hipStreamSynchronize(s));
     }
     if (!ws) dev_free(key, alloc);
-    key = k2; val = v2; len = l2; cap = nc;
+    key = k2; val = v2; len = l2; cap = nc; bytes = size;
 }
 
 void RecBuf::release() {
     if (!ws) dev_free(key, alloc);
-    key = val = nullptr; len = nullptr; cap = count = 0;
+    key = val = nullptr; len = nullptr; cap = count = 0; bytes = 0;
 }
 
 // The tables k_tables makes, and what the bucket function's Horner steps are made of.

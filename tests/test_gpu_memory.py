@@ -130,3 +130,20 @@ def test_many_queries_after_a_frequent_one(mj):
     assert alloc.peak < 1 << 30
     index.close()
     ctx.close()
+
+
+@pytest.mark.parametrize("n,table", [(0, False), (1, False), (37, True), (1000, False)])
+def test_index_bytes(mj, n, table):
+    """mj_index_bytes is what freeing the index gives back to the allocator."""
+    import torch
+    say("index bytes", n, table)
+    rng = np.random.default_rng(n)
+    I = dg.from_list([rng.integers(0, 4, int(rng.integers(100, 500))).astype(np.uint8) for _ in range(n)], 4)
+    alloc = limited(mj)
+    ctx = mj.Context(allocator=alloc)
+    pi = torch.from_numpy(rng.permutation(4 ** 5).astype(np.int64)).cuda() if table else None
+    index = mj.Index(dev(mj, I), mj.Params(q=5, k=10, t_div=1, pi_table=pi), ctx=ctx)
+    with_index, said = sum(alloc.live.values()), index.device_bytes
+    index.close()
+    assert with_index - sum(alloc.live.values()) == said > 0
+    ctx.close()
