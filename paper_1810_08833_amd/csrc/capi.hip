@@ -110,17 +110,23 @@ static bool use_buckets(const mj_ctx *ctx, int64_t records, bool members, int64_
 
 extern "C" int mj_ctx_grouping(const mj_ctx *ctx) { return ctx ? ctx->grouping | (ctx->left << 8) : -1; }
 
-// The context's memo of the parameters, a new one if they are others than the last call's.
+// The context's memo of the parameters, which *ctx->buckets is then.
 static BucketMemo &bucket_memo(mj_ctx *ctx, const mj_strings *st, const mj_params *p) {
-    BucketMemo &m = ctx->buckets;
-    if (m.key.q != p->q || m.key.t_div != p->t_div || m.key.t_fixed != p->t_fixed ||
-        m.key.reps != p->reps || m.key.seed != p->seed || m.key.k != p->k || m.sigma != st->sigma ||
-        m.packing != st->packing) {
-        m = BucketMemo();
-        m.key = *p;
-        m.sigma = st->sigma;
-        m.packing = st->packing;
+    for (BucketMemo &m : ctx->memos) {
+        if (m.key.q == p->q && m.key.t_div == p->t_div && m.key.t_fixed == p->t_fixed &&
+            m.key.reps == p->reps && m.key.seed == p->seed && m.key.k == p->k &&
+            m.sigma == st->sigma && m.packing == st->packing) {
+            ctx->buckets = &m;
+            return m;
+        }
     }
+    BucketMemo &m = ctx->memos[ctx->next_memo];
+    ctx->next_memo = (ctx->next_memo + 1) % (int)(sizeof(ctx->memos) / sizeof(ctx->memos[0]));
+    m = BucketMemo();
+    m.key = *p;
+    m.sigma = st->sigma;
+    m.packing = st->packing;
+    ctx->buckets = &m;
     return m;
 }
 
@@ -552,7 +558,7 @@ static mj_pairs *run_join(mj_ctx *ctx, const mj_strings *strings, const mj_param
         if (e.status != MJ_ENOMEM || !ctx->tried_buckets) throw;
     }
     after_enomem(ctx, s);
-    ctx->buckets.group.failed();
+    ctx->buckets->group.failed();
     ctx->grouping = 0;
     ctx->left = MJ_LEFT_MEMORY;
     return run_join_by(ctx, strings, params, s, upto, stats, false);
@@ -725,9 +731,9 @@ static bool plan_streamed(mj_ctx *ctx, const mj_params *params, const DevStrings
     pl.emit = h.emit;
     pl.rexp = std::min<int64_t>(
         pl.mcap, (int64_t)((pl.members ? h.mem_per_bound : h.rec_per_bound) * (double)pl.rcap));
-    pl.bucket = use_buckets(ctx, pl.mcap, pl.members, d.total) && !ctx->buckets.group.skip();
-    pl.fine = ctx->buckets.fine && !pl.members;
-    pl.dedup = pl.bucket && dedup_buckets_fit(pl.cexp, d.n, d.n) && !ctx->buckets.dedup.skip();
+    pl.bucket = use_buckets(ctx, pl.mcap, pl.members, d.total) && !ctx->buckets->group.skip();
+    pl.fine = ctx->buckets->fine && !pl.members;
+    pl.dedup = pl.bucket && dedup_buckets_fit(pl.cexp, d.n, d.n) && !ctx->buckets->dedup.skip();
     pl.longs = h.longs;
     return true;
 }
@@ -803,7 +809,7 @@ static mj_pairs *finish_streamed(mj_ctx *ctx, const StreamedPlan &pl, const Stre
     const int64_t R = (int64_t)hv[0], c0h = (int64_t)hv[4], C = (int64_t)hv[5], nout = (int64_t)hv[6];
     const int64_t M = (int64_t)hv[10];
     if (hv[9]) throw Error(MJ_EINVAL, "a symbol code is not below sigma");
-    BucketMemo &memo = ctx->buckets;
+    BucketMemo &memo = *ctx->buckets;
     if (pl.bucket && hv[13] == OVER_MEMBERS && !pl.members && !pl.fine) {
         memo.fine = true;  // stage by stage, in smaller buckets
     } else if (pl.bucket && hv[13]) {

@@ -107,7 +107,9 @@ struct mj_ctx {
     int streaming = 1;  // 0 stage by stage, 1 streamed, 2 streamed and captured (mj_ctx_set_streaming)
     StreamHints stream;
     SearchHints search;
-    BucketMemo buckets;
+    BucketMemo memos[8];  // of the last parameters the context was called with
+    BucketMemo *buckets = memos;  // of those of the call at hand
+    int next_memo = 1;
     JoinGraph graph;
     hipStream_t cap_stream = nullptr;  // the stream graphs are captured on
     int streamed_joins = 0, stream_fallbacks = 0;

@@ -58,6 +58,18 @@ def test_more_tests_than_a_pass(mj):
     assert ctx.grouping() == (False, False, 0)
 
 
+def test_parameters_in_turn(mj):
+    """Calls of several parameters on one context: what each found holds for its next call."""
+    say("parameters in turn")
+    S = tandem(12, 420)
+    ctx = mj.Context()
+    ctx.set_pair_test_pass(1024)
+    for call in range(3):
+        for k in (28, 29, 30, 31, 32):
+            mj.candidates(dev(mj, S), mj.Params(q=5, k=k, t_div=2), ctx=ctx)
+            assert ctx.grouping() == (False, False, 0 if call else mj.LEFT_TESTS)
+
+
 def test_pairs_of_one_dedup_bucket(mj):
     say("left: dedup")
     S = neighbours()
