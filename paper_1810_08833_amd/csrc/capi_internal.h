@@ -22,6 +22,7 @@ struct BucketMemo {
     int32_t sigma = 0, packing = 0;
     Backoff group, dedup;  // the records' buckets, the dedup's
     bool fine = false;     // smaller buckets of records: most of them share their key
+    double candidates = 0; // before the dedup, per record grouped
 };
 
 // What a join of the batched path learned for the next join with the same parameters:

@@ -70,6 +70,21 @@ def test_parameters_in_turn(mj):
             assert ctx.grouping() == (False, False, 0 if call else mj.LEFT_TESTS)
 
 
+def test_candidates_beyond_the_records(mj):
+    """More candidates than the first call has room for: its tests run twice, the next calls' once,
+    and calls with few candidates follow."""
+    say("candidates beyond the records")
+    S, few = tandem(12, 420), near_copies(72, 3, 2)
+    p = mj.Params(q=5, k=30, t_div=2)
+    ctx = mj.Context()
+    for emits in (2, 1, 1):
+        _, st = mj.candidates(dev(mj, S), p, ctx=ctx)
+        assert st["kernel_launches"]["emit"] == emits and ctx.grouping()[0]
+    _, want, _ = oracle.join(few.chars, few.offsets, oracle.make_params(5, 4, k=30, t_div=2))
+    got, _ = mj.join(dev(mj, few), p, ctx=ctx)
+    assert np.array_equal(got, want)
+
+
 def test_pairs_of_one_dedup_bucket(mj):
     say("left: dedup")
     S = neighbours()
