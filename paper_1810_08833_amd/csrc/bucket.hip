@@ -541,8 +541,15 @@ __global__ __launch_bounds__(BK_THREADS) void k_long_units(const ulonglong2 *__r
 }
 
 // A wave takes a share of the tile pairs I <= J in order: lane l holds record 64 I + l, tile
-// J's records are read from LDS by all lanes at once.
+// J's records are read from LDS by all lanes at once.  Candidates are staged by the wave, up to
+// LP_BUF of them, since what bounds the kernel where most pairs pass is the one counter (80 M
+// atomics a second); a tile pair whose first rows are full finds all its candidates first and
+// takes their room at once.  59 M candidates of 4 groups of 1,500: 0.80 -> 0.34 ms with the
+// short slots' kernel, 21 M of 20 groups of 400: 0.35 -> 0.20; taking room so at every tile pair
+// was 0.29 and 0.17 there, but 0.09 ms more on 17 M members of protein-like strings (0.87), whose
+// tile pairs are mostly thin.
 constexpr int LP_WAVES = 4, LP_BUF = 1024;
+constexpr int LP_LOOK = 4, LP_DENSE = 64;  // rows looked at, candidates of theirs
 __global__ __launch_bounds__(64 * LP_WAVES) void k_long_pairs(const uint64_t *__restrict__ ustart,
                                                               BucketOut o) {
     __shared__ uint64_t tkey[LP_WAVES][64];
@@ -613,18 +620,53 @@ __global__ __launch_bounds__(64 * LP_WAVES) void k_long_pairs(const uint64_t *__
         }
         const int nbx = (int)min<int64_t>(64, z - (int64_t)J * 64);
         const bool diag = I == J;
-        for (int j = 0; j < nbx; j++) {
+        auto passes = [&](int j) -> bool {
             const int4 e = trec[wv][j];
-            const bool pass = ha && (!diag || lane < j) && ka == tkey[wv][j] && xa.x != e.x &&
-                              (uint32_t)max(abs(xa.y - e.y), abs(xa.z - e.z)) <=
-                                  max((uint32_t)xa.w, (uint32_t)e.w);
+            return ha && (!diag || lane < j) && ka == tkey[wv][j] && xa.x != e.x &&
+                   (uint32_t)max(abs(xa.y - e.y), abs(xa.z - e.z)) <= max((uint32_t)xa.w, (uint32_t)e.w);
+        };
+        auto pair = [&](int j) -> uint64_t {
+            const int ex = trec[wv][j].x;
+            return ((uint64_t)(uint32_t)min(xa.x, ex) << 32) | (uint32_t)max(xa.x, ex);
+        };
+        uint32_t found = 0;  // (wave-uniform)
+        int top = nbx;       // rows from the last on: of the diagonal's the fullest first
+        auto stage = [&](int j) {
+            const bool pass = passes(j);
             const uint64_t m = __ballot(pass);
             if (m) {
-                if (pass)
-                    wb[staged + __popcll(m & ((1ull << lane) - 1))] =
-                        ((uint64_t)(uint32_t)min(xa.x, e.x) << 32) | (uint32_t)max(xa.x, e.x);
+                if (pass) wb[staged + __popcll(m & ((1ull << lane) - 1))] = pair(j);
                 staged += (uint32_t)__popcll(m);
+                found += (uint32_t)__popcll(m);
                 if (staged > LP_BUF - 64) drain();
+            }
+        };
+        for (int r = 0; r < LP_LOOK && top > 0; r++) stage(--top);
+        if (found < LP_DENSE) {
+            while (top > 0) stage(--top);
+        } else if (top > 0) {
+            uint64_t row = 0;  // lane j: the records of tile I that pass with record j of tile J
+            for (int j = 0; j < top; j++) {
+                const uint64_t m = __ballot(passes(j));
+                row = lane == j ? m : row;
+            }
+            uint32_t inc = (uint32_t)__popcll(row);
+#pragma unroll
+            for (int s = 1; s < 64; s <<= 1) {
+                const uint32_t y = (uint32_t)__shfl_up((int)inc, s, 64);
+                if (lane >= s) inc += y;
+            }
+            const uint32_t rest = (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
+            unsigned long long g = 0;
+            if (lane == 0) g = atomicAdd(o.counter, (unsigned long long)rest);
+            g = (unsigned long long)__shfl((long long)g, 0, 64);
+            const uint32_t first = inc - (uint32_t)__popcll(row);
+            for (int j = 0; j < top; j++) {
+                const uint64_t m = (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)row, j) |
+                                   ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(row >> 32), j) << 32);
+                const int64_t at = (int64_t)g + (uint32_t)__builtin_amdgcn_readlane((int)first, j) +
+                                   __popcll(m & ((1ull << lane) - 1));
+                if (((m >> lane) & 1ull) && at < o.cap) o.out[at] = pair(j);
             }
         }
         if (++u >= uend) break;

@@ -5,6 +5,7 @@ import pytest
 
 import oracle
 from paper_1810_08833_amd import datagen as dg
+from tests.test_gpu_buckets import shared_segments
 from tests.test_gpu_parity import dev, say
 
 pytestmark = pytest.mark.gpu
@@ -66,3 +67,19 @@ def test_mostly_members(mj, clusters, buckets):
         c.set_streaming(1)
         got, _ = mj.join(dev(mj, A), p, ctx=c)
         assert np.array_equal(got, w)
+
+
+# tile pairs of which all record pairs are candidates: one, whole and partly filled tiles, several
+@pytest.mark.parametrize("copies", [64, 65, 68, 69, 127, 128, 129, 193])
+def test_full_tile_pairs(mj, copies):
+    say("full tile pairs", copies)
+    S = shared_segments(200 + copies, 1, copies)
+    want_c, want, _ = oracle.join(S.chars, S.offsets, oracle.make_params(5, 4, k=30, t_div=2))
+    p = mj.Params(q=5, k=30, t_div=2)
+    assert len(want_c) >= copies * (copies - 1) // 2
+    ctx = mj.Context()
+    got, _ = mj.candidates(dev(mj, S), p, ctx=ctx)
+    assert np.array_equal(got, want_c) and ctx.grouping()[0]
+    for _ in range(2):
+        got, _ = mj.join(dev(mj, S), p, ctx=ctx)
+        assert np.array_equal(got, want)
