@@ -537,6 +537,8 @@ static mj_pairs *run_join_by(mj_ctx *ctx, const mj_strings *strings, const mj_pa
     tm.mark();  // 5 verify
     mj_pairs *out = compact_pairs(uniq, flags, C, ws, s, ctx->pinned);  // synchronises when C > 0
     const int64_t cells = take_cells(ctx, out);
+    if (params->verifier == MJ_VERIFY_BATCHED && !params->verify_lanes && C > 0 && !ctx->no_tuning)
+        ctx->tune.accepted(ctx->tune.last_ci, ctx->tune.last_npi, out->n, C);
     tm.mark();  // 6 output
     if (stats) {
         stats->output = out->n;
@@ -579,7 +581,7 @@ static mj_pairs *run_join(mj_ctx *ctx, const mj_strings *strings, const mj_param
 // What the host reads at the end of a streamed join or search: the counts, in dst[0 .. RES_WORDS).
 // slot: the group counts of a join by the general path; part, state: of one by LDS buckets
 // (see BucketRecords); tests, over (of its dedup): of a search.
-constexpr int RES_WORDS = 18;
+constexpr int RES_WORDS = 17;
 struct Collect {
     const int64_t *R;
     const uint64_t *slot;
@@ -592,7 +594,6 @@ struct Collect {
     int blocks;
     const uint64_t *tests;
     const uint32_t *over;
-    const uint32_t *left;  // pairs verified after the block filter
 };
 
 // by one wave
@@ -628,7 +629,6 @@ __device__ void collect(const Collect &c, uint32_t outn, uint64_t *dst) {
     dst[13] = c.state ? (uint32_t)c.state[1] : 0;
     dst[14] = c.state ? c.state[2] >> 40 : 0;
     dst[16] = shared;
-    dst[17] = c.left ? *c.left : 0;
     dst[15] = c.state ? c.state[1] >> 32 : c.over ? *c.over : 0;
 }
 
@@ -798,7 +798,7 @@ static StreamedDev launch_streamed_main(mj_ctx *ctx, DevStrings &d, const Partit
     dv.outbuf = ws.get_n<uint64_t>(pl.ccap + 1);
     uint64_t *res = ws.get_n<uint64_t>(RES_WORDS);
     const Collect cl{R_dev, g.slot, c0, u, cells, d.symbol_err, M_dev, br.part, br.state, br.blocks,
-                     nullptr, nullptr, nullptr};
+                     nullptr, nullptr};
     collect_output(cl, uniq, flags, pl.ccap, pl.vexp, dv.outbuf, res, ws, s);
     MJ_HIP(hipMemcpyAsync(ctx->pinned, res, RES_WORDS * 8, hipMemcpyDeviceToHost, s));
     return dv;
@@ -862,6 +862,8 @@ static mj_pairs *finish_streamed(mj_ctx *ctx, const StreamedPlan &pl, const Stre
         stats->member_filter = pl.members ? 1 : 0;
         stats->members = M;
     }
+    if (!ctx->stream.verify_lanes)
+        ctx->tune.accepted(std::min(pl.cmax, 63), verify_planes(d.bits) / 2 - 1, nout, C);
     // keep the rates current (capacities of the next join)
     // (the candidates' rate falls slowly: collections of one kind differ by more than the room)
     ctx->stream.cand_per_record = std::max((double)c0h / (double)pl.rcap,
@@ -1263,7 +1265,7 @@ static mj_pairs *run_search_streamed(mj_ctx *ctx, const mj_index *ix, DevStrings
     // (4,000 queries of an index of 40,000 strings, 24 K candidates of 25 or 37 letters: verified in
     // 0.31 ms by the choice for small calls, 0.26 by the one timed.)
     if (!qparams->verify_lanes && !ctx->no_tuning && !ctx->tune.best_g[ci][npi] &&
-        verify_tunes((int64_t)(h.left_per_record * (double)rcap)))
+        verify_tunes((int64_t)vexp))
         return nullptr;
     const int g = qparams->verify_lanes == -2 ? VERIFY_BIDIR
                 : qparams->verify_lanes == -3 ? VERIFY_CLASSES
@@ -1271,6 +1273,7 @@ static mj_pairs *run_search_streamed(mj_ctx *ctx, const mj_index *ix, DevStrings
                 : ctx->tune.best_g[ci][npi] ? ctx->tune.best_g[ci][npi] : verify_small_call_lanes(cmax);
     if (window_words_per_lane(g, cmax) == 0) return nullptr;
     tune.best_g[ci][npi] = g;
+    tune.no_filter[ci][npi] = ctx->tune.no_filter[ci][npi];
     tune.best_blocks[ci][npi] = ctx->tune.best_g[ci][npi] && !qparams->verify_lanes
                                     ? ctx->tune.best_blocks[ci][npi] : 512;
 
@@ -1294,14 +1297,13 @@ static mj_pairs *run_search_streamed(mj_ctx *ctx, const mj_index *ix, DevStrings
     tm.mark();  // 4 dedup
     uint8_t *flags = ws.get_n<uint8_t>(ccap + 4);
     unsigned long long *cells = nullptr;
-    const uint32_t *left = nullptr;
     verify_pairs_batched_streamed(uniq, ccap, u, qd, id, 1, cmax, flags, ws, s, &ctx->kt, tune,
-                                  qparams->verify_lanes, (int64_t)vexp, &cells, &left);
+                                  qparams->verify_lanes, (int64_t)vexp, &cells);
     tm.mark();  // 5 verify
     uint64_t *outbuf = ws.get_n<uint64_t>(ccap + 1);
     uint64_t *res = ws.get_n<uint64_t>(RES_WORDS);
     const Collect cl{R_dev, nullptr, pr.counter, u, cells, qd.symbol_err, R_dev, nullptr, nullptr, 0,
-                     pr.tests, over, left};
+                     pr.tests, over};
     collect_output(cl, uniq, flags, ccap, (int64_t)vexp, outbuf, res, ws, s);
     MJ_HIP(hipMemcpyAsync(ctx->pinned, res, RES_WORDS * 8, hipMemcpyDeviceToHost, s));
     MJ_HIP(hipStreamSynchronize(s));
@@ -1343,7 +1345,7 @@ static mj_pairs *run_search_streamed(mj_ctx *ctx, const mj_index *ix, DevStrings
     h.cand_per_record = std::max((double)c0 / (double)rcap, 0.99 * h.cand_per_record);
     h.tests_per_record = (double)hv[3] / (double)rcap;
     h.verified_per_record = (double)C / (double)rcap;
-    h.left_per_record = (double)hv[17] / (double)rcap;
+    if (!qparams->verify_lanes) ctx->tune.accepted(ci, npi, nout, C);
     return out;
 }
 
@@ -1410,13 +1412,14 @@ static mj_pairs *run_search(mj_ctx *ctx, const mj_index *ix, const mj_strings *q
         stats->positions = qd.total * qp.reps;
     }
     if (qparams->verifier == MJ_VERIFY_BATCHED) {
+        if (!qparams->verify_lanes && C > 0 && !ctx->no_tuning)
+            ctx->tune.accepted(ctx->tune.last_ci, ctx->tune.last_npi, res->n, C);
         // what the next search's stages are sized by
         const double bound = (double)std::max<int64_t>(si.rec_bound * qp.reps, 2);
         const bool same = h.valid && h.n == ix->n && h.records == ix->rec.count;
         h.cand_per_record = std::max((double)c0 / bound, same ? 0.99 * h.cand_per_record : 0.0);
         h.tests_per_record = (double)tests / bound;
         h.verified_per_record = (double)C / bound;
-        h.left_per_record = C ? (double)ctx->tune.last_left / bound : 0.0;
         h.valid = true;
         h.n = ix->n;
         h.records = ix->rec.count;

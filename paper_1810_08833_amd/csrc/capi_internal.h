@@ -52,7 +52,6 @@ struct SearchHints {
     int64_t records = 0;
     int32_t verify_lanes = 0;
     double cand_per_record = 0, tests_per_record = 0, verified_per_record = 0;
-    double left_per_record = 0;  // pairs that the block filter left
     Backoff dedup;  // the dedup's LDS buckets
 };
 

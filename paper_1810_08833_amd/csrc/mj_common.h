@@ -485,8 +485,20 @@ struct VerifyTuning {
     int best_g[64][4] = {};
     int best_blocks[64][4] = {};
     int last_g = 0, last_nwl = 0, last_blocks = 0;
-    int64_t last_left = 0;  // pairs of the last call, or (known where it had no choice timed yet)
-                            // those the block filter left
+    // timed: the block filter costs more than it saves on strings of this mean length (0: not so),
+    // of whose pairs this share is within K (0: not known); it may save several times the bands of
+    // others, so longer strings or a smaller share put it back (accepted, and the mean length there)
+    float no_filter[64][4] = {}, share[64][4] = {};
+    int last_ci = 0, last_npi = 0;
+    bool filter(int ci, int npi, double mean) const {
+        return no_filter[ci][npi] == 0.f || mean > 1.5 * no_filter[ci][npi];
+    }
+    void accepted(int ci, int npi, int64_t within, int64_t pairs) {
+        if (no_filter[ci][npi] == 0.f || pairs <= 0) return;
+        const float now = (float)within / (float)pairs;
+        if (share[ci][npi] == 0.f) share[ci][npi] = now;
+        else if (now < 0.5f * share[ci][npi]) no_filter[ci][npi] = share[ci][npi] = 0.f;
+    }
 };
 // Whether a call with so many pairs to verify times the choices where none is known.
 bool verify_tunes(int64_t pairs);
@@ -510,6 +522,6 @@ void verify_pairs_batched_streamed(const uint64_t *pairs, int64_t cap, const uin
                                    const DevStrings &A, const DevStrings &B, int kmode, int cmax,
                                    uint8_t *flags, Workspace &ws, hipStream_t s, KTimer *kt,
                                    const VerifyTuning &tune, int force_lanes, int64_t expect,
-                                   unsigned long long **cells_out, const uint32_t **left_out = nullptr);
+                                   unsigned long long **cells_out);
 
 }  // namespace mj

@@ -1052,20 +1052,25 @@ int64_t verify_pairs_batched(const uint64_t *pairs, int64_t n, const DevStrings 
     uint32_t *cnt = zb + ZNEXT + 8;
     fill_u32(zb, 0, ZNEXT + 8 + 6 * ZCNT, s);
     bool next_zero = true;
-    // the pairs the block filter leaves, nullptr: all of them
-    const uint8_t *keep = nullptr;
-    // one order per mode, built when a configuration that reads it is timed or chosen
-    uint32_t *off_of[3] = {};
-    int64_t *order_of[3] = {};
-    auto order_for = [&](int g) {
+    // one order per mode, built when a configuration that reads it is timed or chosen: of the
+    // pairs that keep flags (all of them if it is null)
+    struct Orders {
+        const uint8_t *keep = nullptr;
+        uint32_t *zero = nullptr;  // 6 * ZCNT words
+        uint32_t *off[3] = {};
+        int64_t *order[3] = {};
+    };
+    auto order_for = [&](Orders &o, int g) {
         const int m = lpt_mode(g);
-        if (order_of[m]) return m;
-        off_of[m] = ws.get_n<uint32_t>(LPT_BINS + 1);
-        order_of[m] = ws.get_n<int64_t>(n);
-        build_order(pairs, n, va, vb, kmode, m, cnt + 2 * m * ZCNT, cnt + (2 * m + 1) * ZCNT,
-                    off_of[m], order_of[m], ws, s, nullptr, keep);
+        if (o.order[m]) return m;
+        o.off[m] = ws.get_n<uint32_t>(LPT_BINS + 1);
+        o.order[m] = ws.get_n<int64_t>(n);
+        build_order(pairs, n, va, vb, kmode, m, o.zero + 2 * m * ZCNT, o.zero + (2 * m + 1) * ZCNT,
+                    o.off[m], o.order[m], ws, s, nullptr, o.keep);
         return m;
     };
+    Orders ord;
+    ord.zero = cnt;
     int cmax;
     if (uniform_k >= 0) {
         // every pair's K is known (and its ids valid): no pass over the pairs
@@ -1096,23 +1101,22 @@ int64_t verify_pairs_batched(const uint64_t *pairs, int64_t n, const DevStrings 
         if (nwl_for(nw, best_g) == 0)
             throw Error(MJ_ECAPACITY, "verify_lanes: the lanes of a pair cannot hold this band");
     }
-    int64_t left = n;  // pairs to verify
-    if (tune && force_lanes == 0 && block_filter_applies(std::max(A.bits, B.bits), cmax, n)) {
-        block_filter(pairs, n, A, B, kmode, flags, s, nullptr);
-        keep = flags;
-        if (best_g == 0) {
-            const int m = order_for(RING);
-            left = read_back<uint32_t>(off_of[m] + LPT_BINS, s, host_scratch);
-        }
-    }
-    if (best_g == 0 && (left < TUNE_MIN_PAIRS || !tune)) {
+    const double mean = (double)(A.total + B.total) / (double)std::max<int64_t>(1, (int64_t)A.n + B.n);
+    const bool filter = tune && force_lanes == 0 && tune->filter(ci, npi, mean) &&
+                        block_filter_applies(std::max(A.bits, B.bits), cmax, n);
+    if (best_g == 0 && (n < TUNE_MIN_PAIRS || !tune)) {
         // a small call leaves most of the chip idle: the shortest path per pair, since timing
         // the choices would cost more than the work.  Without a tuning table (latency-first
         // callers) the same fixed choice.
         best_g = verify_small_call_lanes(cmax);
         best_blocks = 512;
     }
-    if (best_g == 0) {
+    if (best_g != 0) {
+        if (filter) {
+            block_filter(pairs, n, A, B, kmode, flags, s, nullptr);
+            ord.keep = flags;
+        }
+    } else {
         // time each (lanes per pair, resident workgroups) once on this call's pairs and
         // keep the fastest.  Back-to-back timing favours more resident workgroups than a
         // launch inside the pipeline does (the column split ran 1.30 ms at 768 and 1.32 ms
@@ -1121,55 +1125,88 @@ int64_t verify_pairs_batched(const uint64_t *pairs, int64_t n, const DevStrings 
         hipEvent_t e0, e1;
         MJ_HIP(hipEventCreate(&e0));
         MJ_HIP(hipEventCreate(&e1));
-        float best = 1e30f;
-        best_g = 0;
-        // every order before the first launch: the launches write the filter's flags over
-        order_for(1);
-        if (classes_ok) order_for(CLASSES);
-        order_for(RING);
-        for (int g : G_CHOICES) {
-            if (nwl_for(nw, g) == 0 || (g == CLASSES && !classes_ok)) continue;
-            const int m = order_for(g);
-            int step = 0;
-            for (int mb : {256, 512, 768, 1024, 2048}) {
-                const float penalty = 1.0f + 0.03f * (float)step++;
-                float ms = 1e30f;
-                for (int rep = 0; rep < 2; rep++) {  // best of two: timing noise
-                    MJ_HIP(hipEventRecord(e0, s));
-                    launch_persist(cmax, g, np, mb, pairs, order_of[m], n, va, vb, kmode, flags,
-                                   cells, next, s, next_zero, off_of[m] + LPT_BINS, off_of[m]);
-                    next_zero = false;
-                    MJ_HIP(hipEventRecord(e1, s));
-                    MJ_HIP(hipEventSynchronize(e1));
-                    float t = 0.f;
-                    MJ_HIP(hipEventElapsedTime(&t, e0, e1));
-                    ms = std::min(ms, t);
-                }
-                if (ms * penalty < best) {
-                    best = ms * penalty;
-                    best_g = g;
-                    best_blocks = mb;
+        auto timed = [&](auto launch) -> float {  // best of two: timing noise
+            float ms = 1e30f;
+            for (int rep = 0; rep < 2; rep++) {
+                MJ_HIP(hipEventRecord(e0, s));
+                launch();
+                MJ_HIP(hipEventRecord(e1, s));
+                MJ_HIP(hipEventSynchronize(e1));
+                float t = 0.f;
+                MJ_HIP(hipEventElapsedTime(&t, e0, e1));
+                ms = std::min(ms, t);
+            }
+            return ms;
+        };
+        struct Choice {
+            int g = 0, blocks = 0;
+            float ms = 1e30f, rank = 1e30f;
+        };
+        auto fastest = [&](Orders &o) {
+            Choice c;
+            // every order before the first launch: the launches write the filter's flags over
+            order_for(o, 1);
+            if (classes_ok) order_for(o, CLASSES);
+            order_for(o, RING);
+            constexpr int COUNTS[] = {256, 512, 768, 1024, 2048};
+            for (int g : G_CHOICES) {
+                if (nwl_for(nw, g) == 0 || (g == CLASSES && !classes_ok)) continue;
+                const int m = order_for(o, g);
+                for (int step : {1, 0, 2, 3, 4}) {  // 512 workgroups first
+                    const float penalty = 1.0f + 0.03f * (float)step;
+                    const int mb = COUNTS[step];
+                    const float ms = timed([&] {
+                        launch_persist(cmax, g, np, mb, pairs, o.order[m], n, va, vb, kmode, flags, cells,
+                                       next, s, next_zero, o.off[m] + LPT_BINS, o.off[m]);
+                        next_zero = false;
+                    });
+                    if (ms * penalty < c.rank) c = Choice{g, mb, ms, ms * penalty};
+                    // (other counts change the time by less than this)
+                    if (step == 1 && ms > 1.5f * c.ms) break;
                 }
             }
+            return c;
+        };
+        Choice c;
+        if (filter) {
+            const float tf = timed([&] { block_filter(pairs, n, A, B, kmode, flags, s, nullptr); });
+            ord.keep = flags;
+            c = fastest(ord);
+            // All pairs without the filter: where most of them are within K, or their strings are
+            // short, it costs more than it saves (200,000 pairs of 1,250 symbols, K = 100, all
+            // within it: 0.83 ms against 0.66; all beyond it, 0.37 against 0.40).
+            Orders all;
+            all.zero = ws.get_n<uint32_t>(6 * ZCNT);
+            fill_u32(all.zero, 0, 6 * ZCNT, s);
+            const Choice plain = fastest(all);
+            if (plain.ms < tf + c.ms) {
+                tune->no_filter[ci][npi] = (float)std::max(mean, 1.0);
+                tune->share[ci][npi] = 0.f;
+                ord = all;
+                c = plain;
+            }
+        } else {
+            c = fastest(ord);
         }
+        best_g = c.g;
+        best_blocks = c.blocks;
         (void)hipEventDestroy(e0);
         (void)hipEventDestroy(e1);
-        if (tune) {
-            tune->best_g[ci][npi] = best_g;
-            tune->best_blocks[ci][npi] = best_blocks;
-        }
+        tune->best_g[ci][npi] = best_g;
+        tune->best_blocks[ci][npi] = best_blocks;
         fill_u64((uint64_t *)cells, 0, 1, s);
     }
-    const int om = order_for(best_g);
+    const int om = order_for(ord, best_g);
     int th = kt ? kt->begin(KTimer::VERIFY, s) : -1;
-    launch_persist(cmax, best_g, np, best_blocks, pairs, order_of[om], n, va, vb,
-                   kmode, flags, cells, next, s, next_zero, off_of[om] + LPT_BINS, off_of[om]);
+    launch_persist(cmax, best_g, np, best_blocks, pairs, ord.order[om], n, va, vb,
+                   kmode, flags, cells, next, s, next_zero, ord.off[om] + LPT_BINS, ord.off[om]);
     if (kt) kt->end(th, s);
     if (tune) {
         tune->last_g = best_g;
         tune->last_nwl = nwl_for(nw, best_g);
         tune->last_blocks = best_blocks;
-        tune->last_left = left;
+        tune->last_ci = ci;
+        tune->last_npi = npi;
     }
     if (cells_defer) {
         // the caller reads both words after its next synchronisation of the stream:
@@ -1189,13 +1226,12 @@ int64_t verify_pairs_batched(const uint64_t *pairs, int64_t n, const DevStrings 
 // longest first, then the persistent launch in the configuration the context timed for this
 // band size (the caller makes sure one is known: `cmax` words of band from the largest K),
 // no host read.  expect: how many pairs there may be (speed only).  flags[n .. cap) are not
-// written; the band-cell count and the window error word go to cells_out[0..1] (device), the
-// number of pairs the block filter left to *left_out (device).
+// written; the band-cell count and the window error word go to cells_out[0..1] (device).
 void verify_pairs_batched_streamed(const uint64_t *pairs, int64_t cap, const uint32_t *n_dev,
                                    const DevStrings &A, const DevStrings &B, int kmode, int cmax,
                                    uint8_t *flags, Workspace &ws, hipStream_t s, KTimer *kt,
                                    const VerifyTuning &tune, int force_lanes, int64_t expect,
-                                   unsigned long long **cells_out, const uint32_t **left_out) {
+                                   unsigned long long **cells_out) {
     const int np = verify_planes(std::max(A.bits, B.bits));
     VSet va = vset(A), vb = vset(B);
     cap = std::max<int64_t>(cap, 1);
@@ -1208,7 +1244,6 @@ void verify_pairs_batched_streamed(const uint64_t *pairs, int64_t cap, const uin
     *cells_out = cells;
     uint32_t *off = ws.get_n<uint32_t>(LPT_BINS + 1);
     int64_t *order = ws.get_n<int64_t>(cap);
-    if (left_out) *left_out = off + LPT_BINS;
     if (cmax > persist_max_c())
         throw Error(MJ_ECAPACITY, "threshold K above the batched verifier's band limit (K <= 2047)");
     const int nw = cmax + 1;
@@ -1222,7 +1257,9 @@ void verify_pairs_batched_streamed(const uint64_t *pairs, int64_t cap, const uin
     if (g == 0 || nwl_for(nw, g) == 0)
         throw Error(MJ_EINVAL, "no verifier configuration for this band size");
     const uint8_t *keep = nullptr;
-    if (force_lanes == 0 && block_filter_applies(std::max(A.bits, B.bits), cmax, expect)) {
+    const double mean = (double)(A.total + B.total) / (double)std::max<int64_t>(1, (int64_t)A.n + B.n);
+    if (force_lanes == 0 && tune.filter(ci, npi, mean) &&
+        block_filter_applies(std::max(A.bits, B.bits), cmax, expect)) {
         block_filter(pairs, cap, A, B, kmode, flags, s, n_dev);
         keep = flags;
     }
