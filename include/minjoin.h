@@ -173,16 +173,16 @@ mj_status mj_ctx_set_pair_test_pass(mj_ctx *ctx, int64_t tests);
 /* Joins with at least min_records records (default 2^23; 0: every join; -1: none) first
  * keep only the records that may share their key with another one -- those whose key's top
  * 32 bits occur twice, found with two radix passes over 8-byte elements (ordering them by
- * the key's top 16 bits into buckets) and a per-bucket LDS bitmap -- and group those alone.  A bucket of more than bucket_limit records (0: the default, 65,536) is
- * kept whole.  Results are the same either way (a record whose key occurs once forms no
+ * the key's top 16 bits into buckets) and a per-bucket LDS bitmap -- and group those alone.
+ * A bucket of more than bucket_limit records (0: the default, 65,536) is kept whole.  Results are the same either way (a record whose key occurs once forms no
  * group); the filter saves time when most records are unique.  EINVAL for a NULL context,
  * min_records < -1 or bucket_limit < 0. */
 mj_status mj_ctx_set_member_filter(mj_ctx *ctx, int64_t min_records, int32_t bucket_limit);
 /* Candidate emission by tile pairs (Alg. 3's pair tests within a bucket of D): in a join
  * whose groups of 64 records or more hold at least min_tile_pairs tile pairs of 64 x 64
  * records (default 32,768; 0: every join with such groups, none of which then groups in LDS
- * buckets; -1: none), those groups' record pairs are tested a tile pair per wavefront and the smaller groups' test by test; else
- * every group's test by test.  Results are the same either way (the same pairs are tested
+ * buckets; -1: none), those groups' record pairs are tested a tile pair per wavefront and the
+ * smaller groups' test by test; else every group's test by test.  Results are the same either way (the same pairs are tested
  * with the same filter); tile pairs save time when there are many of them.  A streamed
  * join follows the choice of the last join of its shape.  EINVAL for a NULL context or
  * min_tile_pairs < -1. */
@@ -264,7 +264,7 @@ mj_status mj_verify(mj_ctx *ctx, const mj_strings *strings, const mj_params *par
  * pair are the fixed small-call choice unless verify_lanes fixes them).  A call whose
  * strings, planes and pairs need more scratch than the array holds fails with
  * MJ_ECAPACITY before writing flags (about 12 bytes per string, 2-8 bits per symbol
- * (2 for 4 letters, 6 for 37), 8 bytes per pair, plus ~70 KB).  Calls on one GPU share
+ * (2 for 4 letters, 6 for 37), 8 bytes per pair, plus ~170 KB).  Calls on one GPU share
  * its array, which keeps the last call's contents: the library serialises them with a
  * lock and each returns only after its work on `stream` is complete, so calls from this
  * process never overlap on the device; calls that overlapped would race. */

@@ -13,7 +13,7 @@
 using namespace mj;
 
 // 64 MiB per device: enough for, e.g., 10^6 strings of 50 M DNA symbols in all and 10^6
-// pairs (planes 2 bits per symbol, 12 bytes per string, 8 bytes per pair, ~70 KB fixed).
+// pairs (planes 2 bits per symbol, 12 bytes per string, 8 bytes per pair, ~170 KB fixed).
 constexpr size_t NOALLOC_SCRATCH_BYTES = (size_t)64 << 20;
 static __device__ __align__(256) uint8_t scratch[NOALLOC_SCRATCH_BYTES];
 
