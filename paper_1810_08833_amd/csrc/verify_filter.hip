@@ -13,8 +13,11 @@
 // chunk lies before the band is on none of its diagonals.  (Whole chunks and symbols around X
 // only find more blocks, so no pair within K is rejected.)
 //
-// What bounds it: VALU and LDS issue, about 60 instructions per chunk, 9 lane operations a
-// symbol where the band recurrence takes 13 for each of its words.  The strings come in
+// What bounds it: LDS, busy 0.65 of the time (393 K pairs of 5,500 symbols, 1.29 ms), half of that
+// with bank conflicts of the table's byte writes and look-ups at random codes; VALU 0.41, about 60
+// instructions per chunk, 9 lane operations a symbol where the band recurrence takes 13 for each of
+// its words.  Short strings and pairs within K cost it more than it saves: the verifier times
+// whether to run it.  The strings come in
 // segments of eight chunks through LDS, 16 bytes a lane, loaded a pair ahead (the first
 // segment) or a segment ahead: with each lane loading its own chunk's words one chunk ahead
 // the kernel waited on memory nearly all the time (393 K pairs of 5,500 symbols: 5.6 ms).
