@@ -16,7 +16,8 @@ constexpr int BK_BITS_MAX = 16; // bucket bits (two radix passes)
 constexpr int DD_CAP = 4096, DD_LOG = 13, DD_AVG = 3072, DD_PARTS = 12;
 constexpr int DD_BITS_MAX = 14;  // bucket bits
 constexpr int DD_BATCH = 8;      // loads of a thread in flight
-constexpr int64_t DD_SWEEP = 1 << 18;
+constexpr int64_t DD_SWEEP = 1 << 20;  // of 1.5 M pairs of texts one bucket has 0.5 M candidates: with
+                                       // 2^18 that join took 7.70 ms, 7.28 with these
 
 inline int bits_for(int64_t n, int64_t avg) {  // 2^bits buckets of about avg
     int b = 0;
