@@ -924,14 +924,14 @@ __global__ __launch_bounds__(256) void k_dedup_gather(const uint64_t *__restrict
 }
 
 bool dedup_buckets_fit(int64_t expect, int32_t n_first, int32_t n_second) {
-    return dedup_plan(expect, n_first, n_second).fits;
+    return dedup_plan(expect, 0, n_first, n_second).fits;
 }
 
-const uint32_t *dedup_buckets(uint64_t *pairs, int64_t cap, int64_t expect,
+const uint32_t *dedup_buckets(uint64_t *pairs, int64_t cap, int64_t expect, int64_t distinct,
                               const unsigned long long *count, int32_t n_first, int32_t n_second,
                               uint32_t *over, Workspace &ws, hipStream_t s, uint64_t **result) {
     cap = std::max<int64_t>(cap, 1);
-    const DedupPlan plan = dedup_plan(expect, n_first, n_second);
+    const DedupPlan plan = dedup_plan(expect, distinct, n_first, n_second);
     const int bs = plan.bs, kb = plan.kb, bits = plan.bits;
     if (!plan.fits) throw Error(MJ_ECAPACITY, "pairs beyond the dedup's buckets");
     uint64_t *res = ws.get_n<uint64_t>(cap + 1);

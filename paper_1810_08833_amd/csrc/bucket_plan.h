@@ -51,20 +51,27 @@ inline int id_bits(int32_t count) {
 }
 
 // Pairs (first, second) of n_first and n_second strings as keys of kb bits, of which the top
-// `bits` number the bucket; expect pairs come, duplicates among them.  More buckets than keys
-// do not fit: the pairs are then mostly duplicates of a few, which the sort of kb bits (one or
-// two passes) spreads over the device and buckets would not.  A bucket's table holds the other
-// kb - bits <= 31 bits.
+// `bits` number the bucket; expect pairs come, about `distinct` (0: not known) different ones.
+// More buckets than keys do not fit: the pairs are then mostly duplicates of a few, which the sort
+// of kb bits (one or two passes) spreads over the device and buckets would not.  A bucket's table
+// holds the other kb - bits <= 31 bits.
 struct DedupPlan {
     int bs, kb, bits;
     bool fits;
 };
-inline DedupPlan dedup_plan(int64_t expect, int32_t n_first, int32_t n_second) {
+inline DedupPlan dedup_plan(int64_t expect, int64_t distinct, int32_t n_first, int32_t n_second) {
     DedupPlan p;
     p.bs = id_bits(n_second);
     p.kb = id_bits(n_first) + p.bs;
     p.bits = expect <= DD_CAP * 3 / 4 ? 0 : bits_for(expect, DD_AVG);
     p.fits = p.bits <= DD_BITS_MAX && p.bits <= p.kb && p.kb - p.bits <= 31;
+    // The lesser of two strings' ids is not evenly spread, and a bucket of more than DD_CAP distinct
+    // pairs goes by parts: half as many different pairs a bucket, or as many as one radix pass
+    // still makes (568 K pairs of 24,661 strings, hardly any twice: 0.20 -> 0.13 ms, 0.14 by the sort;
+    // 60 K of 8,000: 0.15 -> 0.09).  Halving them for duplicates too does not pay (protein, 10 M of
+    // 1.3 M: 0.31 -> 0.36 ms; long DNA, a second pass: 0.06 -> 0.08).
+    const int fine = std::max(std::min(8, bits_for(expect, DD_AVG / 2)), bits_for(2 * distinct, DD_AVG));
+    if (p.fits && p.bits > 0 && p.bits < fine) p.bits = std::min(std::min(fine, DD_BITS_MAX), p.kb);
     return p;
 }
 

@@ -449,7 +449,7 @@ static mj_pairs *run_join_by(mj_ctx *ctx, const mj_strings *strings, const mj_pa
         bool done = false;
         if (c0 > 0 && dedup_buckets_fit(c0, d.n, d.n) && !memo.dedup.skip()) {
             uint64_t *res = nullptr;
-            const uint32_t *u = dedup_buckets(cand, c0, c0, br.counter, d.n, d.n, br.dedup_over, ws, s, &res);
+            const uint32_t *u = dedup_buckets(cand, c0, c0, 0, br.counter, d.n, d.n, br.dedup_over, ws, s, &res);
             MJ_HIP(hipMemcpyAsync(ctx->pinned, u, 4, hipMemcpyDeviceToHost, s));
             MJ_HIP(hipMemcpyAsync(ctx->pinned + 1, br.dedup_over, 4, hipMemcpyDeviceToHost, s));
             MJ_HIP(hipStreamSynchronize(s));
@@ -778,7 +778,7 @@ static StreamedDev launch_streamed_main(mj_ctx *ctx, DevStrings &d, const Partit
         c0 = br.counter;
         bucket_pairs(br, d, cand, pl.ccap, pl.longs, s, kt);
         if (tm) tm->mark();  // 3 group + filter
-        u = pl.dedup ? dedup_buckets(cand, pl.ccap, pl.cexp, c0, d.n, d.n, br.dedup_over, ws, s, &uniq)
+        u = pl.dedup ? dedup_buckets(cand, pl.ccap, pl.cexp, pl.vexp, c0, d.n, d.n, br.dedup_over, ws, s, &uniq)
                      : dedup_pairs_streamed(cand, pl.ccap, c0, d.n, d.n, ws, s, &uniq);
     } else {
         sort_records(gkey, gval, pl.mcap, ws, s, ctx->pinned, M_dev);
@@ -1292,7 +1292,7 @@ static mj_pairs *run_search_streamed(mj_ctx *ctx, const mj_index *ix, DevStrings
     uint32_t *over = ws.zeroed(2, s);
     const bool dedup = dedup_buckets_fit((int64_t)cexp, qd.n, ix->n) && !h.dedup.skip();
     const uint32_t *u =
-        dedup ? dedup_buckets(cand, ccap, (int64_t)cexp, pr.counter, qd.n, ix->n, over, ws, s, &uniq)
+        dedup ? dedup_buckets(cand, ccap, (int64_t)cexp, (int64_t)vexp, pr.counter, qd.n, ix->n, over, ws, s, &uniq)
               : dedup_pairs_streamed(cand, ccap, pr.counter, qd.n, ix->n, ws, s, &uniq);
     tm.mark();  // 4 dedup
     uint8_t *flags = ws.get_n<uint8_t>(ccap + 4);

@@ -457,9 +457,10 @@ void bucket_pairs(const BucketRecords &r, const DevStrings &d, uint64_t *out, in
 // Whether about `expect` pairs can be deduplicated by buckets.
 bool dedup_buckets_fit(int64_t expect, int32_t n_first, int32_t n_second);
 // The distinct pairs of pairs[0 .. min(cap, *count)), sorted, in *result (workspace, room for
-// cap); returns the device address of their number.  *over is set (never cleared) when a bucket
-// does not fit.  The input is overwritten.
-const uint32_t *dedup_buckets(uint64_t *pairs, int64_t cap, int64_t expect,
+// cap); returns the device address of their number.  expect: about how many come, distinct: are
+// different (0: not known).  *over is set (never cleared) when a bucket does not fit.  The input is
+// overwritten.
+const uint32_t *dedup_buckets(uint64_t *pairs, int64_t cap, int64_t expect, int64_t distinct,
                               const unsigned long long *count, int32_t n_first, int32_t n_second,
                               uint32_t *over, Workspace &ws, hipStream_t s, uint64_t **result);
 

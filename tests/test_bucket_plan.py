@@ -13,9 +13,9 @@ MAIN = r"""
 #include "bucket_plan.h"
 #include <stdio.h>
 int main() {
-    long long e; int a, b;
-    while (scanf("%lld %d %d", &e, &a, &b) == 3) {
-        const mj::DedupPlan p = mj::dedup_plan(e, a, b);
+    long long e, u; int a, b;
+    while (scanf("%lld %lld %d %d", &e, &u, &a, &b) == 4) {
+        const mj::DedupPlan p = mj::dedup_plan(e, u, a, b);
         printf("%d %d %d %d\n", p.bs, p.kb, p.bits, p.fits ? 1 : 0);
     }
 }
@@ -35,17 +35,19 @@ def test_bucket_bits_stay_within_the_keys(tmp_path):
     src.write_text(MAIN)
     exe = str(tmp_path / "plan")
     subprocess.check_call(["g++", "-std=c++17", "-Wall", "-I", CSRC, str(src), "-o", exe])
-    cases = [(e, a, b) for e in EXPECT for a in COUNTS for b in COUNTS]
-    out = subprocess.run([exe], input="".join("%d %d %d\n" % c for c in cases), text=True,
+    cases = [(e, u, a, b) for e in EXPECT for u in {0, e // 9, e, 3 * e} for a in COUNTS for b in COUNTS]
+    out = subprocess.run([exe], input="".join("%d %d %d %d\n" % c for c in cases), text=True,
                          capture_output=True, check=True).stdout.split()
     got = [tuple(map(int, out[i:i + 4])) for i in range(0, len(out), 4)]
     assert len(got) == len(cases)
-    for (e, a, b), (bs, kb, bits, fits) in zip(cases, got):
-        assert bs == key_bits(b) and kb == key_bits(a) + bs, (e, a, b)
+    for (e, u, a, b), (bs, kb, bits, fits) in zip(cases, got):
+        assert bs == key_bits(b) and kb == key_bits(a) + bs, (e, u, a, b)
         if fits:
-            assert 0 <= bits <= min(kb, 14) and 0 <= kb - bits <= 31, (e, a, b, kb, bits)
+            assert 0 <= bits <= min(kb, 14) and 0 <= kb - bits <= 31, (e, u, a, b, kb, bits)
     # what ordinary calls have fits; two strings with more candidates than their keys' buckets do not
-    fit = {c: g[3] for c, g in zip(cases, got)}
+    fit = {(e, a, b): g[3] for (e, u, a, b), g in zip(cases, got) if u == 0}
+    # whether it fits does not depend on how many are different
+    assert all(g[3] == fit[(e, a, b)] for (e, u, a, b), g in zip(cases, got))
     assert fit[(1300000, 300000, 300000)] and fit[(3072, 2, 2)] and fit[(6144, 60, 60)]
     assert not fit[(1300000, 9, 9)]
     assert not fit[(1 << 24, 2, 2)]
